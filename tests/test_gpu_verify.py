@@ -62,6 +62,21 @@ def test_multiset_compare_known_relations(n, elem):
         assert v != 0 and (v & 1) == 0 and (v & 4) != 0                     # the scrambled sum still sees it
 
 
+@pytest.mark.parametrize("elem", [8, 4])
+@pytest.mark.parametrize("n", [3, 4, 5, 1023, 2047, 4097, 8191, 16383, 16386, 2 * 16384 - 1, 3 * 16384 + 4098])
+def test_multiset_compare_sees_the_ends_of_chunks_and_vectors(n, elem):
+    """One changed bit in the first and last words of every chunk and of the short last one, where
+    the 16-byte loads of the digest begin and end, at a base aligned to one word only."""
+    dt = np.uint64 if elem == 8 else np.uint32
+    a = wl.scrambled_stamp_values(n, elem)
+    assert _compare(a, a[::-1].copy(), elem, offset_words=1) == 0
+    places = {0, n - 1, n - 2} | {c + d for c in range(16384, n, 16384) for d in (-1, 0) if c + d < n}
+    for i in sorted(places):
+        changed = a.copy()
+        changed[i] ^= dt(1) << dt(8 * elem - 1)
+        assert _compare(a, changed, elem, offset_words=1) == 7, i   # sum, exclusive-or and scrambled sum
+
+
 CASES = [((70, 45, 33, 6), (2, 0, 3, 1), 8), ((8, 8, 8, 8, 8), (1, 3, 0, 2, 4), 4), ((5001, 477), (1, 0), 4),
          ((129, 1000), (0, 1), 8), ((33, 5, 7, 16, 3), (0, 3, 1, 4, 2), 4), ((1,), (0,), 8)]
 
