@@ -12,6 +12,8 @@ const void* tile_kernel_u64_256(int nreg, bool use_lds, int nt, bool align, bool
 const void* tile_kernel_u32_256(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
 const void* tile_kernel_u64_64(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
 const void* tile_kernel_u32_64(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
+const void* tile_kernel_lean_u64(int nreg, int nt);
+const void* tile_kernel_lean_u32(int nreg, int nt);
 const void* tile_kernel_big_u64(int nreg, int nt, bool align, bool acc, bool vec2);
 const void* tile_kernel_big_u32(int nreg, int nt, bool align, bool acc, bool vec2);
 
@@ -102,6 +104,8 @@ static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_align
     const int pol = tile_launch_policy(plan, acc, sector_aligned_out);
     const int nt = pol == 2 ? 2 : (pol == 3 ? 1 : (pol == 4 ? 3 : 0));  // template parameter NT
     const bool align = plan.align_out;
+    if (plan.lean && !acc && !plan.loads_first)
+        return plan.elem == 8 ? tile_kernel_lean_u64(plan.nreg, nt) : tile_kernel_lean_u32(plan.nreg, nt);
     if (plan.big) {
         if (!plan.use_lds || plan.loads_first || plan.threads != 256) return nullptr;
         return plan.elem == 8 ? tile_kernel_big_u64(plan.nreg, nt, align, acc, plan.vec2)

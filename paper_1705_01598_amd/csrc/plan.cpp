@@ -273,11 +273,12 @@ static bool finish_candidate(const Canonical& c, int elem, Candidate* cd) {
     // workgroups per compute unit); a single slot cannot keep enough bytes in flight, and
     // beyond twelve slots fewer workgroups fit and LDS padding runs out of room.  4-byte
     // elements moved singly want more slots: their tiles are half the bytes (table smoothed
-    // by hand from a fit over every candidate of 230 4-byte cases; both halves of the sample
-    // gain 1 % over the flatter table used before).
+    // 24 and 32 slots were 1.1 and 1.2 before the kernel's form without masks made them 8 and 20 %
+    // faster: picks on 4-byte tensors of 64 MB and more 95.2 -> 95.8 % of the best candidate, a
+    // ragged rank-5 one of 536 MB 299 -> 264 us.
     static const int kSlots[10] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
     static const double kWeight8[10] = {1.4, 1.05, 0.95, 0.95, 1.1, 1.0, 1.06, 1.1, 1.16, 1.2};
-    static const double kWeight4[10] = {1.4, 1.2, 0.85, 0.85, 0.8, 0.85, 0.9, 1.0, 1.1, 1.2};
+    static const double kWeight4[10] = {1.4, 1.2, 0.85, 0.85, 0.8, 0.85, 0.9, 1.0, 1.0, 1.08};
     // The LDS-free row copy keeps few registers per slot and has no barrier: four to six
     // slots do better there than the LDS-staged table says when they come from more rows
     // (measured on every candidate of the benchmark cases that keep dim 0 in front; making a
@@ -884,9 +885,11 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         if ((int64_t)lds_elems * elem > kMaxLdsBytes) return TPERM_ERR_KERNEL;
         if (lds_elems + 64u > 0xFFFFu) return TPERM_ERR_KERNEL;  // LDS slots are kept in 16 bits
     }
+    // one spare element behind the image takes what the slots beyond the tile write
+    if (cand.use_lds) lds_elems += 1u;
     d.lds_elems = lds_elems;
     if (align_out) d.oa.lstride_b = d.out_order[0].lstride;
-    d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)lds_elems * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;
+    d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)(lds_elems - 1u) * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;
     // grid_mode values >= 2 carry the group size: mode 2 + log2(group) (2 -> groups of 1)
     d.grid_mode = grid_mode >= 2 ? 2u : (uint32_t)grid_mode;
     d.group_log2 = grid_mode >= 2 ? (uint32_t)(grid_mode - 2) : 0u;
@@ -980,6 +983,8 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         // (measured per case over all benchmark sets; see tile_kernel)
         plan->loads_first = cand.aligned && cand.use_lds && nreg <= 6 && !plan->vec2 && !align_out && !opts.big;
     }
+    plan->lean = cand.use_lds && threads == 256 && !plan->vec2 && !align_out && !opts.big && nreg_final >= 6 &&
+                 nreg_final <= 16 && c.volume * elem < kLeanBytes;
     plan->lds_pad = pad;
     plan->align_out = align_out;
     plan->lds_bytes = (int)((int64_t)lds_elems * elem);

@@ -21,6 +21,10 @@ constexpr int64_t kMaxLdsBytes = 64 * 1024;
 constexpr int kDefaultWindow = 1;
 constexpr int kDefaultWindowIn = 0;
 constexpr int kDefaultThreads = 256;
+// Tensors below this size take the lean form of the tile kernel where it exists (measured on both
+// sides of the line, see the kernel: +3 to +11 % below 20 MB, +0 to +9 % up to 40 MB, level from
+// there to 80 MB, then losing).
+constexpr int64_t kLeanBytes = 40 * 1000 * 1000;
 constexpr int kDefaultLdsBuffers = 1;
 // Groups of 32 consecutive tiles are dealt to the XCDs in turn: tiles that are neighbours
 // along the output run then share an L2, which merges the cache lines they both write
@@ -94,6 +98,7 @@ struct Plan {
     int grid_mode = 0;
     int blocks_per_cu = 0;   // cap on resident workgroups per compute unit (0 = none)
     bool vec2 = false;         // 4-byte elements move in pairs; needs 8-byte aligned pointers
+    bool lean = false;         // small tensor, 6 to 16 slots per thread: the kernel form with fewer instructions per tile
     bool loads_first = false;  // next tile's loads are issued before this tile's stores
     int cache_policy = 1;    // 1 = cached, 2 = nontemporal loads and stores, 3 = nontemporal stores, 4 = nontemporal loads
     bool big = false;        // tensor of 4 GiB or more: tiles describe their buffers from their own origin

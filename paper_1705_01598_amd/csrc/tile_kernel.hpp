@@ -91,6 +91,7 @@ struct MajorPos {
     uint32_t rem_a, rem_b;   // remaining extent of the split dims in this tile
     uint32_t lo_b, span_b;   // line-aligned windows: coordinates lo_b <= x < lo_b + span_b
                              // of split dim B exist in this tile
+    uint32_t full;           // 1: every coordinate of the tile exists (no edge of the tensor in it)
 };
 
 // One lane's term of the major sums, kept in registers for the whole kernel.
@@ -99,7 +100,7 @@ struct MajorLane {
     uint32_t ext, stride_in, stride_out;
 };
 
-template <typename D>
+template <bool NO_MASKS, typename D>
 __device__ __forceinline__ MajorPos major_position(const D& d, const MajorLane& ml, uint32_t b) {
     const uint32_t q = fdiv(b, ml.cum);
     const uint32_t c = q - fdiv(q, ml.ext_div) * ml.ext;
@@ -110,6 +111,9 @@ __device__ __forceinline__ MajorPos major_position(const D& d, const MajorLane& 
     p.out = read_lane(sum_out, 15);
     tile_remaining(d, [&](uint32_t lane) { return read_lane(c, lane); }, &p.rem_a, &p.rem_b, &p.lo_b);
     p.span_b = p.rem_b > p.lo_b ? p.rem_b - p.lo_b : 0u;
+    // (without split dims the tile extents are 0 and the remaining ones are not, unless the tile
+    // does not exist)
+    p.full = !NO_MASKS ? 0u : p.rem_a != 0u && p.rem_b != 0u && p.rem_a >= d.split_tile[0] && p.rem_b >= d.split_tile[1] && p.lo_b == 0u ? 1u : 0u;
     return p;
 }
 
@@ -212,7 +216,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
 // and the dropped-offset masking work as before; nbytes is then TPERM_BIG_RANGE, the range one
 // such description covers.  With line-aligned windows the halo origin in front of the tensors
 // moves along with the tile's.  LDS-staged tiles in every form, stores first.
-template <typename T, int NREG, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST, bool VEC2, bool BIG = false>
+template <typename T, int NREG, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST, bool VEC2, bool BIG = false, bool LEAN = false>
 __global__ void __launch_bounds__(THREADS)
 tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_arg, uint32_t nbytes_arg) {
     static_assert(!BIG || (USE_LDS && !LOADS_FIRST), "large tensors: LDS-staged tiles, stores first");
@@ -229,6 +233,21 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // holds the odd end of an input row, or a window clipped by the ends of an output row,
     // moves that side element by element instead (a wave-uniform choice per tile and side).
     constexpr bool PAIRWIN = VEC2 && ALIGN;
+    // NO_MASKS: fewer instructions per tile.  Every slot writes and reads the LDS image, whether its
+    // element exists in this tile or not: the place of an element that does not exist is only read
+    // by stores which are dropped, and slots that no tile uses write to spare elements behind the
+    // image.  A tile without an edge of the tensor issues its loads and stores without looking at
+    // masks (a wave-uniform choice).  What it is for: with two wavefronts per SIMD the masked form
+    // spends 43 % of its time issuing instructions on a 27 MB tensor of 12 slots per thread (a dozen
+    // vector and eight scalar ones per slot and tile); this form needs two.  Measured (same plan,
+    // masked / this form, geometric means over 1900 candidate plans of 141 seeded shapes): 6 to 16
+    // slots 1.03-1.11 on tensors below 20 MB, 1.00-1.09 at 20-40 MB, 0.92-1.02 above 160 MB, where
+    // memory is the bound and workgroups that run apart faster merge fewer of the lines they share
+    // (partial line writes on a 536 MB tensor: 8 % masked, 16 % without); 24 and 32 slots, which
+    // leave one workgroup per SIMD slot, 1.04-1.29 almost throughout.  Hence the LEAN variants for
+    // small tensors, and 24 and 32 slots always.
+    constexpr bool NO_MASKS = USE_LDS && !VEC2 && !ALIGN && !ACC && !BIG && THREADS == 256 && (LEAN || NREG >= 24);
+    static_assert(!LEAN || NO_MASKS, "the lean form is a plain LDS-staged one of 256 threads");
     typedef typename std::conditional<sizeof(T) == 4, uint64_t, Pair64>::type pair_t;
     typedef Elem<typename std::conditional<VEC2, pair_t, T>::type, NT> io;
     typedef Elem<T, NT> io1;  // single elements
@@ -382,12 +401,14 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
                     wr_off[j] += oa.line_elems;
                     loff_o[jj] += oa.line_elems * oa.lstride_b;
                 }
-                wr_off[j] = used_w ? wr_off[j] * (uint32_t)sizeof(T) : 0u;
-                rd_off[j] = used_r ? rd_off[j] * (uint32_t)sizeof(T) : 0u;
+                wr_off[j] = used_w ? wr_off[j] * (uint32_t)sizeof(T) : (NO_MASKS ? kDroppedOffset : 0u);
+                rd_off[j] = used_r ? rd_off[j] * (uint32_t)sizeof(T) : (NO_MASKS ? kDroppedOffset : 0u);
                 wr_mask[j] = used_w ? wr_mask[j] : 0xFFFFFFFFu;  // coordinates no remaining
                 if (USE_LDS) {                                    // extent exceeds: unused
                     rd_mask[j] = used_r ? rd_mask[j] : 0xFFFFFFFFu;
-                    lds_pos[j] = (used_r ? loff_i[jj] : 0u) | ((used_w ? loff_o[jj] : 0u) << 16);
+                    // NO_MASKS: what unused slots write goes to the spare element behind the image
+                    const uint32_t spare = NO_MASKS ? lds_elems - 1u : 0u;
+                    lds_pos[j] = (used_r ? loff_i[jj] : spare) | ((used_w ? loff_o[jj] : 0u) << 16);
                 } else {
                     rd_mask[j] = wr_mask[j];
                 }
@@ -400,7 +421,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     uint32_t b = tile_of(walk, block, grid, it);
     reg_t v[NREG];
     MajorPos pos, nxt;
-    pos.in = pos.out = pos.rem_a = pos.rem_b = pos.lo_b = pos.span_b = 0;
+    pos.in = pos.out = pos.rem_a = pos.rem_b = pos.lo_b = pos.span_b = pos.full = 0;
     nxt = pos;
     // does read-side slot j exist in tile t
     auto read_ok = [&](int j, const MajorPos& t) {
@@ -436,12 +457,17 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
                 return;
             }
         }
+        if (NO_MASKS && t.full != 0u) {
+#pragma unroll
+            for (int j = 0; j < NREG; ++j) v[j] = io::load(rsrc_in, rd_off[j], soff);
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < NREG; ++j)
             v[j] = io::load(rsrc_in, read_ok(j, t) ? rd_off[j] : kDroppedOffset, soff);
     };
     if (b < walk.num_tiles) {
-        pos = major_position(walk, ml, b);
+        pos = major_position<NO_MASKS>(walk, ml, b);
         load_tile(pos);
     }
     // As many dropped stores as a tile has real ones: every pass through the loop below then
@@ -456,7 +482,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // the position of the tile after this one is worked out while the loads are in flight
     uint32_t bn = tile_of(walk, block, grid, it + 1);
     const MajorPos no_tile = nxt;  // all zero: no slot is valid
-    if (bn < walk.num_tiles) nxt = major_position(walk, ml, bn);
+    if (bn < walk.num_tiles) nxt = major_position<NO_MASKS>(walk, ml, bn);
     const bool two_buffers = lds_buffers == 2u;
     // line-aligned windows: phase of the output base pointer within a 128-byte line
     const uint32_t line_mask = ALIGN ? oa.line_elems - 1u : 0u;
@@ -502,23 +528,24 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
             // tile is enough: a wave can only overwrite an image two tiles later, after
             // the barrier of the tile in between
             lds_t* img = lds + ((two_buffers && (it & 1u)) ? lds_elems : 0u);
+            auto put = [&](int j) {
+                const uint32_t at = lds_pos[j] & 0xFFFFu;
+                if constexpr (VEC2) {
+                    // neighbours along input dim 0 are neighbours in the image
+                    if constexpr (sizeof(T) == 4) {
+                        img[at] = v[j].x;
+                        if (!odd_row_end(pos) || read_ok_second(j, pos)) img[at + 1u] = v[j].y;
+                    } else {
+                        img[at] = lds_t{v[j].x, v[j].y};
+                        img[at + 1u] = lds_t{v[j].z, v[j].w};
+                    }
+                } else {
+                    img[at] = v[j];
+                }
+            };
 #pragma unroll
             for (int j = 0; j < NREG; ++j)
-                if (read_ok(j, pos)) {
-                    if constexpr (VEC2) {
-                        // neighbours along input dim 0 are neighbours in the image
-                        if constexpr (sizeof(T) == 4) {
-                            img[lds_pos[j] & 0xFFFFu] = v[j].x;
-                            if (!odd_row_end(pos) || read_ok_second(j, pos))
-                                img[(lds_pos[j] & 0xFFFFu) + 1u] = v[j].y;
-                        } else {
-                            img[lds_pos[j] & 0xFFFFu] = lds_t{v[j].x, v[j].y};
-                            img[(lds_pos[j] & 0xFFFFu) + 1u] = lds_t{v[j].z, v[j].w};
-                        }
-                    } else {
-                        img[lds_pos[j] & 0xFFFFu] = v[j];
-                    }
-                }
+                if (NO_MASKS || read_ok(j, pos)) put(j);
             __syncthreads();
             if (ALIGN) {
 #pragma unroll
@@ -531,27 +558,29 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
                             w[j].y = img[at + oa.lstride_b];
                         }
                     } else if constexpr (!VEC2) {
-                        if (write_at(j) != kDroppedOffset) w[j] = img[at];
+                        if (NO_MASKS || write_at(j) != kDroppedOffset) w[j] = img[at];
                     }
                 }
             } else {
+                auto get = [&](int j) {
+                    const uint32_t at = lds_pos[j] >> 16;
+                    if constexpr (VEC2) {
+                        // neighbours along output dim 0 are pair_lstride apart
+                        if constexpr (sizeof(T) == 4) {
+                            w[j].x = img[at];
+                            w[j].y = img[at + pair_lstride];
+                        } else {
+                            const lds_t lo = img[at];
+                            const lds_t hi = img[at + pair_lstride];
+                            w[j] = reg_t{lo.x, lo.y, hi.x, hi.y};
+                        }
+                    } else {
+                        w[j] = img[at];
+                    }
+                };
 #pragma unroll
                 for (int j = 0; j < NREG; ++j)
-                    if (write_at(j) != kDroppedOffset) {
-                        if constexpr (VEC2) {
-                            // neighbours along output dim 0 are pair_lstride apart
-                            if constexpr (sizeof(T) == 4) {
-                                w[j].x = img[lds_pos[j] >> 16];
-                                w[j].y = img[(lds_pos[j] >> 16) + pair_lstride];
-                            } else {
-                                const lds_t lo = img[lds_pos[j] >> 16];
-                                const lds_t hi = img[(lds_pos[j] >> 16) + pair_lstride];
-                                w[j] = reg_t{lo.x, lo.y, hi.x, hi.y};
-                            }
-                        } else {
-                            w[j] = img[lds_pos[j] >> 16];
-                        }
-                    }
+                    if (NO_MASKS || write_at(j) != kDroppedOffset) get(j);
             }
         } else {
 #pragma unroll
@@ -590,8 +619,13 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
             }
         }
         if (!stored) {
+            if (NO_MASKS && pos.full != 0u) {
 #pragma unroll
-            for (int j = 0; j < NREG; ++j) io::store(w[j], rsrc_out, write_at(j), soff_out);
+                for (int j = 0; j < NREG; ++j) io::store(w[j], rsrc_out, wr_off[j], soff_out);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NREG; ++j) io::store(w[j], rsrc_out, write_at(j), soff_out);
+            }
         }
         if (!LOADS_FIRST) issue_next_loads();
         b = bn;
@@ -599,7 +633,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
         ++it;
         bn = tile_of(walk, block, grid, it + 1);
         nxt = no_tile;
-        if (bn < walk.num_tiles) nxt = major_position(walk, ml, bn);
+        if (bn < walk.num_tiles) nxt = major_position<NO_MASKS>(walk, ml, bn);
         if (USE_LDS && !two_buffers) __syncthreads();  // all waves are done reading the image
     }
 }

@@ -1,0 +1,44 @@
+"""Forms of the tile kernel that a rule on size picks, at the sizes where they can go wrong: tiles
+that exactly fill their slots and tiles one element short, edges of the tensor on either split dim
+and on both, tensors smaller than one tile.  Bit-exact against the CPU oracle, with guard bands."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1705_01598_amd import binding as B
+from paper_1705_01598_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+from gpu_util import GuardedOut, np_uint, to_device  # noqa: E402
+
+
+def _run(dims, perm, elem, **kw):
+    case = wl.make_case(0, 91, dims, perm, elem)
+    a = wl.bitpattern_values(case)
+    plan = B.tperm_plan_create_ex(dims, perm, elem, **kw)
+    a_dev, out = to_device(a), GuardedOut(case.volume, elem)
+    B.tperm_execute(plan, a_dev.data_ptr(), out.ptr, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert np.array_equal(np_uint(out.view().cpu().numpy()), oracle.transpose(a, dims, perm)), B.info_dict(plan.describe())
+    assert out.guards_intact()
+    return plan.describe()
+
+
+# tile of t0 x t1 elements; slots per thread the kernel is instantiated for: 6, 8, 12, 16, 24, 32
+@pytest.mark.parametrize("elem", [4, 8])
+@pytest.mark.parametrize("t0,t1,nreg", [(48, 32, 6), (61, 25, 6), (64, 32, 8), (43, 43, 8), (48, 64, 12), (61, 50, 12),
+                                        (64, 64, 16), (63, 65, 16), (96, 64, 24), (77, 79, 24), (89, 71, 32)])
+def test_form_without_masks_on_small_tensors(t0, t1, nreg, elem):
+    for i, (d0, d1) in enumerate([(t0, t1), (2 * t0, 3 * t1), (3 * t0 + 1, 2 * t1), (2 * t0, 2 * t1 - 1), (2 * t0 - 1, t1 + 1)]):
+        info = _run((d0, 3, d1), (2, 0, 1) if i % 2 else (2, 1, 0), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1,
+                    tile_out=t1, vec2=1, align_out=1, cache_policy=1 + i % 4, lds_buffers=1 + i % 2,
+                    window_in=(0, 2)[i % 2], window_out=(0, 3)[i // 2 % 2])
+        assert info.nreg <= nreg
+
+
+@pytest.mark.parametrize("elem", [4, 8])
+def test_both_sides_of_the_small_tensor_line(elem):
+    """The same tile just below and just above 40 MB, where the form changes."""
+    for d2 in (40_000_000 // elem // (61 * 50), 40_000_000 // elem // (61 * 50) + 1):
+        _run((61, 50, d2), (1, 0, 2), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=61, k=1, tile_out=50, vec2=1)
