@@ -244,9 +244,11 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // slots 1.03-1.11 on tensors below 20 MB, 1.00-1.09 at 20-40 MB, 0.92-1.02 above 160 MB, where
     // memory is the bound and workgroups that run apart faster merge fewer of the lines they share
     // (partial line writes on a 536 MB tensor: 8 % masked, 16 % without); 24 and 32 slots, which
-    // leave one workgroup per SIMD slot, 1.04-1.29 almost throughout.  Hence the LEAN variants for
-    // small tensors, and 24 and 32 slots always.
-    constexpr bool NO_MASKS = USE_LDS && !VEC2 && !ALIGN && !ACC && !BIG && THREADS == 256 && (LEAN || NREG >= 24);
+    // leave few wavefronts per SIMD, 1.04-1.29 almost throughout.  Hence the LEAN variants for small
+    // tensors, and 24 and 32 slots always: accumulating (a ragged rank-4 fp32 tensor of 497 MB 432 ->
+    // 327 us with the tiles picked for it now) and beyond 4 GiB (a ragged rank-5 one of 4.3 GB 2.72 ->
+    // 2.16 ms) too.
+    constexpr bool NO_MASKS = USE_LDS && !VEC2 && !ALIGN && THREADS == 256 && (LEAN || NREG >= 24);
     static_assert(!LEAN || NO_MASKS, "the lean form is a plain LDS-staged one of 256 threads");
     typedef typename std::conditional<sizeof(T) == 4, uint64_t, Pair64>::type pair_t;
     typedef Elem<typename std::conditional<VEC2, pair_t, T>::type, NT> io;
@@ -598,7 +600,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
             reg_t old[NREG];
 #pragma unroll
             for (int j = 0; j < NREG; ++j)
-                old[j] = io::load(rsrc_out, write_at(j), soff_out);
+                old[j] = io::load(rsrc_out, NO_MASKS && pos.full != 0u ? wr_off[j] : write_at(j), soff_out);
 #pragma unroll
             for (int j = 0; j < NREG; ++j) w[j] = io::add(old[j], w[j]);
         }
@@ -639,7 +641,8 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
 }
 
 // Kernel pointer for one element type and workgroup size; nullptr if the combination is
-// not instantiated.  Accumulating kernels (ACC) exist for 256 threads, cached policy.
+// not instantiated.  Accumulating kernels (ACC) exist for 256 threads: cached, nontemporal loads,
+// nontemporal loads and stores; with line-aligned windows cached only.
 template <typename T, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST = false, bool VEC2 = false, bool BIG = false>
 static const void* tile_kernel_ptr(int nreg) {
     switch (nreg) {
@@ -691,9 +694,9 @@ static const void* tile_kernel_select(int nreg, bool use_lds, int nt, bool align
                 return nullptr;
             }
         }
-        if (nt == 3) {
+        if (nt == 3 && !acc) {
             // nontemporal loads only: plain stores-first forms
-            if (acc || loads_first) return nullptr;
+            if (loads_first) return nullptr;
             if (vec2) return use_lds && !align ? tile_kernel_ptr<T, 256, true, 3, false, false, false, true>(nreg) : nullptr;
             if (align) return use_lds ? tile_kernel_ptr<T, 256, true, 3, true, false>(nreg) : nullptr;
             return use_lds ? tile_kernel_ptr<T, 256, true, 3, false, false>(nreg)
@@ -711,10 +714,19 @@ static const void* tile_kernel_select(int nreg, bool use_lds, int nt, bool align
     if constexpr (THREADS == 256) {
         if (align && !use_lds) return nullptr;
         if (acc) {
-            if (nt != 0) return nullptr;
-            if (align) return tile_kernel_ptr<T, 256, true, 0, true, true>(nreg);
-            return use_lds ? tile_kernel_ptr<T, 256, true, 0, false, true>(nreg)
-                           : tile_kernel_ptr<T, 256, false, 0, false, true>(nreg);
+            if (align) return nt == 0 ? tile_kernel_ptr<T, 256, true, 0, true, true>(nreg) : nullptr;
+            switch (nt) {
+                case 0:
+                    return use_lds ? tile_kernel_ptr<T, 256, true, 0, false, true>(nreg)
+                                   : tile_kernel_ptr<T, 256, false, 0, false, true>(nreg);
+                case 2:
+                    return use_lds ? tile_kernel_ptr<T, 256, true, 2, false, true>(nreg)
+                                   : tile_kernel_ptr<T, 256, false, 2, false, true>(nreg);
+                case 3:
+                    return use_lds ? tile_kernel_ptr<T, 256, true, 3, false, true>(nreg)
+                                   : tile_kernel_ptr<T, 256, false, 3, false, true>(nreg);
+                default: return nullptr;
+            }
         }
         if (align) {
             if (nt == 1) return tile_kernel_ptr<T, 256, true, 1, true, false>(nreg);

@@ -42,3 +42,27 @@ def test_both_sides_of_the_small_tensor_line(elem):
     """The same tile just below and just above 40 MB, where the form changes."""
     for d2 in (40_000_000 // elem // (61 * 50), 40_000_000 // elem // (61 * 50) + 1):
         _run((61, 50, d2), (1, 0, 2), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=61, k=1, tile_out=50, vec2=1)
+
+
+@pytest.mark.parametrize("large", [0, 1])
+@pytest.mark.parametrize("elem", [4, 8])
+@pytest.mark.parametrize("policy", [1, 2, 3, 4])
+def test_accumulation_under_every_cache_policy(policy, elem, large):
+    """Staged tiles with edges on both sides and the LDS-free row copy, at output pointers on and off a
+    sector boundary (which changes the policy of the kernel that runs)."""
+    ftype = np.float64 if elem == 8 else np.float32
+    for dims, perm, kw in [((70, 45, 33), (2, 0, 1), dict(kernel_class=B.KERNEL_PACKED, m=1, tile_in=33, k=1, tile_out=16)),
+                           ((64, 40, 48), (1, 2, 0), dict(kernel_class=B.KERNEL_PACKED, m=1, tile_in=32, k=1, tile_out=40)),
+                           ((48, 21, 34), (0, 2, 1), {} if large else dict(kernel_class=B.KERNEL_ROWCOPY))]:
+        vol = int(np.prod(dims))
+        rng = np.random.default_rng(vol + policy)
+        a, b = (rng.standard_normal(vol).astype(ftype) for _ in range(2))
+        for offset in (0, 1):
+            plan = B.tperm_plan_create_ex(dims, perm, elem, cache_policy=policy, large=large, vec2=1, pair_elems=1, **kw)
+            a_dev, out = to_device(a), GuardedOut(vol, elem, offset)
+            out.view().copy_(to_device(b))
+            B.tperm_execute_accumulate(plan, a_dev.data_ptr(), out.ptr, torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            ref = b + oracle.transpose(a, dims, perm)      # one IEEE addition per element: exact
+            assert np.array_equal(np_uint(out.view().cpu().numpy()), np_uint(ref)), (dims, perm, offset)
+            assert out.guards_intact()
