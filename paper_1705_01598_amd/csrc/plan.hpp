@@ -25,6 +25,9 @@ constexpr int kDefaultThreads = 256;
 // sides of the line, see the kernel: +3 to +11 % below 20 MB, +0 to +9 % up to 40 MB, level from
 // there to 80 MB, then losing).
 constexpr int64_t kLeanBytes = 40 * 1000 * 1000;
+// Tensors below this size read with cached loads unless they are line-aligned on both sides (see
+// build_tile_plan).
+constexpr int64_t kCachedLoadBytes = (int64_t)16 << 20;
 constexpr int kDefaultLdsBuffers = 1;
 // Groups of 32 consecutive tiles are dealt to the XCDs in turn: tiles that are neighbours
 // along the output run then share an L2, which merges the cache lines they both write
