@@ -978,7 +978,8 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         plan->blocks_per_cu = std::max(2, std::min(8, bpc));
         // aligned windows write whole lines, whatever the granule of the rows
         const bool store_nt = cand.store_nt || align_out;
-        // Line-aligned input rows against an output that is sector-aligned only: nontemporal loads
+        // Line-aligned input rows against an output that is sector-aligned only (or written in
+        // line-aligned windows): nontemporal loads
         // pay off on large tensors, but what they read neither stays in the 256 MB memory-side cache
         // nor serves the neighbouring tile from L2.  Below 16 MiB cached loads are as fast or
         // faster wherever the input comes from (us with nontemporal -> cached loads, input from HBM /

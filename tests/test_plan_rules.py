@@ -1,0 +1,44 @@
+"""Rules of the planner that depend on a size, on both sides of their lines, and the binding's
+argument arrays.  Host only."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1705_01598_amd import binding as B
+
+
+@pytest.mark.parametrize("d0,d1,elem,policy", [
+    (1024, 2040, 8, 3), (1024, 2056, 8, 2),                        # 16 MiB lies at 1024 x 2048 elements of 8 bytes
+    (2048, 2032, 4, 3), (2048, 2064, 4, 2),
+])
+def test_cached_loads_below_16_mib(d0, d1, elem, policy):
+    """Line-aligned input rows, output rows on 64-byte boundaries."""
+    info = B.tperm_plan_create_ex((d0, d1), (1, 0), elem, kernel_class=B.KERNEL_TILED, m=1, tile_in=128 // elem, k=1,
+                                  tile_out=64, align_out=1, vec2=1).describe()
+    assert info.cache_policy == policy, B.info_dict(info)
+    # line-aligned on both sides: nontemporal loads at any size
+    assert B.tperm_plan_create((512, 512), (1, 0), 8).describe().cache_policy == 2
+
+
+@pytest.mark.parametrize("elem", [4, 8])
+def test_index_maps_of_the_slot_counts_without_masks(elem):
+    """Tiles of 6 to 32 slots per thread with edges on both split dims: the map of positions (and the
+    spare element behind the LDS image) stays inside the image and the tensors."""
+    for t0, t1 in ((48, 32), (61, 25), (64, 64), (77, 79), (89, 71)):
+        dims, perm = (2 * t0 - 1, 3, t1 + 1), (2, 0, 1)
+        plan = B.tperm_plan_create_ex(dims, perm, elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1, vec2=1,
+                                      align_out=1, lds_buffers=2)
+        ref = oracle.transpose(np.arange(int(np.prod(dims)), dtype=np.int64), dims, perm)
+        assert np.array_equal(B.tperm_plan_index_map(plan), ref)
+
+
+def test_argument_arrays_are_taken_by_value():
+    dims = [6, 5, 4]
+    a = B.tperm_plan_create(dims, [2, 0, 1], 8)
+    dims[0] = 7                                            # a list changed after the call names another problem
+    b = B.tperm_plan_create(dims, np.array([2, 0, 1]), 8)
+    c = B.tperm_plan_create(tuple(np.array([6, 5, 4])), (2, 0, 1), 8)
+    assert [B.tperm_plan_describe(p).volume for p in (a, b, c)] == [120, 140, 120]
+    for bad in ([6, 5, 0], []):
+        with pytest.raises((B.TpermError, ValueError)):
+            B.tperm_plan_create(bad, [2, 0, 1] if len(bad) != 0 else [], 8)
