@@ -109,7 +109,7 @@ static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_align
     const int pol = tile_launch_policy(plan, acc, sector_aligned_out);
     const int nt = pol == 2 ? 2 : (pol == 3 ? 1 : (pol == 4 ? 3 : 0));  // template parameter NT
     const bool align = plan.align_out;
-    if (plan.lean && !acc && !plan.loads_first)
+    if (runs_lean(plan, acc))
         return plan.elem == 8 ? tile_kernel_lean_u64(plan.nreg, nt) : tile_kernel_lean_u32(plan.nreg, nt);
     if (plan.big) {
         if (!plan.use_lds || plan.loads_first || plan.threads != 256) return nullptr;

@@ -885,11 +885,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         if ((int64_t)lds_elems * elem > kMaxLdsBytes) return TPERM_ERR_KERNEL;
         if (lds_elems + 64u > 0xFFFFu) return TPERM_ERR_KERNEL;  // LDS slots are kept in 16 bits
     }
-    // one spare element behind the image takes what the slots beyond the tile write
-    if (cand.use_lds) lds_elems += 1u;
-    d.lds_elems = lds_elems;
     if (align_out) d.oa.lstride_b = d.out_order[0].lstride;
-    d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)(lds_elems - 1u) * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;
     // grid_mode values >= 2 carry the group size: mode 2 + log2(group) (2 -> groups of 1)
     d.grid_mode = grid_mode >= 2 ? 2u : (uint32_t)grid_mode;
     d.group_log2 = grid_mode >= 2 ? (uint32_t)(grid_mode - 2) : 0u;
@@ -905,6 +901,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
     // and even tile extents along both dims (all other strides are then even too).  Half
     // the global memory instructions per byte; the LDS image and its padding stay as laid
     // out above, in single elements.
+    const bool padded = lds_elems > d.tile_vol;
     int nreg_final = nreg;
     plan->vec2 = false;
     {
@@ -962,6 +959,13 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         if ((std::max(span_in, span_out) + 2u + (uint64_t)line_elems) * (uint64_t)elem > (uint64_t)TPERM_BIG_RANGE)
             return TPERM_ERR_KERNEL;
     }
+    plan->lean = cand.use_lds && threads == 256 && !plan->vec2 && !align_out && !opts.big && nreg_final >= 6 &&
+                 nreg_final <= 16 && c.volume * elem < kLeanBytes;
+    plan->spare = d.tile_vol < (uint32_t)nreg_final * (uint32_t)threads &&
+                  tile_form_without_masks(nreg_final, threads, cand.use_lds, align_out, plan->vec2, plan->lean);
+    if (plan->spare && !padded) ++lds_elems;
+    d.lds_elems = lds_elems;
+    d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)lds_elems * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;
     plan->tile = d;
     plan->cand = cand;
     plan->kclass = cand.kclass;
@@ -994,8 +998,6 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         // (measured per case over all benchmark sets; see tile_kernel)
         plan->loads_first = cand.aligned && cand.use_lds && nreg <= 6 && !plan->vec2 && !align_out && !opts.big;
     }
-    plan->lean = cand.use_lds && threads == 256 && !plan->vec2 && !align_out && !opts.big && nreg_final >= 6 &&
-                 nreg_final <= 16 && c.volume * elem < kLeanBytes;
     plan->lds_pad = pad;
     plan->align_out = align_out;
     plan->lds_bytes = (int)((int64_t)lds_elems * elem);
@@ -1210,9 +1212,15 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
         return TPERM_OK;
     }
     const TileDesc& d = plan.tile;
+    // places an element of the tensor may take in the LDS image: not the one that slots beyond the
+    // tile write
+    const uint32_t places = plan.use_lds && plan.spare ? d.lds_elems - 1u : d.lds_elems;
     std::vector<int64_t> lds(plan.use_lds ? d.lds_elems : 1, -1);
     const uint32_t slots = (uint32_t)plan.nreg * (uint32_t)plan.threads;
     if (slots < d.tile_vol) return TPERM_ERR_INTERNAL;
+    if (plan.use_lds && (int64_t)d.lds_elems * d.lds_buffers * plan.elem > kMaxLdsBytes) return TPERM_ERR_INTERNAL;
+    for (bool acc : {false, true})
+        if (runs_without_masks(plan, acc) && slots > d.tile_vol && !plan.spare) return TPERM_ERR_INTERNAL;
     // visit tiles the way a launch with `grid` workgroups would; any grid gives the same
     // set of tiles, use a small one that still exercises the iteration arithmetic
     const uint32_t grid = d.grid_mode != 0u ? 16u : 7u;
@@ -1245,7 +1253,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                         const uint32_t xa = d.pair_a_split ? s.xa + e : s.xa;
                         if (!(xa < rem_a && (s.xb - lo_b) < span_b)) continue;
                         const int64_t gi = (int64_t)maj_in + (int64_t)s.goff + e - (int64_t)oa.in_halo_elems;
-                        if (gi < 0 || gi >= vol || s.loff + e >= d.lds_elems) return TPERM_ERR_INTERNAL;
+                        if (gi < 0 || gi >= vol || s.loff + e >= places) return TPERM_ERR_INTERNAL;
                         if (lds[s.loff + e] != -1) return TPERM_ERR_INTERNAL;
                         lds[s.loff + e] = gi;
                     }
@@ -1261,7 +1269,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                         if (!(so.xa < rem_a && (xb - lo_b) < span_b)) continue;
                         const int64_t go = (int64_t)maj_out + (int64_t)so.goff + e - (int64_t)shift;
                         const int64_t li = (int64_t)so.loff + (int64_t)(oa.line_elems - shift + e) * oa.lstride_b;
-                        if (go < 0 || go >= vol || li < 0 || li >= (int64_t)d.lds_elems) return TPERM_ERR_INTERNAL;
+                        if (go < 0 || go >= vol || li < 0 || li >= (int64_t)places) return TPERM_ERR_INTERNAL;
                         if (lds[li] == -1) return TPERM_ERR_INTERNAL;
                         if (out_to_in[go] != -1) return TPERM_ERR_INTERNAL;
                         out_to_in[go] = lds[li];
@@ -1275,7 +1283,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                     if (!(s.xa < rem_a && s.xb < rem_b)) continue;
                     for (uint32_t e = 0; e < 2; ++e) {
                         const uint64_t gi = maj_in + s.goff + e;
-                        if (gi >= (uint64_t)vol || s.loff + e >= d.lds_elems) return TPERM_ERR_INTERNAL;
+                        if (gi >= (uint64_t)vol || s.loff + e >= places) return TPERM_ERR_INTERNAL;
                         if (lds[s.loff + e] != -1) return TPERM_ERR_INTERNAL;
                         lds[s.loff + e] = (int64_t)gi;
                     }
@@ -1286,7 +1294,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                     for (uint32_t e = 0; e < 2; ++e) {
                         const uint64_t go = maj_out + s.goff + e;
                         const uint32_t li = s.loff + e * d.pair_lstride;
-                        if (go >= (uint64_t)vol || li >= d.lds_elems) return TPERM_ERR_INTERNAL;
+                        if (go >= (uint64_t)vol || li >= places) return TPERM_ERR_INTERNAL;
                         if (lds[li] == -1) return TPERM_ERR_INTERNAL;
                         if (out_to_in[go] != -1) return TPERM_ERR_INTERNAL;
                         out_to_in[go] = lds[li];
@@ -1302,7 +1310,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                     const Slot s = tile_slot(d.in_order, d.n_tile_dims, k);
                     if (!(s.xa < rem_a && (s.xb - lo_b) < span_b)) continue;
                     const int64_t gi = (int64_t)maj_in + (int64_t)s.goff - (int64_t)oa.in_halo_elems;
-                    if (gi < 0 || gi >= vol || s.loff >= d.lds_elems) return TPERM_ERR_INTERNAL;
+                    if (gi < 0 || gi >= vol || s.loff >= places) return TPERM_ERR_INTERNAL;
                     if (lds[s.loff] != -1) return TPERM_ERR_INTERNAL;
                     lds[s.loff] = gi;
                 }
@@ -1316,7 +1324,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                     if (!(so.xa < rem_a && (xb - lo_b) < span_b)) continue;
                     const int64_t go = (int64_t)maj_out + (int64_t)so.goff - (int64_t)shift;
                     const int64_t li = (int64_t)so.loff + (int64_t)(oa.line_elems - shift) * oa.lstride_b;
-                    if (go < 0 || go >= vol || li < 0 || li >= (int64_t)d.lds_elems) return TPERM_ERR_INTERNAL;
+                    if (go < 0 || go >= vol || li < 0 || li >= (int64_t)places) return TPERM_ERR_INTERNAL;
                     if (lds[li] == -1) return TPERM_ERR_INTERNAL;
                     if (out_to_in[go] != -1) return TPERM_ERR_INTERNAL;
                     out_to_in[go] = lds[li];
@@ -1327,7 +1335,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                     const Slot s = tile_slot(d.in_order, d.n_tile_dims, k);
                     if (!(s.xa < rem_a && s.xb < rem_b)) continue;
                     const uint64_t gi = maj_in + s.goff;
-                    if (gi >= (uint64_t)vol || s.loff >= d.lds_elems) return TPERM_ERR_INTERNAL;
+                    if (gi >= (uint64_t)vol || s.loff >= places) return TPERM_ERR_INTERNAL;
                     if (lds[s.loff] != -1) return TPERM_ERR_INTERNAL;
                     lds[s.loff] = (int64_t)gi;
                 }
@@ -1335,7 +1343,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                     const Slot s = tile_slot(d.out_order, d.n_tile_dims, k);
                     if (!(s.xa < rem_a && s.xb < rem_b)) continue;
                     const uint64_t go = maj_out + s.goff;
-                    if (go >= (uint64_t)vol || s.loff >= d.lds_elems) return TPERM_ERR_INTERNAL;
+                    if (go >= (uint64_t)vol || s.loff >= places) return TPERM_ERR_INTERNAL;
                     if (lds[s.loff] == -1) return TPERM_ERR_INTERNAL;
                     if (out_to_in[go] != -1) return TPERM_ERR_INTERNAL;
                     out_to_in[go] = lds[s.loff];

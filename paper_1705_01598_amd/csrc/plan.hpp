@@ -105,11 +105,21 @@ struct Plan {
     bool loads_first = false;  // next tile's loads are issued before this tile's stores
     int cache_policy = 1;    // 1 = cached, 2 = nontemporal loads and stores, 3 = nontemporal stores, 4 = nontemporal loads
     bool big = false;        // tensor of 4 GiB or more: tiles describe their buffers from their own origin
+    // Slots beyond the tile write the last element of the LDS image (forms without masks).  With
+    // padded rows that is padding; an image without any is one element longer than the tile.  It
+    // stays within kMaxLdsBytes: there are fewer elements than slots, and all slots fit.
+    bool spare = false;
     TileDesc tile;
     NaiveDesc naive;
     // launch geometry, resolved on first execute (needs the device); 0 = not yet
     int max_blocks = 0;
 };
+
+// The variant for small tensors runs the plan / the kernel that runs it has no masks.
+inline bool runs_lean(const Plan& p, bool accumulate) { return p.lean && !accumulate && !p.loads_first; }
+inline bool runs_without_masks(const Plan& p, bool accumulate) {
+    return tile_form_without_masks(p.nreg, p.threads, p.use_lds, p.align_out, p.vec2, runs_lean(p, accumulate));
+}
 
 tperm_status_t validate(int rank, const int64_t* dims, const int* perm, size_t elem);
 void canonicalise(int rank, const int64_t* dims, const int* perm, Canonical* out);

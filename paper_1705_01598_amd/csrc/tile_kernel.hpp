@@ -235,8 +235,8 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     constexpr bool PAIRWIN = VEC2 && ALIGN;
     // NO_MASKS: fewer instructions per tile.  Every slot writes and reads the LDS image, whether its
     // element exists in this tile or not: the place of an element that does not exist is only read
-    // by stores which are dropped, and slots that no tile uses write to spare elements behind the
-    // image.  A tile without an edge of the tensor issues its loads and stores without looking at
+    // by stores which are dropped, and slots beyond the tile write the image's last element, where no
+    // element of the tensor lies (Plan::spare).  A tile without an edge of the tensor issues its loads and stores without looking at
     // masks (a wave-uniform choice).  What it is for: with two wavefronts per SIMD the masked form
     // spends 43 % of its time issuing instructions on a 27 MB tensor of 12 slots per thread (a dozen
     // vector and eight scalar ones per slot and tile); this form needs two.  Measured (same plan,
@@ -248,7 +248,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // tensors, and 24 and 32 slots always: accumulating (a ragged rank-4 fp32 tensor of 497 MB 432 ->
     // 327 us with the tiles picked for it now) and beyond 4 GiB (a ragged rank-5 one of 4.3 GB 2.72 ->
     // 2.16 ms) too.
-    constexpr bool NO_MASKS = USE_LDS && !VEC2 && !ALIGN && THREADS == 256 && (LEAN || NREG >= 24);
+    constexpr bool NO_MASKS = tile_form_without_masks(NREG, THREADS, USE_LDS, ALIGN, VEC2, LEAN);
     static_assert(!LEAN || NO_MASKS, "the lean form is a plain LDS-staged one of 256 threads");
     typedef typename std::conditional<sizeof(T) == 4, uint64_t, Pair64>::type pair_t;
     typedef Elem<typename std::conditional<VEC2, pair_t, T>::type, NT> io;
@@ -408,7 +408,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
                 wr_mask[j] = used_w ? wr_mask[j] : 0xFFFFFFFFu;  // coordinates no remaining
                 if (USE_LDS) {                                    // extent exceeds: unused
                     rd_mask[j] = used_r ? rd_mask[j] : 0xFFFFFFFFu;
-                    // NO_MASKS: what unused slots write goes to the spare element behind the image
+                    // NO_MASKS: slots beyond the tile write the image's last element
                     const uint32_t spare = NO_MASKS ? lds_elems - 1u : 0u;
                     lds_pos[j] = (used_r ? loff_i[jj] : spare) | ((used_w ? loff_o[jj] : 0u) << 16);
                 } else {

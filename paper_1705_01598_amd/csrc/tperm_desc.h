@@ -98,7 +98,7 @@ struct TileDesc {
                             // tiles overlap: line-aligned output windows)
     uint32_t split_halo[2]; // leading coordinates of the dim that do not exist (the halo in
                             // front of the first chunk); 0 normally
-    uint32_t lds_elems;     // size of one LDS image (with padding), elements
+    uint32_t lds_elems;     // size of one LDS image (with padding; see Plan::spare), elements
     uint32_t lds_buffers;   // 1, or 2: tiles alternate between two images (one barrier per tile)
     uint32_t vec2;          // 1: 4-byte elements move in pairs (8-byte global accesses): entry 0
                             // of in_order counts pairs along input dim 0, entry 0 of out_order
@@ -153,6 +153,12 @@ TPERM_HD TileWalk tile_walk_of(const D& d) {
     w.lane_a = d.lane_a;
     w.lane_b = d.lane_b;
     return w;
+}
+
+// Whether a kernel of the tile family runs without masks (see NO_MASKS in tile_kernel.hpp for what
+// that means and for why the line lies here).  lean: the variants instantiated for small tensors.
+constexpr bool tile_form_without_masks(int nreg, int threads, bool use_lds, bool align, bool vec2, bool lean) {
+    return use_lds && !vec2 && !align && threads == 256 && (lean || nreg >= 24);
 }
 
 // Per-thread, per-slot minor position for the read side (Eq. (4) and the LDS store slot).

@@ -2,6 +2,7 @@
 // UndefinedBehaviorSanitizer (see test_planner_host.py).  It links plan.cpp alone (the
 // planner has no HIP dependency), creates plans for random problems and options, and checks
 // every plan's index map for being a bijection of 0..vol-1.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -13,7 +14,7 @@
 int main(int argc, char** argv) {
     const int iters = argc > 1 ? atoi(argv[1]) : 400;
     std::mt19937_64 rng(12345);
-    int made = 0, rejected = 0, windows = 0, pair_windows = 0;
+    int made = 0, rejected = 0, windows = 0, pair_windows = 0, images = 0;
     for (int it = 0; it < iters; ++it) {
         const int rank = 1 + (int)(rng() % 16);
         int64_t dims[TPERM_MAX_RANK];
@@ -111,6 +112,26 @@ int main(int argc, char** argv) {
             }
             seen[(size_t)map[(size_t)i]] = 1;
         }
+        if (p->use_lds && !p->align_out && p->tile.n_tile_dims > 0) {
+            // The index map must refuse an image that ends one element too early: shrink it to what
+            // the tile's first (full) instance needs and by one more.
+            const tperm::TileDesc& d = p->tile;
+            uint32_t last = 0;
+            for (uint32_t k = 0; k < d.tile_vol; ++k)
+                last = std::max(last, tperm::tile_slot(d.in_order, d.n_tile_dims, k).loff + (d.vec2 ? 1u : 0u));
+            const uint32_t behind = p->spare ? 1u : 0u;
+            tperm::Plan cut = *p;
+            cut.tile.lds_elems = last + 1u + behind;
+            const tperm_status_t fits = tperm::index_map(cut, map.data());
+            cut.tile.lds_elems = last + behind;
+            const bool unpadded = last + 1u == d.tile_vol * (d.vec2 ? 2u : 1u);
+            if (fits != TPERM_OK || tperm::index_map(cut, map.data()) != TPERM_ERR_INTERNAL ||
+                (unpadded && d.lds_elems != last + 1u + behind)) {
+                std::printf("an image that is too small passes, or one is too large, iteration %d\n", it);
+                return 1;
+            }
+            ++images;
+        }
         if (p->kclass == TPERM_KERNEL_ROWCOPY || p->kclass == TPERM_KERNEL_TILED || p->kclass == TPERM_KERNEL_PACKED) {
             // the analytical model walks sampled tiles with the kernel's arithmetic: its byte
             // count per tile can never exceed the tile, and the estimate must be finite
@@ -126,7 +147,7 @@ int main(int argc, char** argv) {
         delete p;
         ++made;
     }
-    std::printf("ok: %d plans checked (%d with line-aligned windows, %d of them in pairs), %d option sets rejected\n", made, windows, pair_windows,
-                rejected);
+    std::printf("ok: %d plans checked (%d with line-aligned windows, %d of them in pairs, %d LDS images cut), %d option sets rejected\n", made, windows, pair_windows,
+                images, rejected);
     return 0;
 }

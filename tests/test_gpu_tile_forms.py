@@ -32,7 +32,7 @@ def _run(dims, perm, elem, **kw):
 def test_form_without_masks_on_small_tensors(t0, t1, nreg, elem):
     for i, (d0, d1) in enumerate([(t0, t1), (2 * t0, 3 * t1), (3 * t0 + 1, 2 * t1), (2 * t0, 2 * t1 - 1), (2 * t0 - 1, t1 + 1)]):
         info = _run((d0, 3, d1), (2, 0, 1) if i % 2 else (2, 1, 0), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1,
-                    tile_out=t1, vec2=1, align_out=1, cache_policy=1 + i % 4, lds_buffers=1 + i % 2,
+                    tile_out=t1, vec2=1, align_out=1, cache_policy=1 + i % 4, lds_buffers=1 + i % 2, lds_pad=(0, 0, -1, -1, 1)[i],
                     window_in=(0, 2)[i % 2], window_out=(0, 3)[i // 2 % 2])
         assert info.nreg <= nreg
 

@@ -20,16 +20,35 @@ def test_cached_loads_below_16_mib(d0, d1, elem, policy):
     assert B.tperm_plan_create((512, 512), (1, 0), 8).describe().cache_policy == 2
 
 
+@pytest.mark.parametrize("pad", [-1, 0, 1])
 @pytest.mark.parametrize("elem", [4, 8])
-def test_index_maps_of_the_slot_counts_without_masks(elem):
-    """Tiles of 6 to 32 slots per thread with edges on both split dims: the map of positions (and the
-    spare element behind the LDS image) stays inside the image and the tensors."""
+def test_index_maps_of_the_slot_counts_without_masks(elem, pad):
+    """Tiles of 6 to 32 slots per thread with edges on both split dims: the map of positions stays
+    inside the tensors and inside the LDS image, and no element lies on the place that slots beyond
+    the tile write (the map fails if one does)."""
     for t0, t1 in ((48, 32), (61, 25), (64, 64), (77, 79), (89, 71)):
         dims, perm = (2 * t0 - 1, 3, t1 + 1), (2, 0, 1)
         plan = B.tperm_plan_create_ex(dims, perm, elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1, vec2=1,
-                                      align_out=1, lds_buffers=2)
+                                      align_out=1, lds_buffers=2, lds_pad=pad)
         ref = oracle.transpose(np.arange(int(np.prod(dims)), dtype=np.int64), dims, perm)
         assert np.array_equal(B.tperm_plan_index_map(plan), ref)
+
+
+@pytest.mark.parametrize("elem", [4, 8])
+def test_lds_image_holds_the_tile_and_its_padding_only(elem):
+    """One more element only where slots beyond the tile need a place to write and the rows have no
+    padding: not for tiles that fill their slots, padded rows, pairs, windows or 64 threads."""
+    def lds_bytes(t0, t1, pad, **kw):
+        kw = {**dict(vec2=1, align_out=1, lds_buffers=2), **kw}
+        dims = (2 * t0, 3, 2 * t1)
+        return B.tperm_plan_create_ex(dims, (2, 0, 1), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1,
+                                      lds_pad=pad, pair_elems=1, **kw).describe().lds_bytes
+    assert lds_bytes(64, 64, 0) == 64 * 64 * elem          # two images of 8-byte elements: 64 KiB, and no more
+    assert lds_bytes(61, 50, 0) == (61 * 50 + 1) * elem
+    assert lds_bytes(61, 50, 1) == 62 * 50 * elem
+    assert lds_bytes(60, 50, 0, vec2=2) == 60 * 50 * elem
+    assert lds_bytes(61, 32, 0, align_out=2) == 61 * (32 + 128 // elem) * elem
+    assert lds_bytes(30, 50, 0, threads=64) == 30 * 50 * elem
 
 
 def test_argument_arrays_are_taken_by_value():
