@@ -121,7 +121,9 @@ typedef struct {
                                             * from its own origin; LDS-staged tiles of 256  *
                                             * threads in all their forms, or the gather     *
                                             * kernel when no tile fits.                     */
-    int reserved[1];
+    int without_masks;                     /* 1 if tperm_execute launches the form of the   *
+                                            * tile kernel without masks, + 2 if accumulation*
+                                            * does (see tile_kernel.hpp)                    */
 } tperm_plan_info_t;
 
 /* Create a plan: the first call of the create / execute / destroy triple of Section 2.3.  The

@@ -71,7 +71,7 @@ class PlanInfo(ctypes.Structure):
                 ("blocks_per_cu", ctypes.c_int), ("cache_policy", ctypes.c_int),
                 ("align_out", ctypes.c_int), ("paired", ctypes.c_int),
                 ("loads_first", ctypes.c_int), ("vec2", ctypes.c_int), ("large", ctypes.c_int),
-                ("reserved", ctypes.c_int * 1)]
+                ("without_masks", ctypes.c_int)]
 
 
 class TpermError(RuntimeError):
@@ -406,4 +406,5 @@ def info_dict(info: PlanInfo) -> dict:
             "lds_pad": info.lds_pad, "score": round(info.score, 4),
             "blocks_per_cu": info.blocks_per_cu, "cache_policy": info.cache_policy,
             "align_out": info.align_out, "paired": info.paired,
-            "loads_first": info.loads_first, "vec2": info.vec2, "large": info.large}
+            "loads_first": info.loads_first, "vec2": info.vec2, "large": info.large,
+            "without_masks": info.without_masks}

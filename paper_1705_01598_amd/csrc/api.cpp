@@ -368,6 +368,9 @@ tperm_status_t tperm_plan_describe(tperm_plan_t plan, tperm_plan_info_t* info) {
         info->loads_first = p.loads_first ? 1 : 0;
         info->vec2 = p.vec2 ? 1 : 0;
         info->large = p.big ? 1 : 0;
+        // (accumulation runs the plan without its twin)
+        const Plan& q = *plan->base.p;
+        info->without_masks = (tperm::runs_without_masks(p, false) ? 1 : 0) + (tperm::runs_without_masks(q, true) ? 2 : 0);
     } else {
         info->large = (p.kclass == TPERM_KERNEL_NAIVE && p.big) ? 1 : 0;
         info->threads = 256;

@@ -1,6 +1,7 @@
 """Forms of the tile kernel that a rule on size picks, at the sizes where they can go wrong: tiles
 that exactly fill their slots and tiles one element short, edges of the tensor on either split dim
-and on both, tensors smaller than one tile.  Bit-exact against the CPU oracle, with guard bands."""
+and on both, one tile for the whole tensor.  Every test asserts which form ran.  Bit-exact against
+the CPU oracle, with guard bands."""
 import numpy as np
 import pytest
 
@@ -33,32 +34,61 @@ def test_form_without_masks_on_small_tensors(t0, t1, nreg, elem):
     for i, (d0, d1) in enumerate([(t0, t1), (2 * t0, 3 * t1), (3 * t0 + 1, 2 * t1), (2 * t0, 2 * t1 - 1), (2 * t0 - 1, t1 + 1)]):
         info = _run((d0, 3, d1), (2, 0, 1) if i % 2 else (2, 1, 0), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1,
                     tile_out=t1, vec2=1, align_out=1, cache_policy=1 + i % 4, lds_buffers=1 + i % 2, lds_pad=(0, 0, -1, -1, 1)[i],
+                    loads_first=1,
                     window_in=(0, 2)[i % 2], window_out=(0, 3)[i // 2 % 2])
-        assert info.nreg <= nreg
+        assert info.nreg == nreg and info.loads_first == 0 and info.without_masks & 1
+
+
+@pytest.mark.parametrize("elem", [4, 8])
+@pytest.mark.parametrize("t0,t1,nreg", [(48, 32, 6), (61, 50, 12)])
+def test_masked_form_where_loads_go_first(t0, t1, nreg, elem):
+    """The order with the loads first exists with masks only."""
+    info = _run((2 * t0 - 1, 3, t1 + 1), (2, 0, 1), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1,
+                vec2=1, align_out=1, loads_first=2)
+    assert info.nreg == nreg and info.loads_first == 1 and info.without_masks == 0
+
+
+@pytest.mark.parametrize("policy", [1, 2, 3, 4])
+@pytest.mark.parametrize("elem", [4, 8])
+@pytest.mark.parametrize("t0,t1,nreg", [(61, 50, 12), (77, 79, 24), (89, 71, 32)])
+def test_form_of_large_tensors(t0, t1, nreg, elem, policy):
+    """The kernels that address every tile from its own origin."""
+    for dims, perm in (((2 * t0 - 1, 3, t1 + 1), (2, 0, 1)), ((t0 + 1, 3, 2 * t1 - 1), (2, 1, 0))):
+        info = _run(dims, perm, elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1, vec2=1, align_out=1,
+                    large=1, cache_policy=policy, lds_pad=0)
+        assert info.nreg == nreg and info.large == 1
+        assert info.without_masks == (3 if nreg >= 24 else 0)
 
 
 @pytest.mark.parametrize("elem", [4, 8])
 def test_both_sides_of_the_small_tensor_line(elem):
     """The same tile just below and just above 40 MB, where the form changes."""
-    for d2 in (40_000_000 // elem // (61 * 50), 40_000_000 // elem // (61 * 50) + 1):
-        _run((61, 50, d2), (1, 0, 2), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=61, k=1, tile_out=50, vec2=1)
+    for more, form in ((0, 1), (1, 0)):
+        info = _run((61, 50, 40_000_000 // elem // (61 * 50) + more), (1, 0, 2), elem, kernel_class=B.KERNEL_PACKED, m=1,
+                    tile_in=61, k=1, tile_out=50, vec2=1)
+        assert info.nreg == 12 and info.without_masks == form
 
 
 @pytest.mark.parametrize("large", [0, 1])
 @pytest.mark.parametrize("elem", [4, 8])
 @pytest.mark.parametrize("policy", [1, 2, 3, 4])
 def test_accumulation_under_every_cache_policy(policy, elem, large):
-    """Staged tiles with edges on both sides and the LDS-free row copy, at output pointers on and off a
-    sector boundary (which changes the policy of the kernel that runs)."""
+    """Staged tiles with edges on both sides, few slots and as many as the form without masks takes, and
+    the LDS-free row copy, at output pointers on and off a sector boundary (which changes the policy
+    of the kernel that runs)."""
     ftype = np.float64 if elem == 8 else np.float32
-    for dims, perm, kw in [((70, 45, 33), (2, 0, 1), dict(kernel_class=B.KERNEL_PACKED, m=1, tile_in=33, k=1, tile_out=16)),
-                           ((64, 40, 48), (1, 2, 0), dict(kernel_class=B.KERNEL_PACKED, m=1, tile_in=32, k=1, tile_out=40)),
-                           ((48, 21, 34), (0, 2, 1), {} if large else dict(kernel_class=B.KERNEL_ROWCOPY))]:
+    tile = lambda t0, t1: dict(kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1, align_out=1)  # noqa: E731
+    for dims, perm, kw, nreg in [((70, 45, 33), (2, 0, 1), tile(33, 16), 3), ((64, 40, 48), (1, 2, 0), tile(32, 40), 6),
+                                 ((153, 3, 80), (2, 0, 1), tile(77, 79), 24), ((90, 3, 141), (2, 1, 0), tile(89, 71), 32),
+                                 ((96, 3, 128), (2, 1, 0), tile(96, 64), 24),
+                                 ((48, 21, 34), (0, 2, 1), {} if large else dict(kernel_class=B.KERNEL_ROWCOPY), 0)]:
         vol = int(np.prod(dims))
         rng = np.random.default_rng(vol + policy)
         a, b = (rng.standard_normal(vol).astype(ftype) for _ in range(2))
         for offset in (0, 1):
             plan = B.tperm_plan_create_ex(dims, perm, elem, cache_policy=policy, large=large, vec2=1, pair_elems=1, **kw)
+            info = plan.describe()
+            assert nreg == 0 or (info.nreg == nreg and info.without_masks & 2 == (2 if nreg >= 24 else 0))
             a_dev, out = to_device(a), GuardedOut(vol, elem, offset)
             out.view().copy_(to_device(b))
             B.tperm_execute_accumulate(plan, a_dev.data_ptr(), out.ptr, torch.cuda.current_stream().cuda_stream)
