@@ -959,10 +959,15 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         if ((std::max(span_in, span_out) + 2u + (uint64_t)line_elems) * (uint64_t)elem > (uint64_t)TPERM_BIG_RANGE)
             return TPERM_ERR_KERNEL;
     }
-    plan->lean = cand.use_lds && threads == 256 && !plan->vec2 && !align_out && !opts.big && nreg_final >= 6 &&
-                 nreg_final <= 16 && c.volume * elem < kLeanBytes;
-    plan->spare = d.tile_vol < (uint32_t)nreg_final * (uint32_t)threads &&
-                  tile_form_without_masks(nreg_final, threads, cand.use_lds, align_out, plan->vec2, plan->lean);
+    const int64_t bytes = c.volume * elem;
+    plan->lean = cand.use_lds && threads == 256 && !plan->vec2 && !align_out && !opts.big &&
+                 ((nreg_final >= 6 && nreg_final <= 16 && bytes < kLeanBytes) ||
+                  (nreg_final == 24 && elem == 4 && bytes < kLeanBytes24));
+    auto without_masks = [&](bool acc) {
+        return tile_form_without_masks(elem, nreg_final, threads, cand.use_lds, align_out, acc, plan->vec2, opts.big,
+                                       plan->lean && !acc);
+    };
+    plan->spare = d.tile_vol < (uint32_t)nreg_final * (uint32_t)threads && (without_masks(false) || without_masks(true));
     if (plan->spare && !padded) ++lds_elems;
     d.lds_elems = lds_elems;
     d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)lds_elems * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;

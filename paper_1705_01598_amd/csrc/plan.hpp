@@ -21,10 +21,11 @@ constexpr int64_t kMaxLdsBytes = 64 * 1024;
 constexpr int kDefaultWindow = 1;
 constexpr int kDefaultWindowIn = 0;
 constexpr int kDefaultThreads = 256;
-// Tensors below this size take the lean form of the tile kernel where it exists (measured on both
-// sides of the line, see the kernel: +3 to +11 % below 20 MB, +0 to +9 % up to 40 MB, level from
-// there to 80 MB, then losing).
+// Tensors below these sizes take the lean variants of the tile kernel, which run without masks: 6 to
+// 16 slots per thread, and 24 slots of 4-byte elements (measured on both sides of the lines, see
+// NO_MASKS in tile_kernel.hpp).
 constexpr int64_t kLeanBytes = 40 * 1000 * 1000;
+constexpr int64_t kLeanBytes24 = 640 * 1000 * 1000;
 // Tensors below this size read with cached loads unless they are line-aligned on both sides (see
 // build_tile_plan).
 constexpr int64_t kCachedLoadBytes = (int64_t)16 << 20;
@@ -101,7 +102,7 @@ struct Plan {
     int grid_mode = 0;
     int blocks_per_cu = 0;   // cap on resident workgroups per compute unit (0 = none)
     bool vec2 = false;         // 4-byte elements move in pairs; needs 8-byte aligned pointers
-    bool lean = false;         // small tensor, 6 to 16 slots per thread: the kernel form with fewer instructions per tile
+    bool lean = false;         // small tensor: the variants of the kernel without masks (6 to 16 slots per thread, 24 for 4-byte elements)
     bool loads_first = false;  // next tile's loads are issued before this tile's stores
     int cache_policy = 1;    // 1 = cached, 2 = nontemporal loads and stores, 3 = nontemporal stores, 4 = nontemporal loads
     bool big = false;        // tensor of 4 GiB or more: tiles describe their buffers from their own origin
@@ -118,7 +119,8 @@ struct Plan {
 // The variant for small tensors runs the plan / the kernel that runs it has no masks.
 inline bool runs_lean(const Plan& p, bool accumulate) { return p.lean && !accumulate && !p.loads_first; }
 inline bool runs_without_masks(const Plan& p, bool accumulate) {
-    return tile_form_without_masks(p.nreg, p.threads, p.use_lds, p.align_out, p.vec2, runs_lean(p, accumulate));
+    return tile_form_without_masks(p.elem, p.nreg, p.threads, p.use_lds, p.align_out, accumulate, p.vec2, p.big,
+                                   runs_lean(p, accumulate));
 }
 
 tperm_status_t validate(int rank, const int64_t* dims, const int* perm, size_t elem);

@@ -1,5 +1,6 @@
 // Instantiations of the tile kernel's lean form (see NO_MASKS there) for uint32_t elements: plain
-// LDS-staged tiles of 256 threads, 6 to 16 slots per thread, the four cache policies.
+// LDS-staged tiles of 256 threads, 6 to 16 and 24 slots per thread, the four cache
+// policies.
 #include "tile_kernel.hpp"
 
 namespace tperm {
@@ -21,6 +22,7 @@ const void* tile_kernel_lean_u32(int nreg, int nt) {
         case 8: return lean_kernel_ptr<8>(nt);
         case 12: return lean_kernel_ptr<12>(nt);
         case 16: return lean_kernel_ptr<16>(nt);
+        case 24: return lean_kernel_ptr<24>(nt);
         default: return nullptr;
     }
 }

@@ -239,16 +239,25 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // element of the tensor lies (Plan::spare).  A tile without an edge of the tensor issues its loads and stores without looking at
     // masks (a wave-uniform choice).  What it is for: with two wavefronts per SIMD the masked form
     // spends 43 % of its time issuing instructions on a 27 MB tensor of 12 slots per thread (a dozen
-    // vector and eight scalar ones per slot and tile); this form needs two.  Measured (same plan,
-    // masked / this form, geometric means over 1900 candidate plans of 141 seeded shapes): 6 to 16
-    // slots 1.03-1.11 on tensors below 20 MB, 1.00-1.09 at 20-40 MB, 0.92-1.02 above 160 MB, where
-    // memory is the bound and workgroups that run apart faster merge fewer of the lines they share
-    // (partial line writes on a 536 MB tensor: 8 % masked, 16 % without); 24 and 32 slots, which
-    // leave few wavefronts per SIMD, 1.04-1.29 almost throughout.  Hence the LEAN variants for small
-    // tensors, and 24 and 32 slots always: accumulating (a ragged rank-4 fp32 tensor of 497 MB 432 ->
-    // 327 us with the tiles picked for it now) and beyond 4 GiB (a ragged rank-5 one of 4.3 GB 2.72 ->
-    // 2.16 ms) too.
-    constexpr bool NO_MASKS = tile_form_without_masks(NREG, THREADS, USE_LDS, ALIGN, VEC2, LEAN);
+    // vector and eight scalar ones per slot and tile); this form needs two.  What it costs: where
+    // memory is the bound, workgroups that run apart faster merge fewer of the lines they share.
+    // Measured (same plan, time with masks / without, geometric means over 10500 candidate plans of
+    // 1800 seeded ragged shapes; tensors of up to 20, 40, 80, 160, 320, 640, 1280 and 3400 MB, and
+    // beyond 4 GiB):
+    //    4-byte,  6 slots  1.03  1.01  1.00  0.97  0.97  0.96  0.94  0.95
+    //             8        1.04  1.01  0.98  0.95  0.94  0.92  0.90  0.91
+    //            12        1.09  1.10  1.07  1.07  1.04  1.01  0.99  0.98
+    //            16        1.11  1.10  1.07  1.03  0.99  0.97  0.95  0.94
+    //            24              1.19  1.16  1.12  1.06  1.02  0.99  0.98  0.92
+    //            32                    1.35  1.31  1.32  1.31  1.27  1.25  1.16
+    //    8-byte, 6-16      1.04  1.03  1.01  1.00  0.98  0.99  0.99  0.98
+    //            24                                1.06  1.04  1.02  1.01  1.02
+    //            32                                      1.15  1.28  1.13  1.08
+    // Accumulating: 24 slots 1.12 to 0.99 (4-byte; 0.98 beyond 4 GiB) and 1.14 to 1.04 (8-byte), 32
+    // slots 1.30 to 1.21 and 1.13 to 1.07; 6 to 16 slots gain 0 to 2 % on average below 40 MB and are
+    // not instantiated.  Hence without masks: 32 slots, and 24 of 8-byte elements, always; 24 of
+    // 4-byte elements accumulating below 4 GiB; and the LEAN variants for small tensors.
+    constexpr bool NO_MASKS = tile_form_without_masks((int)sizeof(T), NREG, THREADS, USE_LDS, ALIGN, ACC, VEC2, BIG, LEAN);
     static_assert(!LEAN || NO_MASKS, "the lean form is a plain LDS-staged one of 256 threads");
     typedef typename std::conditional<sizeof(T) == 4, uint64_t, Pair64>::type pair_t;
     typedef Elem<typename std::conditional<VEC2, pair_t, T>::type, NT> io;

@@ -156,9 +156,11 @@ TPERM_HD TileWalk tile_walk_of(const D& d) {
 }
 
 // Whether a kernel of the tile family runs without masks (see NO_MASKS in tile_kernel.hpp for what
-// that means and for why the line lies here).  lean: the variants instantiated for small tensors.
-constexpr bool tile_form_without_masks(int nreg, int threads, bool use_lds, bool align, bool vec2, bool lean) {
-    return use_lds && !vec2 && !align && threads == 256 && (lean || nreg >= 24);
+// that means and for why the lines lie here).  lean: the variants instantiated for small tensors.
+constexpr bool tile_form_without_masks(int elem, int nreg, int threads, bool use_lds, bool align, bool acc, bool vec2,
+                                       bool big, bool lean) {
+    return use_lds && !vec2 && !align && threads == 256 &&
+           (lean || nreg >= 32 || (nreg == 24 && (elem == 8 || (acc && !big))));
 }
 
 // Per-thread, per-slot minor position for the read side (Eq. (4) and the LDS store slot).

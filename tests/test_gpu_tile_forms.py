@@ -57,16 +57,16 @@ def test_form_of_large_tensors(t0, t1, nreg, elem, policy):
         info = _run(dims, perm, elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1, vec2=1, align_out=1,
                     large=1, cache_policy=policy, lds_pad=0)
         assert info.nreg == nreg and info.large == 1
-        assert info.without_masks == (3 if nreg >= 24 else 0)
+        assert info.without_masks == (3 if nreg == 32 or (nreg, elem) == (24, 8) else 0)
 
 
-@pytest.mark.parametrize("elem", [4, 8])
-def test_both_sides_of_the_small_tensor_line(elem):
-    """The same tile just below and just above 40 MB, where the form changes."""
+@pytest.mark.parametrize("elem,t0,t1,nreg,line", [(4, 61, 50, 12, 40_000_000), (8, 61, 50, 12, 40_000_000), (4, 77, 79, 24, 640_000_000)])
+def test_both_sides_of_the_small_tensor_lines(elem, t0, t1, nreg, line):
+    """The same tile just below and just above the size where the form changes."""
     for more, form in ((0, 1), (1, 0)):
-        info = _run((61, 50, 40_000_000 // elem // (61 * 50) + more), (1, 0, 2), elem, kernel_class=B.KERNEL_PACKED, m=1,
-                    tile_in=61, k=1, tile_out=50, vec2=1)
-        assert info.nreg == 12 and info.without_masks == form
+        info = _run((t0, t1, line // elem // (t0 * t1) + more), (1, 0, 2), elem, kernel_class=B.KERNEL_PACKED, m=1,
+                    tile_in=t0, k=1, tile_out=t1, vec2=1)
+        assert info.nreg == nreg and info.without_masks & 1 == form
 
 
 @pytest.mark.parametrize("large", [0, 1])
@@ -88,7 +88,7 @@ def test_accumulation_under_every_cache_policy(policy, elem, large):
         for offset in (0, 1):
             plan = B.tperm_plan_create_ex(dims, perm, elem, cache_policy=policy, large=large, vec2=1, pair_elems=1, **kw)
             info = plan.describe()
-            assert nreg == 0 or (info.nreg == nreg and info.without_masks & 2 == (2 if nreg >= 24 else 0))
+            assert nreg == 0 or (info.nreg == nreg and info.without_masks & 2 == (2 if nreg == 32 or (nreg == 24 and (elem == 8 or not large)) else 0))
             a_dev, out = to_device(a), GuardedOut(vol, elem, offset)
             out.view().copy_(to_device(b))
             B.tperm_execute_accumulate(plan, a_dev.data_ptr(), out.ptr, torch.cuda.current_stream().cuda_stream)
