@@ -273,12 +273,18 @@ static bool finish_candidate(const Canonical& c, int elem, Candidate* cd) {
     // workgroups per compute unit); a single slot cannot keep enough bytes in flight, and
     // beyond twelve slots fewer workgroups fit and LDS padding runs out of room.  4-byte
     // elements moved singly want more slots: their tiles are half the bytes (table smoothed
-    // 24 and 32 slots were 1.1 and 1.2 before the kernel's form without masks made them 8 and 20 %
-    // faster: picks on 4-byte tensors of 64 MB and more 95.2 -> 95.8 % of the best candidate, a
-    // ragged rank-5 one of 536 MB 299 -> 264 us.
+    // by hand from a fit over every candidate of 230 4-byte cases; both halves of the sample
+    // gain 1 % over the flatter table used before).  LDS-staged tiles whose kernel has no masks weigh
+    // less than the table says: 32 slots 1.08 for 1.2, and 24 slots 1.0 for 1.1 on tensors below
+    // 320 MB (kernel gains of 25 and 6 to 19 %; above, those of 24 slots end).  Picks on ragged
+    // 4-byte tensors, of the best candidate, with the table alone -> with these: 94.6 -> 94.9 % at 160
+    // to 320 MB (156 seeded shapes), 94.2 -> 94.4 at 320 to 640 (252), 92.7 -> 93.3 above (609); 24
+    // slots at 1.0 everywhere: 94.9, 93.6 and 92.9.  A ragged rank-5 tensor of 536 MB 299 -> 264 us.
     static const int kSlots[10] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
     static const double kWeight8[10] = {1.4, 1.05, 0.95, 0.95, 1.1, 1.0, 1.06, 1.1, 1.16, 1.2};
-    static const double kWeight4[10] = {1.4, 1.2, 0.85, 0.85, 0.8, 0.85, 0.9, 1.0, 1.0, 1.08};
+    static const double kWeight4[10] = {1.4, 1.2, 0.85, 0.85, 0.8, 0.85, 0.9, 1.0, 1.1, 1.2};
+    static const double kWeight4Slots24 = 1.0, kWeight4Slots32 = 1.08;
+    constexpr int64_t kSlots24Bytes = 320 * 1000 * 1000;
     // The LDS-free row copy keeps few registers per slot and has no barrier: four to six
     // slots do better there than the LDS-staged table says when they come from more rows
     // (measured on every candidate of the benchmark cases that keep dim 0 in front; making a
@@ -309,7 +315,10 @@ static bool finish_candidate(const Canonical& c, int elem, Candidate* cd) {
             bucket = i;
             break;
         }
-    cost *= (!cd->use_lds && n_tile_dims >= 2 ? kWeightRc : (pairs8 ? kWeight8Pairs : (elem == 4 && !pairs && !window_pairs ? kWeight4 : kWeight8)))[bucket];
+    const bool singles4 = elem == 4 && !pairs && !window_pairs;
+    if (singles4 && cd->use_lds && kSlots[bucket] == 32) cost *= kWeight4Slots32;
+    else if (singles4 && cd->use_lds && kSlots[bucket] == 24 && c.volume * elem < kSlots24Bytes) cost *= kWeight4Slots24;
+    else cost *= (!cd->use_lds && n_tile_dims >= 2 ? kWeightRc : (pairs8 ? kWeight8Pairs : (singles4 ? kWeight4 : kWeight8)))[bucket];
     // A tile that does not fill the 256 lanes of its workgroup wastes the rest of them.
     if (need == 1) cost /= std::pow((double)slots_needed / TPERM_MAX_THREADS, 0.75);
     // Pipeline fill and drain: a persistent workgroup spends about four tile times without

@@ -20,6 +20,19 @@ def test_cached_loads_below_16_mib(d0, d1, elem, policy):
     assert B.tperm_plan_create((512, 512), (1, 0), 8).describe().cache_policy == 2
 
 
+@pytest.mark.parametrize("dims,perm,nreg,vec2,align_out", [
+    # above 320 MB tiles of 24 single elements displace neither pairs and windows nor smaller tiles (measured,
+    # us with them / with 24 slots: 971 / 1177, 364 / 457, 218 / 234, 335 / 368, 697 / 846)
+    ((479, 2315, 525), (2, 0, 1), 12, 1, 1), ((42, 1142, 4617), (2, 1, 0), 12, 1, 1), ((407012, 310), (1, 0), 8, 1, 0),
+    ((21, 6, 70, 9, 37, 76), (2, 0, 1, 5, 3, 4), 12, 1, 0), ((6861, 155, 371), (2, 0, 1), 16, 0, 0),
+    # below they are taken (68 -> 54 us), and 32 slots at any size (301 -> 267 us)
+    ((15, 12, 38, 5, 8, 19, 6), (5, 4, 1, 6, 3, 0, 2), 24, 0, 0), ((231, 23, 62, 11, 37), (3, 1, 4, 2, 0), 32, 0, 0),
+])
+def test_many_slots_of_single_elements(dims, perm, nreg, vec2, align_out):
+    info = B.tperm_plan_create(dims, perm, 4).describe()
+    assert (info.nreg, info.vec2, info.align_out) == (nreg, vec2, align_out), B.info_dict(info)
+
+
 @pytest.mark.parametrize("elem,nreg,mb,form", [
     (4, 12, 39, 1), (4, 12, 41, 0), (8, 12, 39, 1), (8, 12, 41, 0),
     # 24 slots of 4-byte elements: masks cost 2 to 19 % on average below the line, save 2 % above it (23 % at most)
