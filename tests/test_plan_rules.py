@@ -86,3 +86,5 @@ def test_argument_arrays_are_taken_by_value():
     for bad in ([6, 5, 0], []):
         with pytest.raises((B.TpermError, ValueError)):
             B.tperm_plan_create(bad, [2, 0, 1] if len(bad) != 0 else [], 8)
+    with pytest.raises(TypeError):
+        B.tperm_plan_create(iter((6, 5, 4)), (2, 0, 1), 8)
