@@ -90,7 +90,9 @@ typedef struct {
                                             * 1 = cached, 2 = nontemporal loads and stores, *
                                             * 3 = nontemporal stores, 4 = nontemporal loads *
                                             * (from any other `out` the stores are cached:  *
-                                            * 2 runs as 4, 3 as 1); accumulation is cached   */
+                                            * 2 runs as 4, 3 as 1).  Accumulation runs under*
+                                            * 2 from a 32-byte aligned `out` without line-  *
+                                            * aligned windows, else cached                  */
     int align_out;                         /* 1 if the plan writes line-aligned windows     */
     int paired;                            /* 1: a 4-byte problem whose stride-1 dimension  *
                                             * stays in front and has an even extent is run  *

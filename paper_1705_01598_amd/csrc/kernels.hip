@@ -84,27 +84,6 @@ accumulate_kernel(const F* __restrict__ in, F* __restrict__ out, uint64_t n) {
 // dispatch
 // ---------------------------------------------------------------------------------------
 
-// Cache policy (1 = cached, 2 = nontemporal loads and stores, 3 = nontemporal stores, 4 =
-// nontemporal loads) of the kernel variant that runs the plan.  It is the plan's policy unless:
-// the run accumulates under policy 3 or with line-aligned windows (cached then: nontemporal stores
-// alone change nothing there, the line has just been read; the other two policies are worth as
-// much as in plain runs and more, since two of three passes are loads: policy 2 on line-aligned
-// tensors of 34 to 680 MB +4 to +15 %, 64-element rows of fp64 89.0 -> 78.3 us for 467 MB, policy 4
-// +7 % where it is chosen, measured on 25 shapes); the output base pointer is not a multiple of 32 bytes
-// (sector_aligned_out false: the planner's choice of nontemporal stores assumes whole sectors,
-// from any other base the written pieces end inside sectors and cached stores are the right
-// ones; line-aligned windows follow the pointer's phase by themselves); or the variant is not
-// instantiated (nontemporal loads alone exist for stores-first 256-thread kernels; 64-thread
-// kernels have cached and fully nontemporal forms).
-int tile_launch_policy(const Plan& plan, bool acc, bool sector_aligned_out) {
-    int pol = plan.cache_policy;
-    if (acc && (pol == 3 || plan.align_out)) pol = 1;
-    if (!sector_aligned_out && !plan.align_out) pol = (pol == 2 || pol == 4) ? 4 : 1;
-    if (pol == 4 && ((plan.loads_first && !acc) || plan.threads != 256)) pol = 1;
-    if (pol == 3 && plan.threads != 256) pol = 2;
-    return pol;
-}
-
 static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_aligned_out) {
     const int pol = tile_launch_policy(plan, acc, sector_aligned_out);
     const int nt = pol == 2 ? 2 : (pol == 3 ? 1 : (pol == 4 ? 3 : 0));  // template parameter NT

@@ -1019,6 +1019,15 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
     return TPERM_OK;
 }
 
+int tile_launch_policy(const Plan& plan, bool acc, bool sector_aligned_out) {
+    int pol = plan.cache_policy;
+    if (acc) return pol == 2 && sector_aligned_out && !plan.align_out ? 2 : 1;
+    if (!sector_aligned_out && !plan.align_out) pol = (pol == 2 || pol == 4) ? 4 : 1;
+    if (pol == 4 && (plan.loads_first || plan.threads != 256)) pol = 1;
+    if (pol == 3 && plan.threads != 256) pol = 2;
+    return pol;
+}
+
 void build_naive_desc(Plan* plan) {
     const Canonical& c = plan->c;
     NaiveDesc nd;

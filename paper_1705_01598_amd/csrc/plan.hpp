@@ -123,6 +123,20 @@ inline bool runs_without_masks(const Plan& p, bool accumulate) {
                                    runs_lean(p, accumulate));
 }
 
+// Cache policy (1 = cached, 2 = nontemporal loads and stores, 3 = nontemporal stores, 4 =
+// nontemporal loads) of the kernel variant that runs the plan.  It is the plan's policy unless:
+// the output base pointer is not a multiple of 32 bytes (sector_aligned_out false: the planner's
+// choice of nontemporal stores assumes whole sectors, from any other base the written pieces end
+// inside sectors and cached stores are the right ones; line-aligned windows follow the pointer's
+// phase by themselves); the variant is not instantiated (nontemporal loads alone exist for
+// stores-first 256-thread kernels; 64-thread kernels have cached and fully nontemporal forms); or
+// the run accumulates, where two of three passes are loads and the written line has just been
+// read: policy 2 from a sector-aligned base, else cached.  Measured accumulating, time cached /
+// under the policy: 2 +6 to +14 % (145 seeded shapes of 4 to 1600 MB, 0.95 at worst; 64-element
+// rows of fp64, 467 MB, 89.0 -> 78.3 us), 4 -3 % (100 shapes, 0.87 to 1.07; -4 % above 128 MB), 2
+// turned into 4 by an odd base pointer -9 to +7 % (100 shapes, 0.72 to 1.14).
+int tile_launch_policy(const Plan& plan, bool accumulate, bool sector_aligned_out);
+
 tperm_status_t validate(int rank, const int64_t* dims, const int* perm, size_t elem);
 void canonicalise(int rank, const int64_t* dims, const int* perm, Canonical* out);
 FastDiv make_fastdiv(uint32_t d);

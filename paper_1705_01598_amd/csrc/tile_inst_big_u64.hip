@@ -1,7 +1,7 @@
 // Instantiations of the tile kernel for tensors of 4 GiB and more (BIG), 8-byte elements:
 // LDS-staged tiles of 256 threads, stores first, the four cache policies; single elements or
 // pairs, plain or in line-aligned windows; the accumulating forms (single elements; cached,
-// nontemporal loads, nontemporal loads and stores).
+// nontemporal loads and stores).
 #include "tile_kernel.hpp"
 
 namespace tperm {
@@ -14,7 +14,6 @@ const void* tile_kernel_big_u64(int nreg, int nt, bool align, bool acc, bool vec
         switch (nt) {
             case 0: return tile_kernel_ptr<T, 256, true, 0, false, true, false, false, true>(nreg);
             case 2: return tile_kernel_ptr<T, 256, true, 2, false, true, false, false, true>(nreg);
-            case 3: return tile_kernel_ptr<T, 256, true, 3, false, true, false, false, true>(nreg);
             default: return nullptr;
         }
     }

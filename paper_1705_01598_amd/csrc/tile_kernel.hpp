@@ -650,8 +650,8 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
 }
 
 // Kernel pointer for one element type and workgroup size; nullptr if the combination is
-// not instantiated.  Accumulating kernels (ACC) exist for 256 threads: cached, nontemporal loads,
-// nontemporal loads and stores; with line-aligned windows cached only.
+// not instantiated.  Accumulating kernels (ACC) exist for 256 threads: cached, and nontemporal
+// loads and stores; with line-aligned windows cached only.
 template <typename T, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST = false, bool VEC2 = false, bool BIG = false>
 static const void* tile_kernel_ptr(int nreg) {
     switch (nreg) {
@@ -703,9 +703,9 @@ static const void* tile_kernel_select(int nreg, bool use_lds, int nt, bool align
                 return nullptr;
             }
         }
-        if (nt == 3 && !acc) {
+        if (nt == 3) {
             // nontemporal loads only: plain stores-first forms
-            if (loads_first) return nullptr;
+            if (acc || loads_first) return nullptr;
             if (vec2) return use_lds && !align ? tile_kernel_ptr<T, 256, true, 3, false, false, false, true>(nreg) : nullptr;
             if (align) return use_lds ? tile_kernel_ptr<T, 256, true, 3, true, false>(nreg) : nullptr;
             return use_lds ? tile_kernel_ptr<T, 256, true, 3, false, false>(nreg)
@@ -731,9 +731,6 @@ static const void* tile_kernel_select(int nreg, bool use_lds, int nt, bool align
                 case 2:
                     return use_lds ? tile_kernel_ptr<T, 256, true, 2, false, true>(nreg)
                                    : tile_kernel_ptr<T, 256, false, 2, false, true>(nreg);
-                case 3:
-                    return use_lds ? tile_kernel_ptr<T, 256, true, 3, false, true>(nreg)
-                                   : tile_kernel_ptr<T, 256, false, 3, false, true>(nreg);
                 default: return nullptr;
             }
         }

@@ -112,6 +112,17 @@ int main(int argc, char** argv) {
             }
             seen[(size_t)map[(size_t)i]] = 1;
         }
+        // accumulation: nontemporal loads and stores or cached, the latter from odd base pointers and
+        // with line-aligned windows
+        for (int pol = 1; pol <= 4; ++pol) {
+            tperm::Plan q = *p;
+            q.cache_policy = pol;
+            if (tperm::tile_launch_policy(q, true, true) != (pol == 2 && !q.align_out ? 2 : 1) ||
+                tperm::tile_launch_policy(q, true, false) != 1) {
+                std::printf("an accumulating run takes the wrong cache policy, iteration %d\n", it);
+                return 1;
+            }
+        }
         if (p->use_lds && !p->align_out && p->tile.n_tile_dims > 0) {
             // The index map must refuse an image that ends one element too early: shrink it to what
             // the tile's first (full) instance needs and by one more.
