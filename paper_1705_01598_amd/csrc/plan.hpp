@@ -10,8 +10,8 @@
 
 namespace tperm {
 
-// Largest tile the tile kernels accept: NREG_MAX slots per thread, and an LDS image that
-// fits the 64 KiB a workgroup may take without opting in to more.
+// Largest tile the tile kernels accept: kMaxNreg slots per thread, and LDS images that together fit
+// the 64 KiB a workgroup may take without opting in to more.
 constexpr int kMaxNreg = 32;
 constexpr int64_t kMaxTileVol = (int64_t)kMaxNreg * TPERM_MAX_THREADS;  // 8192 elements
 constexpr int64_t kMaxLdsBytes = 64 * 1024;
@@ -26,8 +26,8 @@ constexpr int kDefaultThreads = 256;
 // NO_MASKS in tile_kernel.hpp).
 constexpr int64_t kLeanBytes = 40 * 1000 * 1000;
 constexpr int64_t kLeanBytes24 = 640 * 1000 * 1000;
-// Tensors below this size read with cached loads unless they are line-aligned on both sides (see
-// build_tile_plan).
+// Line-aligned inputs of tensors below this size are read with cached loads where the output is
+// written with nontemporal stores but not line-aligned too (see build_tile_plan).
 constexpr int64_t kCachedLoadBytes = (int64_t)16 << 20;
 constexpr int kDefaultLdsBuffers = 1;
 // Groups of 32 consecutive tiles are dealt to the XCDs in turn: tiles that are neighbours

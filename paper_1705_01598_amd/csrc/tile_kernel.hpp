@@ -236,11 +236,13 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // NO_MASKS: fewer instructions per tile.  Every slot writes and reads the LDS image, whether its
     // element exists in this tile or not: the place of an element that does not exist is only read
     // by stores which are dropped, and slots beyond the tile write the image's last element, where no
-    // element of the tensor lies (Plan::spare).  A tile without an edge of the tensor issues its loads and stores without looking at
-    // masks (a wave-uniform choice).  What it is for: with two wavefronts per SIMD the masked form
-    // spends 43 % of its time issuing instructions on a 27 MB tensor of 12 slots per thread (a dozen
-    // vector and eight scalar ones per slot and tile); this form needs two.  What it costs: where
-    // memory is the bound, workgroups that run apart faster merge fewer of the lines they share.
+    // element of the tensor lies (Plan::spare).  A tile without an edge of the tensor issues its loads
+    // and stores without looking at masks (a wave-uniform choice).  What it is for: on a 28 MB tensor
+    // of 12 slots per thread the masked form spends 43 % of its wavefronts' time issuing instructions,
+    // with 1.6 times the vector and 1.75 times the scalar ones of this form; on large tensors of 24
+    // and 32 slots 2.3 to 2.9 and 2.6 times.  What it costs: where memory is the bound, workgroups
+    // that run apart faster merge fewer of the lines they share (partial line writes of two 1.1 GB
+    // tensors of 24 slots 5.1 -> 6.7 %).
     // Measured (same plan, time with masks / without, geometric means over 10500 candidate plans of
     // 1800 seeded ragged shapes; tensors of up to 20, 40, 80, 160, 320, 640, 1280 and 3400 MB, and
     // beyond 4 GiB):
@@ -569,7 +571,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
                             w[j].y = img[at + oa.lstride_b];
                         }
                     } else if constexpr (!VEC2) {
-                        if (NO_MASKS || write_at(j) != kDroppedOffset) w[j] = img[at];
+                        if (write_at(j) != kDroppedOffset) w[j] = img[at];
                     }
                 }
             } else {

@@ -4,11 +4,11 @@
 // and their exclusive-or, and the sum of a scrambled image of every word, all modulo 2^64 --
 // are computed for both tensors and compared on the device.
 //
-// Work layout: the tensor is cut into chunks of kVerifyChunk elements; one workgroup digests
-// one chunk and writes one partial result (32 bytes) into a scratch buffer, slot = chunk
-// number; a last, single workgroup adds up the partials of both tensors, compares the two
-// totals and writes the verdict.  Every slot that is read has been written by the same call,
-// so the scratch needs no clearing.
+// Work layout: both tensors are cut into chunks of kVerifyChunk elements; one workgroup digests one
+// chunk and writes one partial result (32 bytes) into a scratch buffer, the first tensor's chunks in
+// the slots 0 to chunks - 1 and the second's behind them; a last, single workgroup adds up the
+// differences of the two tensors' partials and writes the verdict.  Every slot that is read has been
+// written by the same call, so the scratch needs no clearing.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
