@@ -999,14 +999,14 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         // Line-aligned input rows against an output that is sector-aligned only (or written in
         // line-aligned windows): nontemporal loads pay off on large tensors, but what they read
         // neither stays in the 256 MB memory-side cache nor serves the neighbouring tile from L2.
-        // Below 16 MiB the loads are cached, a trade by where the input comes from (time nontemporal /
-        // cached, geometric means over 150 seeded shapes; input from HBM, read again and again, three
-        // inputs in turn, just written by another kernel): 1-2 MB 0.98 1.08 1.10 0.94, 2-4 MB 0.98 1.10
-        // 1.11 0.96, 4-8 MB 0.98 1.15 1.16 0.96, 8-16 MB 0.94 1.29 1.21 0.95.  Above, and on tensors that
-        // are line-aligned on both sides, the loss outweighs that: (2624, 3664) fp32, 38 MB, 17.1 ->
-        // 17.3, 17.0 -> 14.7 and, just written, 12.5 -> 14.0 us; 2048^2 fp64 13.9 -> 13.4, 13.7 -> 11.3
-        // and 9.5 -> 10.9.  Plans without nontemporal stores (policy 4) keep their loads at any size,
-        // and 64-thread plans run policy 3 as 2 (see tile_launch_policy).
+        // Below 512 KiB cached loads are as fast or faster wherever the input comes from, and above the
+        // gain on inputs read again costs the others (time nontemporal / cached, geometric means over
+        // 300 seeded shapes; input from HBM, read again and again, three inputs in turn, just written by
+        // another kernel): up to 0.5 MB 1.00 1.08 1.12 1.03, 0.5-1 MB 0.98 1.10 1.13 1.01, 1-2 MB 0.98
+        // 1.08 1.11 0.95, 2-8 MB 0.98 1.12 1.13 0.96, 8-16 MB 0.94 1.29 1.21 0.95.  Likewise on tensors
+        // that are line-aligned on both sides (2048^2 fp64 13.9 -> 13.4, 13.7 -> 11.3, just written 9.5 ->
+        // 10.9 us).  Plans without nontemporal stores (policy 4) keep their loads at any size, and
+        // 64-thread plans run policy 3 as 2 (see tile_launch_policy).
         const bool load_nt = cand.load_nt && !(store_nt && c.volume * elem < kCachedLoadBytes);
         plan->cache_policy = cand.aligned ? 2 : (store_nt ? (load_nt ? 2 : 3) : (load_nt ? 4 : 1));
         // loads before stores pays on line-aligned shapes with small LDS-staged tiles only

@@ -28,7 +28,7 @@ constexpr int64_t kLeanBytes = 40 * 1000 * 1000;
 constexpr int64_t kLeanBytes24 = 640 * 1000 * 1000;
 // Line-aligned inputs of tensors below this size are read with cached loads where the output is
 // written with nontemporal stores but not line-aligned too (see build_tile_plan).
-constexpr int64_t kCachedLoadBytes = (int64_t)16 << 20;
+constexpr int64_t kCachedLoadBytes = (int64_t)512 << 10;
 constexpr int kDefaultLdsBuffers = 1;
 // Groups of 32 consecutive tiles are dealt to the XCDs in turn: tiles that are neighbours
 // along the output run then share an L2, which merges the cache lines they both write

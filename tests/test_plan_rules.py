@@ -8,10 +8,10 @@ from paper_1705_01598_amd import binding as B
 
 
 @pytest.mark.parametrize("d0,d1,elem,policy", [
-    (1024, 2040, 8, 3), (1024, 2056, 8, 2),                        # 16 MiB lies at 1024 x 2048 elements of 8 bytes
-    (2048, 2032, 4, 3), (2048, 2064, 4, 2),
+    (256, 248, 8, 3), (256, 264, 8, 2),                            # 512 KiB lies at 256 x 256 elements of 8 bytes
+    (512, 240, 4, 3), (512, 272, 4, 2), (1024, 2040, 8, 2), (2048, 2032, 4, 2),
 ])
-def test_cached_loads_below_16_mib(d0, d1, elem, policy):
+def test_cached_loads_below_512_kib(d0, d1, elem, policy):
     """Line-aligned input rows, output rows on 64-byte boundaries."""
     info = B.tperm_plan_create_ex((d0, d1), (1, 0), elem, kernel_class=B.KERNEL_TILED, m=1, tile_in=128 // elem, k=1,
                                   tile_out=64, align_out=1, vec2=1).describe()
