@@ -284,6 +284,46 @@ tperm_status_t tperm_cache_tune(int rank, const int64_t *dims, const int *perm, 
 tperm_status_t tperm_cache_stats(int64_t *entries, int64_t *hits, int64_t *misses);
 tperm_status_t tperm_cache_clear(void);
 
+/*
+ * Matrix product added into a permuted tensor: the last two steps of a contraction by transposes
+ * (Section 3.4: matrix product, accumulating transpose) in one kernel, without the product in between.
+ *
+ * The result index i runs over the first left_dims of the dims given, j over the others (first
+ * dimension fastest in both), and out is the tensor of all of them permuted by perm as in
+ * tperm_transpose:  out[pos(i, j)] = out[pos(i, j)] + sum over k of left(i, k) * right(k, j).  The sum
+ * is formed in the working precision (IEEE binary32 / binary64, elem_size 4 / 8), then added once.
+ * left_k_first: 0 = left(i, k) lies at i + extent(i) * k, else at k + extent(k) * i; right_k_first:
+ * 0 = right(k, j) lies at j + extent(j) * k, else at k + extent(k) * j.  Either index may have no
+ * dimensions (left_dims 0 or rank: extent 1).
+ *
+ * create: host only, no device memory.  Statuses of tperm_plan_create, RANK (left_dims outside
+ * 0..rank), DIMS (k < 1), TOO_LARGE (an operand or out of 2^32 - 256 bytes or more).
+ * accumulate: asynchronous on hip_stream; left, right and out are DEVICE pointers aligned to the
+ * element size; out must not overlap the operands (ALIAS; the operands may overlap each other).
+ * workspace: caller-owned DEVICE memory of workspace_bytes >= info.workspace_bytes bytes, aligned to
+ * the element size, apart from the three tensors (NULL, ALIGN, TOO_LARGE, ALIAS); not looked at when
+ * info.workspace_bytes is 0.  It needs no initialisation; two calls that use the same one at the same
+ * time race.  A handle is immutable: concurrent calls on several streams are allowed.  Results do not
+ * depend on how the work is scheduled: the same call on the same values gives the same bits. */
+typedef struct tperm_product_s *tperm_product_t;
+typedef struct {
+    size_t workspace_bytes; /* device memory for partial products; 0: none                      */
+    int pays;               /* 1: expected to be faster than a library product into a buffer and *
+                             * an accumulating transpose                                        */
+    int pieces;             /* the summed index is cut into this many pieces, summed in order   */
+    int shape;              /* tiles: 0 wide, 1 few fast indices, 2 few slow ones               */
+    int vec;                /* neighbours in out that one access moves: 1, 2, 4 elements        */
+    int left_fast;          /* 1: out's stride-1 dimension belongs to left                      */
+} tperm_product_info_t;
+tperm_status_t tperm_product_create(tperm_product_t *product, int rank, const int64_t *dims,
+                                    const int *perm, int left_dims, int64_t k, size_t elem_size,
+                                    int left_k_first, int right_k_first);
+tperm_status_t tperm_product_accumulate(tperm_product_t product, const void *left, const void *right,
+                                        void *out, void *workspace, size_t workspace_bytes,
+                                        void *hip_stream);
+tperm_status_t tperm_product_describe(tperm_product_t product, tperm_product_info_t *info);
+tperm_status_t tperm_product_destroy(tperm_product_t product);
+
 /* Plain device-to-device copy of nbytes with the library's copy kernel: the measured bandwidth
  * ceiling the transposes are compared with, in the way Section 3 normalises by a STREAM
  * figure.  in / out: DEVICE pointers, 4-byte aligned, nbytes a multiple of 4 (ALIGN otherwise),

@@ -32,7 +32,9 @@ EXPORTS = ["tperm_plan_create", "tperm_plan_create_forced", "tperm_plan_create_m
            "tperm_execute", "tperm_execute_accumulate", "tperm_execute_verified", "tperm_execute_verified_static",
            "tperm_plan_describe", "tperm_plan_destroy",
            "tperm_status_string", "tperm_copy_bytes", "tperm_transpose", "tperm_transpose_accumulate",
-           "tperm_cache_tune", "tperm_cache_stats", "tperm_cache_clear"]
+           "tperm_cache_tune", "tperm_cache_stats", "tperm_cache_clear",
+           "tperm_product_create", "tperm_product_accumulate", "tperm_product_describe",
+           "tperm_product_destroy"]
 # include/tperm_tuning.h
 TUNING_EXPORTS = ["tperm_plan_create_ex", "tperm_plan_candidate_count", "tperm_plan_create_candidate",
                   "tperm_plan_index_map", "tperm_plan_model", "tperm_multiset_compare",
@@ -72,6 +74,12 @@ class PlanInfo(ctypes.Structure):
                 ("align_out", ctypes.c_int), ("paired", ctypes.c_int),
                 ("loads_first", ctypes.c_int), ("vec2", ctypes.c_int), ("large", ctypes.c_int),
                 ("without_masks", ctypes.c_int)]
+
+
+class ProductInfo(ctypes.Structure):
+    """tperm_product_info_t"""
+    _fields_ = [("workspace_bytes", ctypes.c_size_t), ("pays", ctypes.c_int), ("pieces", ctypes.c_int),
+                ("shape", ctypes.c_int), ("vec", ctypes.c_int), ("left_fast", ctypes.c_int)]
 
 
 class TpermError(RuntimeError):
@@ -123,6 +131,11 @@ def lib() -> ctypes.CDLL:
         L.tperm_cache_tune.argtypes = [ctypes.c_int, i64p, ip, ctypes.c_size_t, vp, vp, vp]
         L.tperm_cache_stats.argtypes = [i64p, i64p, i64p]
         L.tperm_cache_clear.argtypes = []
+        L.tperm_product_create.argtypes = [ctypes.POINTER(vp), ctypes.c_int, i64p, ip, ctypes.c_int, ctypes.c_int64,
+                                           ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
+        L.tperm_product_accumulate.argtypes = [vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
+        L.tperm_product_describe.argtypes = [vp, ctypes.POINTER(ProductInfo)]
+        L.tperm_product_destroy.argtypes = [vp]
         L.tperm_status_string.argtypes = [ctypes.c_int]
         L.tperm_status_string.restype = ctypes.c_char_p
         for name in EXPORTS + TUNING_EXPORTS:
@@ -385,6 +398,56 @@ def tperm_cache_clear() -> None:
     st = lib().tperm_cache_clear()
     if st != OK:
         raise TpermError(st, "tperm_cache_clear")
+
+
+class Product:
+    """Owns one tperm_product_t: a matrix product added into a permuted tensor."""
+
+    def __init__(self, handle: ctypes.c_void_p):
+        self._h = handle
+
+    @property
+    def handle(self):
+        return self._h
+
+    def destroy(self) -> None:
+        if self._h is not None:
+            lib().tperm_product_destroy(self._h)
+            self._h = None
+
+    def __del__(self):
+        try:
+            self.destroy()
+        except Exception:
+            pass
+
+
+def tperm_product_create(dims: Sequence[int], perm: Sequence[int], left_dims: int, k: int, elem_size: int,
+                         left_k_first: bool = False, right_k_first: bool = False) -> Product:
+    rank, cd, cp = _marshal(dims, perm)
+    h = ctypes.c_void_p()
+    st = lib().tperm_product_create(ctypes.byref(h), rank, cd, cp, int(left_dims), int(k), int(elem_size),
+                                    int(bool(left_k_first)), int(bool(right_k_first)))
+    if st != OK:
+        raise TpermError(st, "tperm_product_create")
+    return Product(h)
+
+
+def tperm_product_describe(product: Product) -> ProductInfo:
+    info = ProductInfo()
+    st = lib().tperm_product_describe(product.handle, ctypes.byref(info))
+    if st != OK:
+        raise TpermError(st, "tperm_product_describe")
+    return info
+
+
+def tperm_product_accumulate(product: Product, left_ptr: int, right_ptr: int, out_ptr: int, stream: int = 0,
+                             workspace_ptr: int = 0, workspace_bytes: int = 0) -> None:
+    st = lib().tperm_product_accumulate(product.handle, ctypes.c_void_p(left_ptr), ctypes.c_void_p(right_ptr),
+                                        ctypes.c_void_p(out_ptr), ctypes.c_void_p(workspace_ptr), int(workspace_bytes),
+                                        ctypes.c_void_p(stream))
+    if st != OK:
+        raise TpermError(st, "tperm_product_accumulate")
 
 
 def tperm_plan_destroy(plan: Plan) -> None:

@@ -82,7 +82,9 @@ def layout(d_labels: str, l_labels: str, r_labels: str, extents: Dict[str, int])
 
 
 class Contraction:
-    """A planned contraction: three cached-plan transposes, one GEMM, workspace included."""
+    """A planned contraction, workspace included: transposes that bring the operands to matrix layout,
+    then a product that is added straight into the destination (``tperm_product_accumulate``), or,
+    where that is expected to be slower, a library product and an accumulating transpose."""
 
     def __init__(self, d_labels: str, l_labels: str, r_labels: str, extents: Dict[str, int], dtype, device="cuda"):
         import torch
@@ -93,43 +95,106 @@ class Contraction:
             raise ValueError("float32 or float64 only")
         self.dtype = dtype
         self.elem = 4 if dtype == torch.float32 else 8
+        self._device = torch.empty(0, dtype=dtype, device=device).device
+        self._t = None
+        self._product, operands = self._one_kernel()
+        if self._product is not None:
+            self._operands = self._buffers(operands)
+            n = B.tperm_product_describe(self._product).workspace_bytes
+            self._workspace = torch.empty(n // self.elem, dtype=dtype, device=self._device) if n else None
+        else:
+            self._library_buffers()
+
+    def _one_kernel(self):
+        """The product that adds into the destination, and the permutations its operands need: None
+        where an operand is in either of the two matrix layouts already."""
+        lay, best = self.lay, None
+        if not 1 <= len(lay.d_labels) <= self._B.TPERM_MAX_RANK:
+            return None, None
+        for summed in (lay.summed, "".join(c for c in lay.r_labels if c in lay.l_labels)):
+            ops = []
+            for labels, free in ((lay.l_labels, lay.free_l), (lay.r_labels, lay.free_r)):
+                if labels in (free + summed, summed + free):
+                    ops.append((None, labels != free + summed, 0))
+                else:
+                    ops.append((tuple(labels.index(c) for c in free + summed), False, math.prod(lay.dims(labels))))
+            if best is None or ops[0][2] + ops[1][2] < best[0][2] + best[1][2]:
+                best = ops
+        try:
+            product = self._B.tperm_product_create(lay.dims(lay.free_l + lay.free_r), lay.t_perm, len(lay.free_l),
+                                                   lay.k, self.elem, best[0][1], best[1][1])
+        except self._B.TpermError:    # tensors of 4 GiB and more
+            return None, None
+        if not self._B.tperm_product_describe(product).pays:
+            return None, None
+        return product, (best[0][0], best[1][0])
+
+    def _buffers(self, perms):
+        """(permutation, buffer) of either operand; inputs already in matrix layout are used in place."""
+        lay, torch = self.lay, self._torch
+        sizes = (lay.m * lay.k, lay.k * lay.n)
+        return [(p, None if p is None else torch.empty(n, dtype=self.dtype, device=self._device))
+                for p, n in zip(perms, sizes)]
+
+    def _library_buffers(self):
         lay = self.lay
         ident = lambda p: tuple(p) == tuple(range(len(p)))
-        # inputs already in matrix layout are used in place
-        self._lp = None if ident(lay.l_perm) else torch.empty(lay.m * lay.k, dtype=dtype, device=device)
-        self._rp = None if ident(lay.r_perm) else torch.empty(lay.k * lay.n, dtype=dtype, device=device)
-        self._t = torch.empty(lay.m * lay.n, dtype=dtype, device=device)
+        self._library = self._buffers([None if ident(p) else p for p in (lay.l_perm, lay.r_perm)])
+        self._t = self._torch.empty(lay.m * lay.n, dtype=self.dtype, device=self._device)
+
+    def _in_one_kernel(self, l, r, d) -> bool:
+        """Whether this call may add into d while it reads its operands.  Operands that are used in place
+        have to lie apart from d and on this object's device; what the library product refuses (operands
+        that require a gradient) goes there to be refused."""
+        if self._product is None:
+            return False
+        for (perm, _), t in zip(self._operands, (l, r)):
+            if perm is None:
+                a, b = t.data_ptr(), d.data_ptr()
+                if t.device != self._device or (t.requires_grad and self._torch.is_grad_enabled()) or \
+                        (a < b + d.numel() * self.elem and b < a + t.numel() * self.elem):
+                    return False
+        return True
 
     def run(self, l, r, d, timings: dict = None) -> None:
-        """d += l * r; all three are flat device tensors of the contraction's dtype."""
+        """d += l * r; all three are flat device tensors of the contraction's dtype.  ``timings`` receives
+        the milliseconds of the steps (transpose_d_ms is 0 where gemm_ms includes that step)."""
         torch, B, lay = self._torch, self._B, self.lay
         for t, labels in ((l, lay.l_labels), (r, lay.r_labels), (d, lay.d_labels)):
             if t.dtype != self.dtype or t.numel() != math.prod(lay.dims(labels)) or not t.is_contiguous():
                 raise ValueError("operand does not match the planned contraction")
+        one_kernel = self._in_one_kernel(l, r, d)
+        if not one_kernel and self._t is None:
+            self._library_buffers()
         stream = torch.cuda.current_stream().cuda_stream
         ev = [torch.cuda.Event(enable_timing=True) for _ in range(5)] if timings is not None else None
         mark = (lambda i: ev[i].record()) if ev else (lambda i: None)
         mark(0)
-        lp, rp = l, r
-        if self._lp is not None:
-            B.tperm_transpose(lay.dims(lay.l_labels), lay.l_perm, self.elem, l.data_ptr(), self._lp.data_ptr(), stream)
-            lp = self._lp
-        mark(1)
-        if self._rp is not None:
-            B.tperm_transpose(lay.dims(lay.r_labels), lay.r_perm, self.elem, r.data_ptr(), self._rp.data_ptr(), stream)
-            rp = self._rp
-        mark(2)
-        # column-major (m x k)(k x n) = (m x n)  is  row-major (n x k)(k x m) = (n x m)
-        torch.mm(rp.view(lay.n, lay.k), lp.view(lay.k, lay.m), out=self._t.view(lay.n, lay.m))
-        mark(3)
-        t_dims = lay.dims(lay.free_l + lay.free_r)
-        B.tperm_transpose(t_dims, lay.t_perm, self.elem, self._t.data_ptr(), d.data_ptr(), stream, accumulate=True)
+        ops = []
+        for i, (t, labels) in enumerate(((l, lay.l_labels), (r, lay.r_labels))):
+            perm, buffer = (self._operands if one_kernel else self._library)[i]
+            if perm is not None:
+                B.tperm_transpose(lay.dims(labels), perm, self.elem, t.data_ptr(), buffer.data_ptr(), stream)
+                t = buffer
+            ops.append(t)
+            mark(1 + i)
+        if one_kernel:
+            ws = self._workspace
+            B.tperm_product_accumulate(self._product, ops[0].data_ptr(), ops[1].data_ptr(), d.data_ptr(), stream,
+                                       0 if ws is None else ws.data_ptr(), 0 if ws is None else ws.numel() * self.elem)
+            mark(3)
+        else:
+            # column-major (m x k)(k x n) = (m x n)  is  row-major (n x k)(k x m) = (n x m)
+            torch.mm(ops[1].view(lay.n, lay.k), ops[0].view(lay.k, lay.m), out=self._t.view(lay.n, lay.m))
+            mark(3)
+            t_dims = lay.dims(lay.free_l + lay.free_r)
+            B.tperm_transpose(t_dims, lay.t_perm, self.elem, self._t.data_ptr(), d.data_ptr(), stream, accumulate=True)
         mark(4)
         if ev:
             ev[4].synchronize()
             names = ("transpose_l_ms", "transpose_r_ms", "gemm_ms", "transpose_d_ms")
             for i, name in enumerate(names):
-                timings[name] = ev[i].elapsed_time(ev[i + 1])
+                timings[name] = 0.0 if one_kernel and i == 3 else ev[i].elapsed_time(ev[i + 1])
             timings["total_ms"] = ev[0].elapsed_time(ev[4])
 
 

@@ -10,6 +10,7 @@
 #include "../../include/tperm_tuning.h"
 #include "kernels.hpp"
 #include "plan.hpp"
+#include "product.hpp"
 #include "verify.hpp"
 
 using tperm::Plan;
@@ -35,6 +36,11 @@ struct tperm_plan_s {
     }
 };
 
+struct tperm_product_s {
+    tperm::Product p;
+    std::atomic<uint64_t> cu_count{0};  // as in tperm_plan_s
+};
+
 namespace {
 
 tperm_status_t device_cu_count(int* num_cu) {
@@ -52,8 +58,9 @@ tperm_status_t device_cu_count(int* num_cu) {
     return TPERM_OK;
 }
 
-// Compute units of the current device, remembered per plan for the device it was asked on.
-tperm_status_t cached_cu_count(tperm_plan_s* handle, int* num_cu) {
+// Compute units of the current device, remembered per handle for the device it was asked on.
+template <typename H>
+tperm_status_t cached_cu_count(H* handle, int* num_cu) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
@@ -329,6 +336,65 @@ tperm_status_t tperm_multiset_compare(const void* a, const void* b, int64_t coun
         (void)hipGetLastError();
         return TPERM_ERR_HIP;
     }
+    return TPERM_OK;
+}
+
+tperm_status_t tperm_product_create(tperm_product_t* product, int rank, const int64_t* dims, const int* perm,
+                                    int left_dims, int64_t k, size_t elem_size, int left_k_first, int right_k_first) {
+    if (product == nullptr) return TPERM_ERR_NULL;
+    *product = nullptr;
+    tperm_product_s* h = new (std::nothrow) tperm_product_s();
+    if (h == nullptr) return TPERM_ERR_NOMEM;
+    const tperm_status_t st = tperm::build_product(&h->p, rank, dims, perm, left_dims, k, elem_size, left_k_first, right_k_first);
+    if (st != TPERM_OK) {
+        delete h;
+        return st;
+    }
+    *product = h;
+    return TPERM_OK;
+}
+
+tperm_status_t tperm_product_accumulate(tperm_product_t product, const void* left, const void* right, void* out,
+                                        void* workspace, size_t workspace_bytes, void* hip_stream) {
+    if (product == nullptr || left == nullptr || right == nullptr || out == nullptr) return TPERM_ERR_NULL;
+    const tperm::Product& p = product->p;
+    const uintptr_t l = (uintptr_t)left, r = (uintptr_t)right, o = (uintptr_t)out;
+    if (((l | r | o) % (uintptr_t)p.elem) != 0) return TPERM_ERR_ALIGN;
+    const uintptr_t l1 = l + (p.left_fast ? p.d.fast_bytes : p.d.slow_bytes);
+    const uintptr_t r1 = r + (p.left_fast ? p.d.slow_bytes : p.d.fast_bytes), o1 = o + p.d.out_bytes;
+    if ((l < o1 && o < l1) || (r < o1 && o < r1)) return TPERM_ERR_ALIAS;
+    if (p.workspace > 0) {
+        if (workspace == nullptr) return TPERM_ERR_NULL;
+        const uintptr_t w = (uintptr_t)workspace, w1 = w + p.workspace;
+        if ((w % (uintptr_t)p.elem) != 0) return TPERM_ERR_ALIGN;
+        if (workspace_bytes < p.workspace) return TPERM_ERR_TOO_LARGE;
+        if ((w < o1 && o < w1) || (w < l1 && l < w1) || (w < r1 && r < w1)) return TPERM_ERR_ALIAS;
+    }
+    int num_cu = 0;
+    const tperm_status_t st = cached_cu_count(product, &num_cu);
+    if (st != TPERM_OK) return st;
+    if (tperm::launch_product(p, left, right, out, workspace, num_cu, (hipStream_t)hip_stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return TPERM_ERR_HIP;
+    }
+    return TPERM_OK;
+}
+
+tperm_status_t tperm_product_describe(tperm_product_t product, tperm_product_info_t* info) {
+    if (product == nullptr || info == nullptr) return TPERM_ERR_NULL;
+    const tperm::Product& p = product->p;
+    info->workspace_bytes = p.workspace;
+    info->pays = p.pays ? 1 : 0;
+    info->pieces = (int)p.d.splits;
+    info->shape = p.shape;
+    info->vec = p.vec;
+    info->left_fast = p.left_fast ? 1 : 0;
+    return TPERM_OK;
+}
+
+tperm_status_t tperm_product_destroy(tperm_product_t product) {
+    if (product == nullptr) return TPERM_ERR_NULL;
+    delete product;
     return TPERM_OK;
 }
 

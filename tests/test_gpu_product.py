@@ -1,0 +1,191 @@
+"""Matrix product added into a permuted tensor (tperm_product_accumulate).
+
+Reference: the product in float64, laid out by torch's permute.  Bound per element: K products, each
+rounded in the working precision (unit roundoff eps), summed in any order with one rounding per step,
+err <= 2 K eps sum_k |l||r| (the standard bound for recursive summation, K eps to first order, doubled
+for the higher orders and for products that are not fused), plus the roundings of the final addition
+and of the reference, 2 eps (|ref| + sum_k |l||r|)."""
+import math
+
+import pytest
+
+from paper_1705_01598_amd import binding as B
+
+# (left dims, right dims, perm, K): tiles are 128 x 32 (fp64) and 128 x 64 (fp32); thin ones 16 x 128,
+# 16 x 256, 256 x 16.  dims count from the stride-1 one, left first.
+CASES = [
+    ((128,), (64,), (0, 1), 16),
+    ((127,), (65,), (0, 1), 15),               # odd edges, odd runs
+    ((129,), (31,), (1, 0), 17),               # the right operand is the fast one
+    ((4, 33), (6, 11), (0, 2, 1, 3), 33),      # runs of 4, digits interleaved
+    ((6, 22), (5, 13), (0, 3, 2, 1), 48),      # runs of 2
+    ((8, 8, 4), (27, 3), (0, 1, 3, 2, 4), 70),
+    ((3, 50), (7, 40), (3, 0, 1, 2), 1),
+    ((5,), (700,), (0, 1), 300),               # few fast indices
+    ((16,), (9, 60), (0, 2, 1), 40),
+    ((17,), (300,), (0, 1), 500),
+    ((600,), (3,), (0, 1), 129),               # few slow indices
+    ((64, 9), (16,), (0, 2, 1), 24),
+    ((605,), (3,), (0, 1), 20),
+    ((602,), (5,), (0, 1), 31),
+    ((40,), (24,), (1, 0), 4096),              # the summed index in pieces
+    ((8,), (9,), (0, 1), 5003),
+    ((300,), (70,), (0, 1), 1000),
+    ((1,), (100,), (1, 0), 20),
+    ((150, 40), (30, 25), (2, 0, 3, 1), 24),   # many tiles to a workgroup
+]
+GUARD = 64
+
+
+def _operand(torch, mat, k_first, offset):
+    """mat (n x K, double, on the host) in memory as the call wants it, `offset` elements into a buffer."""
+    flat = (mat if k_first else mat.t()).contiguous().reshape(-1)
+    buf = torch.full((flat.numel() + offset,), float("nan"), dtype=mat.dtype)
+    buf[offset:] = flat
+    return buf
+
+
+def _run(torch, left, right, perm, k, dtype, lk, rk, offset=0, values=None):
+    m, n = math.prod(left), math.prod(right)
+    gen = torch.Generator().manual_seed(m * 1000 + n + k)
+    rand = lambda *s: torch.rand(*s, generator=gen, dtype=torch.float64).mul_(2).sub_(1).to(dtype)  # noqa: E731
+    l, r, d = (rand(m, k), rand(n, k), rand(m * n)) if values is None else values(rand)
+    dims = list(left) + list(right)
+    prod = B.tperm_product_create(dims, perm, len(left), k, d.element_size(), lk, rk)
+    info = B.tperm_product_describe(prod)
+    ls, rs = (_operand(torch, x, f, offset).cuda() for x, f in ((l, lk), (r, rk)))
+    out = torch.full((m * n + 2 * GUARD + offset,), 7.0, dtype=dtype)
+    lo = GUARD + offset
+    out[lo:lo + m * n] = d
+    out = out.cuda()
+    ws = torch.full((max(1, info.workspace_bytes // d.element_size()),), float("nan"), dtype=dtype, device="cuda")
+    esz = d.element_size()
+    B.tperm_product_accumulate(prod, ls.data_ptr() + offset * esz, rs.data_ptr() + offset * esz, out.data_ptr() + lo * esz,
+                               torch.cuda.current_stream().cuda_stream, ws.data_ptr(), info.workspace_bytes)
+    torch.cuda.synchronize()
+    out = out.cpu()
+    assert bool((out[:lo] == 7.0).all()) and bool((out[lo + m * n:] == 7.0).all()), "wrote outside the destination"
+
+    def arranged(t):                                     # (m x n) -> flat destination order
+        rank = len(dims)
+        axes = [rank - 1 - perm[rank - 1 - i] for i in range(rank)]
+        return t.t().reshape(tuple(reversed(dims))).permute(axes).reshape(-1)
+    ld, rd = l.double(), r.double()
+    ref = d.double() + arranged(ld @ rd.t())
+    size = arranged(ld.abs() @ rd.abs().t())
+    return info, out[lo:lo + m * n], ref, size
+
+
+def _check(torch, got, ref, size, k, dtype):
+    eps = torch.finfo(dtype).eps
+    err = (got.double() - ref).abs()
+    bound = 2 * k * eps * size + 2 * eps * (ref.abs() + size)
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+@pytest.mark.parametrize("left,right,perm,k", CASES)
+def test_product_matches_the_reference(left, right, perm, k, dtype_name):
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    for lk, rk, offset in ((0, 0, 0), (0, 1, 1), (1, 0, 0), (1, 1, 3)):
+        _, got, ref, size = _run(torch, left, right, perm, k, dtype, lk, rk, offset)
+        _check(torch, got, ref, size, k, dtype)
+
+
+def test_the_cases_reach_every_form():
+    seen = set()
+    for elem in (8, 4):
+        for left, right, perm, k in CASES:
+            i = B.tperm_product_describe(B.tperm_product_create(left + right, perm, len(left), k, elem))
+            seen.add((elem, i.shape, i.vec if i.pieces == 1 else 0))
+    # (element, shape, neighbours moved together; 0: in pieces)
+    need = {(8, 0, 1), (8, 0, 2), (8, 0, 0), (8, 1, 1), (8, 1, 0)}
+    need |= {(4, 0, v) for v in (0, 1, 2, 4)} | {(4, 1, v) for v in (0, 1)} | {(4, 2, v) for v in (0, 1, 2, 4)}
+    assert need <= seen, need - seen
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+def test_large_destination(dtype_name):
+    """More than 128 MiB: nontemporal accesses to the destination."""
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    elem = torch.finfo(dtype).bits // 8
+    left, right, perm, k = (8, 8, 61), (27, 40 * 8 // elem), (0, 1, 3, 2, 4), 5
+    left = (8, 8, 61 * 4)
+    info, got, ref, size = _run(torch, left, right, perm, k, dtype, 0, 0)
+    assert math.prod(left) * math.prod(right) * elem > 128 << 20
+    _check(torch, got, ref, size, k, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+def test_special_values(dtype_name):
+    """Subnormal products are not flushed; an infinity or a NaN reaches its own row or column only."""
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    tiny = torch.finfo(dtype).tiny / 1024
+
+    def small(rand):
+        return ((rand(50, 13) * 8).round().to(dtype) * tiny, (rand(21, 13) * 4).round().to(dtype), torch.zeros(50 * 21, dtype=dtype))
+    _, got, ref, _ = _run(torch, (50,), (21,), (1, 0), 13, dtype, 0, 0, values=small)
+    assert torch.equal(got, ref.to(dtype))            # multiples of tiny: every sum is exact
+    assert bool((got != 0).any())
+
+    def odd(rand):
+        l, r, d = rand(130, 9), rand(40, 9), rand(130 * 40)
+        l[129, 8], r[39, 0] = float("inf"), float("nan")
+        return l, r, d
+    _, got, ref, _ = _run(torch, (130,), (40,), (0, 1), 9, dtype, 0, 0, values=odd)
+    assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+
+
+def test_arguments():
+    make = B.tperm_product_create
+    for bad, status in ((dict(left_dims=3), B.ERR_RANK), (dict(left_dims=-1), B.ERR_RANK), (dict(k=0), B.ERR_DIMS),
+                        (dict(elem_size=2), B.ERR_ELEM_SIZE), (dict(perm=(0, 0)), B.ERR_PERM), (dict(dims=(0, 4)), B.ERR_DIMS),
+                        (dict(dims=(1 << 15, 1 << 15)), B.ERR_TOO_LARGE), (dict(k=1 << 28), B.ERR_TOO_LARGE)):
+        args = dict(dims=(5, 4), perm=(1, 0), left_dims=1, k=3, elem_size=8)
+        args.update(bad)
+        with pytest.raises(B.TpermError) as e:
+            make(**args)
+        assert e.value.status == status, bad
+    p = make((5, 4), (1, 0), 1, 3, 8)
+    for ptrs, status in (((0, 8, 4096), B.ERR_NULL), ((4096, 0, 8), B.ERR_NULL), ((4100, 8192, 16384), B.ERR_ALIGN),
+                         ((4096, 8192, 4096 + 8), B.ERR_ALIAS), ((4096, 8192, 8192 - 8), B.ERR_ALIAS)):
+        with pytest.raises(B.TpermError) as e:
+            B.tperm_product_accumulate(p, *ptrs)
+        assert e.value.status == status, ptrs
+    p = make((40, 24), (1, 0), 1, 4096, 8)                     # in pieces: wants a workspace
+    need = B.tperm_product_describe(p).workspace_bytes
+    assert need > 0
+    base = 1 << 30
+    for ws, n, status in ((0, 0, B.ERR_NULL), (4 * base, need - 1, B.ERR_TOO_LARGE), (4 * base + 4, need, B.ERR_ALIGN),
+                          (base, need, B.ERR_ALIAS), (3 * base, need, B.ERR_ALIAS)):
+        with pytest.raises(B.TpermError) as e:
+            B.tperm_product_accumulate(p, base, 2 * base, 3 * base, 0, ws, n)
+        assert e.value.status == status, (ws, n)
+
+
+def test_which_contractions_run_in_one_kernel():
+    pays = lambda m, n, k, elem: B.tperm_product_describe(B.tperm_product_create((m, n), (1, 0), 1, k, elem)).pays  # noqa: E731
+    for elem in (4, 8):
+        assert pays(11264, 1728, 70, elem) and pays(64, 100000, 256, elem)
+    assert not pays(64, 8085, 2048, 4)                         # 88 us against 60
+    assert pays(80, 64, 115620, 8)                             # the library's product runs along the summed index
+
+
+@pytest.mark.gpu
+def test_contraction_whose_operand_is_its_destination():
+    """d += l r with d in place of l: the product is finished before d changes."""
+    torch = pytest.importorskip("torch")
+    from paper_1705_01598_amd.contraction import Contraction
+    con = Contraction("ab", "ak", "kb", dict(a=24, k=24, b=24), torch.float64)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x, y = (torch.rand(24 * 24, dtype=torch.float64, device="cuda", generator=g) for _ in range(2))
+    want = x.view(24, 24) + y.view(24, 24) @ x.view(24, 24)    # row-major views of column-major data
+    t = {}
+    con.run(x, y, x, t)
+    assert torch.allclose(x.view(24, 24), want, rtol=1e-13) and set(t) == {"transpose_l_ms", "transpose_r_ms", "gemm_ms", "transpose_d_ms", "total_ms"}
