@@ -207,7 +207,7 @@ tperm_status_t tperm_plan_destroy(tperm_plan_t plan) {
 }
 
 static tperm_status_t execute_impl(tperm_plan_t plan, const void* in, void* out, void* hip_stream,
-                                   bool accumulate) {
+                                   bool accumulate, bool read_again = false) {
     if (plan == nullptr || in == nullptr || out == nullptr) return TPERM_ERR_NULL;
     if (in == out) return TPERM_ERR_ALIAS;
     const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
@@ -251,7 +251,7 @@ static tperm_status_t execute_impl(tperm_plan_t plan, const void* in, void* out,
             int grid = 0;
             tperm_status_t st = resolve_grid(slot, &grid);
             if (st != TPERM_OK) return st;
-            err = tperm::launch_tile(p, in, out, stream, grid, accumulate);
+            err = tperm::launch_tile(p, in, out, stream, grid, accumulate, read_again);
             break;
         }
         default:
@@ -298,7 +298,7 @@ tperm_status_t tperm_execute_verified(tperm_plan_t plan, const void* in, void* o
     tperm_status_t st = check_verify_args(in, out, (size_t)vol * (size_t)p.elem, verdict, workspace, workspace_bytes,
                                           tperm::verify_scratch_bytes(vol));
     if (st != TPERM_OK) return st;
-    st = execute_impl(plan, in, out, hip_stream, false);
+    st = execute_impl(plan, in, out, hip_stream, false, true);
     if (st != TPERM_OK) return st;
     if (tperm::launch_multiset_compare(in, out, vol, p.elem, workspace, verdict, (hipStream_t)hip_stream) != hipSuccess) {
         (void)hipGetLastError();

@@ -84,8 +84,8 @@ accumulate_kernel(const F* __restrict__ in, F* __restrict__ out, uint64_t n) {
 // dispatch
 // ---------------------------------------------------------------------------------------
 
-static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_aligned_out) {
-    const int pol = tile_launch_policy(plan, acc, sector_aligned_out);
+static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_aligned_out, bool read_again = false) {
+    const int pol = tile_launch_policy(plan, acc, sector_aligned_out, read_again);
     const int nt = pol == 2 ? 2 : (pol == 3 ? 1 : (pol == 4 ? 3 : 0));  // template parameter NT
     const bool align = plan.align_out;
     if (runs_lean(plan, acc))
@@ -114,8 +114,8 @@ hipError_t tile_blocks_per_cu(const Plan& plan, int* blocks) {
 }
 
 hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t stream, int grid,
-                       bool accumulate) {
-    const void* f = tile_kernel_for(plan, accumulate, (reinterpret_cast<uintptr_t>(out) & 31u) == 0);
+                       bool accumulate, bool read_again) {
+    const void* f = tile_kernel_for(plan, accumulate, (reinterpret_cast<uintptr_t>(out) & 31u) == 0, read_again);
     if (f == nullptr || grid < 1) return hipErrorInvalidValue;
     TileDesc d = plan.tile;
     // large tensors: the range one buffer description covers from a tile's origin

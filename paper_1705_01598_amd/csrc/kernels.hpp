@@ -13,9 +13,10 @@ hipError_t tile_blocks_per_cu(const Plan& plan, int* blocks);
 bool tile_kernel_exists(const Plan& plan, bool acc);
 
 // Enqueue the tile kernel (ROWCOPY / TILED / PACKED classes) with `grid` workgroups.
-// accumulate: out = out + transposed in (elements are IEEE floats of the element size).
+// accumulate: out = out + transposed in (elements are IEEE floats of the element size).  read_again:
+// both tensors are about to be read (see tile_launch_policy).
 hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t stream, int grid,
-                       bool accumulate);
+                       bool accumulate, bool read_again = false);
 
 // Enqueue the naive one-thread-per-output-element gather.
 hipError_t launch_naive(const Plan& plan, const void* in, void* out, hipStream_t stream,

@@ -1020,8 +1020,10 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
     return TPERM_OK;
 }
 
-int tile_launch_policy(const Plan& plan, bool acc, bool sector_aligned_out) {
+int tile_launch_policy(const Plan& plan, bool acc, bool sector_aligned_out, bool read_again) {
     int pol = plan.cache_policy;
+    const int64_t bytes = plan.c.volume * plan.elem;
+    if (read_again && bytes < kReadAgainBytes && (pol != 3 || bytes >= kReadAgainBytes3)) return 1;
     if (acc) return pol == 2 && sector_aligned_out && !plan.align_out ? 2 : 1;
     if (!sector_aligned_out && !plan.align_out) pol = (pol == 2 || pol == 4) ? 4 : 1;
     if (pol == 4 && (plan.loads_first || plan.threads != 256)) pol = 1;

@@ -135,7 +135,14 @@ inline bool runs_without_masks(const Plan& p, bool accumulate) {
 // under the policy: 2 +6 to +14 % (145 seeded shapes of 4 to 1600 MB, 0.95 at worst; 64-element
 // rows of fp64, 467 MB, 89.0 -> 78.3 us), 4 -3 % (100 shapes, 0.87 to 1.07; -4 % above 128 MB), 2
 // turned into 4 by an odd base pointer -9 to +7 % (100 shapes, 0.72 to 1.14).
-int tile_launch_policy(const Plan& plan, bool accumulate, bool sector_aligned_out);
+// read_again: both tensors are read right behind the transpose (the self-checking execute).  As long as
+// they fit the memory-side cache together, or nearly, they had better stay there: cached up to
+// kReadAgainBytes, with policy 3 from kReadAgainBytes3 on (its loads are cached anyway).  Time of the
+// whole call under the policy / cached, geometric means over 134 seeded shapes; tensors of up to 32, 64,
+// 128, 160, 200, 260, 400 MB: policy 2 1.06 1.03 1.05 1.05 1.00 0.95 0.93; 4 1.04 1.04 1.07 1.05 - 1.01 0.98; 3 1.00 0.99 1.03 1.03 0.99
+// 0.95 0.93.
+constexpr int64_t kReadAgainBytes = 160 * 1000 * 1000, kReadAgainBytes3 = 64 * 1000 * 1000;
+int tile_launch_policy(const Plan& plan, bool accumulate, bool sector_aligned_out, bool read_again = false);
 
 tperm_status_t validate(int rank, const int64_t* dims, const int* perm, size_t elem);
 void canonicalise(int rank, const int64_t* dims, const int* perm, Canonical* out);

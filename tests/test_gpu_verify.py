@@ -121,3 +121,24 @@ def test_execute_verified_argument_errors_launch_nothing():
         assert e.value.status == status
     torch.cuda.synchronize()
     assert bool((out.view() == out.sent).all()) and int(verdict[0].item()) == 99     # untouched
+
+
+@pytest.mark.parametrize("dims,perm,elem,policy", [
+    ((512, 96), (1, 0), 8, 2), ((256, 1001), (1, 0), 8, 4), ((1001, 64, 72), (1, 0, 2), 4, 3), ((1000, 72, 250), (1, 0, 2), 4, 3)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_execute_verified_under_every_cache_policy(dims, perm, elem, policy, off):
+    """The transposing step takes other cache policies than tperm_execute (72 MB: the one case of
+    policy 3 that does); the result does not depend on them, at either output alignment."""
+    case = wl.make_case(0, 78, dims, perm, elem)
+    a = wl.bitpattern_values(case)
+    a_dev = to_device(a)
+    out = GuardedOut(case.volume, elem, off)
+    verdict = torch.full((1,), 99, dtype=torch.int64, device="cuda")
+    nws = B.verify_workspace_bytes(case.volume)
+    ws = torch.empty(nws // 8, dtype=torch.int64, device="cuda")
+    plan = B.tperm_plan_create(dims, perm, elem)
+    assert plan.describe().cache_policy == policy
+    B.tperm_execute_verified(plan, a_dev.data_ptr(), out.ptr, _stream(), verdict.data_ptr(), ws.data_ptr(), nws)
+    torch.cuda.synchronize()
+    assert np.array_equal(np_uint(out.view().cpu().numpy()), oracle.transpose(a, dims, perm))
+    assert out.guards_intact() and int(verdict.item()) == 0
