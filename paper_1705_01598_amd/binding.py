@@ -14,6 +14,7 @@ from typing import Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtperm.so")
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
 
 TPERM_MAX_RANK = 16
 
@@ -89,15 +90,16 @@ class TpermError(RuntimeError):
 
 
 _lib = None
+_fast = None    # the extension module that converts the arguments of the execute calls
 
 
 def lib() -> ctypes.CDLL:
     """Load libtperm.so (raises if it has not been built)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                f"{LIB_PATH} is missing: build it with `python -m paper_1705_01598_amd.build`")
+        for path in (LIB_PATH, FASTCALL_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(f"{path} is missing: build it with `python -m paper_1705_01598_amd.build`")
         L = ctypes.CDLL(LIB_PATH)
         vp = ctypes.c_void_p
         i64p = ctypes.POINTER(ctypes.c_int64)
@@ -141,6 +143,11 @@ def lib() -> ctypes.CDLL:
         for name in EXPORTS + TUNING_EXPORTS:
             if name != "tperm_status_string":
                 getattr(L, name).restype = ctypes.c_int
+        from . import _fastcall
+        _fastcall.bind(*(ctypes.cast(getattr(L, name), vp).value for name in (
+            "tperm_execute", "tperm_execute_accumulate", "tperm_execute_verified", "tperm_transpose",
+            "tperm_transpose_accumulate", "tperm_product_accumulate")))
+        _fast = _fastcall
         _lib = L
     return _lib
 
@@ -169,6 +176,7 @@ class Plan:
 
     def __init__(self, handle: ctypes.c_void_p):
         self._h = handle
+        self._addr = handle.value    # what the execute calls take; None once destroyed
 
     @property
     def handle(self):
@@ -183,7 +191,7 @@ class Plan:
     def destroy(self) -> None:
         if self._h is not None:
             lib().tperm_plan_destroy(self._h)
-            self._h = None
+            self._h = self._addr = None
 
     def __del__(self):
         try:
@@ -280,15 +288,13 @@ def tperm_plan_create_candidate(dims: Sequence[int], perm: Sequence[int], elem_s
 
 
 def tperm_execute(plan: Plan, in_ptr: int, out_ptr: int, stream: int = 0) -> None:
-    st = lib().tperm_execute(plan.handle, ctypes.c_void_p(in_ptr), ctypes.c_void_p(out_ptr),
-                             ctypes.c_void_p(stream))
+    st = _fast.execute(plan._addr, in_ptr, out_ptr, stream)
     if st != OK:
         raise TpermError(st, "tperm_execute")
 
 
 def tperm_execute_accumulate(plan: Plan, in_ptr: int, out_ptr: int, stream: int = 0) -> None:
-    st = lib().tperm_execute_accumulate(plan.handle, ctypes.c_void_p(in_ptr), ctypes.c_void_p(out_ptr),
-                                        ctypes.c_void_p(stream))
+    st = _fast.accumulate(plan._addr, in_ptr, out_ptr, stream)
     if st != OK:
         raise TpermError(st, "tperm_execute_accumulate")
 
@@ -303,9 +309,7 @@ def verify_workspace_bytes(volume: int) -> int:
 
 def tperm_execute_verified(plan: Plan, in_ptr: int, out_ptr: int, stream: int, verdict_ptr: int,
                            workspace_ptr: int, workspace_bytes: int) -> None:
-    st = lib().tperm_execute_verified(plan.handle, ctypes.c_void_p(in_ptr), ctypes.c_void_p(out_ptr),
-                                      ctypes.c_void_p(stream), ctypes.c_void_p(verdict_ptr),
-                                      ctypes.c_void_p(workspace_ptr), int(workspace_bytes))
+    st = _fast.verified(plan._addr, in_ptr, out_ptr, stream, verdict_ptr, workspace_ptr, workspace_bytes)
     if st != OK:
         raise TpermError(st, "tperm_execute_verified")
 
@@ -369,10 +373,9 @@ def tperm_plan_model(plan: Plan) -> Model:
 def tperm_transpose(dims: Sequence[int], perm: Sequence[int], elem_size: int, in_ptr: int,
                     out_ptr: int, stream: int = 0, accumulate: bool = False) -> None:
     """Cached-plan transpose (tperm_transpose / tperm_transpose_accumulate)."""
-    rank, cd, cp = _marshal(dims, perm)
-    fn = lib().tperm_transpose_accumulate if accumulate else lib().tperm_transpose
-    st = fn(rank, cd, cp, int(elem_size), ctypes.c_void_p(in_ptr), ctypes.c_void_p(out_ptr),
-            ctypes.c_void_p(stream))
+    if _fast is None:
+        lib()
+    st = _fast.transpose(dims, perm, elem_size, in_ptr, out_ptr, stream, accumulate)
     if st != OK:
         raise TpermError(st, "tperm_transpose")
 
@@ -405,6 +408,7 @@ class Product:
 
     def __init__(self, handle: ctypes.c_void_p):
         self._h = handle
+        self._addr = handle.value    # what the execute calls take; None once destroyed
 
     @property
     def handle(self):
@@ -413,7 +417,7 @@ class Product:
     def destroy(self) -> None:
         if self._h is not None:
             lib().tperm_product_destroy(self._h)
-            self._h = None
+            self._h = self._addr = None
 
     def __del__(self):
         try:
@@ -443,9 +447,7 @@ def tperm_product_describe(product: Product) -> ProductInfo:
 
 def tperm_product_accumulate(product: Product, left_ptr: int, right_ptr: int, out_ptr: int, stream: int = 0,
                              workspace_ptr: int = 0, workspace_bytes: int = 0) -> None:
-    st = lib().tperm_product_accumulate(product.handle, ctypes.c_void_p(left_ptr), ctypes.c_void_p(right_ptr),
-                                        ctypes.c_void_p(out_ptr), ctypes.c_void_p(workspace_ptr), int(workspace_bytes),
-                                        ctypes.c_void_p(stream))
+    st = _fast.product(product._addr, left_ptr, right_ptr, out_ptr, workspace_ptr, stream, workspace_bytes)
     if st != OK:
         raise TpermError(st, "tperm_product_accumulate")
 

@@ -4,16 +4,18 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtperm.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")   # Python calls of the execute entry points (CPython extension)
 PROBE = os.path.join(HERE, "pattern_probe")
 LATENCY_PROBE = os.path.join(HERE, "latency_probe")
 SOURCES = ["plan.cpp", "model.cpp", "api.cpp", "cache.cpp", "kernels.hip", "verify.hip", "product.hip", "tile_inst_u64_256.hip", "tile_inst_u32_256.hip",
            "tile_inst_u64_64.hip", "tile_inst_u32_64.hip", "tile_inst_big_u64.hip", "tile_inst_big_u32.hip",
            "tile_inst_lean_u64.hip", "tile_inst_lean_u32.hip"]
-HEADERS = ["pattern_probe.hip", "latency_probe.hip", "plan.hpp", "kernels.hpp", "verify.hpp", "product.hpp", "tperm_desc.h", "tile_kernel.hpp", os.path.join("..", "..", "include", "tperm.h"),
+HEADERS = ["fastcall.cpp", "pattern_probe.hip", "latency_probe.hip", "plan.hpp", "kernels.hpp", "verify.hpp", "product.hpp", "tperm_desc.h", "tile_kernel.hpp", os.path.join("..", "..", "include", "tperm.h"),
            os.path.join("..", "..", "include", "tperm_tuning.h")]
 
 # -packed-fp32-ops is switched off for all device code built here (no packed FP32
@@ -32,9 +34,9 @@ def hipcc() -> str:
 
 
 def needs_build() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(FASTCALL):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(FASTCALL))
     deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
     return any(os.path.getmtime(d) > t for d in deps)
 
@@ -57,6 +59,11 @@ def build(force: bool = True, verbose: bool = False) -> str:
         if p.wait() != 0:
             raise RuntimeError("compile failed: " + " ".join(cmd))
     cmd = [hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    cmd = [hipcc(), *COMMON_FLAGS, *HOST_FLAGS, "-I" + sysconfig.get_paths()["include"], "-shared",
+           os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
