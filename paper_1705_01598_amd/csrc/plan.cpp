@@ -993,7 +993,16 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         // workgroups from 6 KiB tiles up, three below)
         const double tile_bytes = (double)cand.tile_vol * elem;
         int bpc = (int)std::lround((cand.use_lds ? 20480.0 : 14336.0) / tile_bytes);
-        plan->blocks_per_cu = std::max(2, std::min(8, bpc));
+        bpc = std::max(2, std::min(8, bpc));
+        // With few rounds of tiles the start of so many workgroups (dispatch, index tables) is what
+        // counts: more than four per compute unit lose.  Time with 5 to 8 / with 4, geometric mean (least)
+        // over 139 seeded tensors of 0.4 to 22 MB; below 0.5, 1, 1.5, 2, 2.5 and 3.5 rounds: 8 workgroups
+        // 1.00 (0.98) 1.13 (1.07) 1.16 (1.12) 1.09 (1.06) 1.07 (1.04) 1.07; 7: 1.00 1.05 1.09 1.11 - 0.98;
+        // 6: 1.00 1.03 1.03 1.02 1.04 1.03; 5: 1.00 1.01 1.07 (1.06) 0.98 (0.96) 1.01 1.01.  Three lose from
+        // two rounds on (0.95 to 1.04), two almost everywhere.
+        const double rounds = (double)d.num_tiles / (256.0 * bpc);
+        if (bpc > 4 && rounds < (bpc == 5 ? 1.5 : 2.5)) bpc = 4;
+        plan->blocks_per_cu = bpc;
         // aligned windows write whole lines, whatever the granule of the rows
         const bool store_nt = cand.store_nt || align_out;
         // Line-aligned input rows against an output that is sector-aligned only (or written in

@@ -88,3 +88,13 @@ def test_argument_arrays_are_taken_by_value():
             B.tperm_plan_create(bad, [2, 0, 1] if len(bad) != 0 else [], 8)
     with pytest.raises(TypeError):
         B.tperm_plan_create(iter((6, 5, 4)), (2, 0, 1), 8)
+
+
+@pytest.mark.parametrize("n,tile_in,workgroups", [
+    (1279, 16, 4), (1281, 16, 8),        # tiles of 2 KiB, eight to a compute unit: four below 2.5 rounds of 2048
+    (959, 32, 4), (961, 32, 5),          # tiles of 4 KiB, five: four below 1.5 rounds of 1280
+])
+def test_workgroups_of_small_tensors(n, tile_in, workgroups):
+    info = B.tperm_plan_create_ex((32, 32, n), (1, 0, 2), 8, kernel_class=B.KERNEL_TILED, m=1, tile_in=tile_in, k=1,
+                                  tile_out=16, align_out=1, vec2=1).describe()
+    assert info.blocks_per_cu == workgroups, B.info_dict(info)
