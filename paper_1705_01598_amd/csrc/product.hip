@@ -118,13 +118,15 @@ template <typename T, int FREE, bool K_FIRST> struct Panel {
     // the panel at (f0, k0) of a tensor of n x depth elements
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t n, uint32_t depth, uint32_t f0, uint32_t k0) {
         const uint32_t soff = (K_FIRST ? k0 + depth * f0 : f0 + n * k0) * (uint32_t)sizeof(T);
-        if (K_FIRST ? k0 + kDepth <= depth : f0 + FREE <= n) {
-            // vectors are there or not as a whole
+        // Vectors along the free index may run past its end wherever another row follows: what they
+        // fetch there reaches rows and columns of the result that do not exist.  The summed index has to
+        // end exactly.
+        if (K_FIRST ? k0 + kDepth <= depth : f0 + FREE <= n || (k0 + kDepth < depth && n >= (uint32_t)V)) {
 #pragma unroll
             for (int p = 0; p < kPasses; ++p) {
                 uint32_t f, k;
                 place(p, &f, &k);
-                const bool there = K_FIRST ? f0 + f < n : k0 + k < depth;
+                const bool there = f0 + f < n && (K_FIRST || k0 + k < depth);
                 reg[p].load(r, there ? (K_FIRST ? k + depth * f : f + n * k) * (uint32_t)sizeof(T) : kDropped, soff);
             }
         } else {
@@ -420,10 +422,11 @@ static double product_us(int elem, double units, uint32_t depth, bool split) {
 }
 
 // The same for the library's product and the transpose that adds it: its rate on large products, a
-// floor for small ones (fp64 ones also run along the summed index), two passes over the product.
+// floor for small ones, where the host is the bound (fp64 products also run along the summed index), two
+// passes over the product.
 static double library_us(const ProductDesc& d, int elem) {
     const double flops = 2.0 * d.n_fast * d.n_slow * (double)d.k;
-    const double gemm = elem == 8 ? std::max({10.0, flops / 55e6, 0.035 * d.k}) : std::max(12.0, flops / 100e6);
+    const double gemm = elem == 8 ? std::max({18.0, flops / 58e6, 0.035 * d.k}) : std::max(20.0, flops / 140e6);
     return gemm + 2.0 * d.out_bytes / 4.5e6;
 }
 
@@ -516,11 +519,11 @@ tperm_status_t build_product(Product* p, int rank, const int64_t* dims, const in
     }
     p->workspace = d.splits > 1u ? (size_t)tiles * d.splits * p->tile_bytes : 0;
     d.per_xcd = (uint32_t)((tiles * d.splits + 7u) / 8u);
-    // Up to 256 summed indices the one kernel wins (334 seeded contractions: 1.9 to 2.2 times the speed up
-    // to 128, 1.3 to 1.5 up to 256, the slowest 0.88); beyond that where the estimates say so (366: 12
-    // slower, by up to 24 %; always taken, 71 would be, by up to 31 %).  Of 350 others the rule takes 257,
-    // 2.2 times as fast together, 7 of them slower, 16 % at worst.
-    p->pays = d.k <= 256 || best <= (elem == 8 ? 1.0 : 0.9) * library_us(d, p->elem);
+    // Up to 256 summed indices the one kernel wins (334 of 700 seeded contractions: 1.9 to 2.3 times the
+    // speed up to 128, 1.3 to 1.5 up to 256, the slowest 0.87); beyond that it is taken where the
+    // estimates say so: one of the other 366 is slower then, by 13 %, the rest 1.5 times as fast together
+    // (always taken, 55 would be slower, by up to 28 %).
+    p->pays = d.k <= 256 || best <= library_us(d, p->elem);
     return TPERM_OK;
 }
 

@@ -173,7 +173,7 @@ def test_which_contractions_run_in_one_kernel():
     pays = lambda m, n, k, elem: B.tperm_product_describe(B.tperm_product_create((m, n), (1, 0), 1, k, elem)).pays  # noqa: E731
     for elem in (4, 8):
         assert pays(11264, 1728, 70, elem) and pays(64, 100000, 256, elem)
-    assert not pays(64, 8085, 2048, 4)                         # 88 us against 60
+    assert not pays(64, 8085, 2048, 4)                         # 83 us against 60
     assert pays(80, 64, 115620, 8)                             # the library's product runs along the summed index
 
 
