@@ -9,18 +9,29 @@
 
 namespace tperm {
 
-// keep in step with the instantiation lists in kernels.hip
+// Slots per thread the kernels are instantiated for; keep in step with tile_kernel_ptr.  A slot beyond the
+// tile is issued like the others (its accesses are dropped), and wavefronts that are bound by what they
+// issue pay for it, so LDS-staged tiles of single elements have counts in between too (kNregSetSingle).
+// The same 50 tiles with the next larger count of kNregSet256 / with these, means: 12 -> 10 slots 1.08 (4-byte
+// elements; 1.00 to 1.12) and 1.02 (8-byte), 8 -> 7 1.03 and 1.01, 16 -> 14 1.05, 6 -> 5 1.04, above kLeanBytes only:
+// below, six slots run without masks and five do not.  The least 0.993.
+// 20 slots lose against 24 (0.97, 4-byte elements above kLeanBytes); pairs and the row copy gain 0 to 2 %.
 static const int kNregSet256[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+static const int kNregSetSingle[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 24, 32};
 static const int kNregSet64[] = {4, 8, 12, 16, 24, 32};
 
-int pick_nreg(int64_t tile_vol, int threads) {
-    const int64_t need = (tile_vol + threads - 1) / threads;
-    const int* set = threads == 64 ? kNregSet64 : kNregSet256;
-    const int n = threads == 64 ? (int)(sizeof(kNregSet64) / sizeof(int))
-                                : (int)(sizeof(kNregSet256) / sizeof(int));
-    for (int i = 0; i < n; ++i)
-        if (set[i] >= need) return set[i];
+template <size_t N>
+static int first_of(const int (&set)[N], int64_t need) {
+    for (int n : set)
+        if (n >= need) return n;
     return -1;
+}
+
+int pick_nreg(int64_t tile_vol, int threads, bool single, int64_t bytes) {
+    const int64_t need = (tile_vol + threads - 1) / threads;
+    if (threads == 64) return first_of(kNregSet64, need);
+    if (!single || (need == 5 && bytes < kLeanBytes)) return first_of(kNregSet256, need);
+    return first_of(kNregSetSingle, need);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -841,7 +852,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
         d.oa.total_slots = (uint32_t)cand.tile_vol;
         d.oa.in_halo_elems = (uint32_t)(line_elems * sI[q0]);
     }
-    const int nreg = pick_nreg(read_vol, threads);
+    const int nreg = pick_nreg(read_vol, threads, cand.use_lds, c.volume * elem);  // pairs choose their own below
     if (nreg < 0) return TPERM_ERR_KERNEL;
 
     // LDS image: tile in input order, rows of the contiguous input run separated by a padded

@@ -58,9 +58,10 @@ constexpr double kAlign4HaloWeight = 1.0;
 constexpr double kAlign4HaloPower = 2.0;
 constexpr double kAlign4Weight = 0.7;
 
-// The per-thread slot counts the tile kernel is instantiated for, by workgroup size.
+// The per-thread slot counts the tile kernel is instantiated for, by workgroup size; single: for
+// LDS-staged tiles of single elements, which have more of them, of a tensor of that many bytes.
 // Returns the smallest instantiated count >= need, or -1.
-int pick_nreg(int64_t tile_vol, int threads);
+int pick_nreg(int64_t tile_vol, int threads, bool single = false, int64_t bytes = 0);
 
 struct Canonical {
     int rank = 0;

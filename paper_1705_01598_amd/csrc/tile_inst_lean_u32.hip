@@ -19,8 +19,11 @@ static const void* lean_kernel_ptr(int nt) {
 const void* tile_kernel_lean_u32(int nreg, int nt) {
     switch (nreg) {
         case 6: return lean_kernel_ptr<6>(nt);
+        case 7: return lean_kernel_ptr<7>(nt);
         case 8: return lean_kernel_ptr<8>(nt);
+        case 10: return lean_kernel_ptr<10>(nt);
         case 12: return lean_kernel_ptr<12>(nt);
+        case 14: return lean_kernel_ptr<14>(nt);
         case 16: return lean_kernel_ptr<16>(nt);
         case 24: return lean_kernel_ptr<24>(nt);
         default: return nullptr;

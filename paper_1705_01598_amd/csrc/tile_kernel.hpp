@@ -331,11 +331,11 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     uint32_t wr_aux[NREG];   // ALIGN: unshifted tile coordinate along the shifted dim |
                              // phase of the row start << 16
     {
-        // Slots walk the tile dims in groups of up to four: each dim's constants are fetched
-        // once per group (scalar loads) and the group's independent digit steps overlap,
-        // instead of one dependent chain per slot that waits for the same loads again.
+        // Slots walk the tile dims in groups of up to four (5 of 5 and 10 slots, 7 of 7 and 14): each dim's
+        // constants are fetched once per group (scalar loads) and the group's independent digit steps
+        // overlap, instead of one dependent chain per slot that waits for the same loads again.
         // Larger groups would raise the register peak of the kernel above the main loop's.
-        constexpr int G = NREG <= 4 ? NREG : (NREG % 4 == 0 ? 4 : 3);
+        constexpr int G = NREG <= 5 ? NREG : (NREG % 4 == 0 ? 4 : (NREG % 5 == 0 ? 5 : (NREG % 7 == 0 ? 7 : 3)));
         static_assert(NREG % G == 0, "slot groups must tile the slots");
         // ALIGN: the write side has fewer slots than the read side (no halo)
         const uint32_t write_slots = ALIGN ? oa.total_slots : tile_vol;
@@ -675,6 +675,16 @@ static const void* tile_kernel_ptr(int nreg) {
             TPERM_CASE(2)
             TPERM_CASE(3)
             TPERM_CASE(6)
+            default:
+                break;
+        }
+    }
+    if constexpr (THREADS == 256 && USE_LDS && !VEC2) {
+        switch (nreg) {
+            TPERM_CASE(5)
+            TPERM_CASE(7)
+            TPERM_CASE(10)
+            TPERM_CASE(14)
             default:
                 break;
         }

@@ -96,3 +96,51 @@ def test_accumulation_under_every_cache_policy(policy, elem, large):
             ref = b + oracle.transpose(a, dims, perm)      # one IEEE addition per element: exact
             assert np.array_equal(np_uint(out.view().cpu().numpy()), np_uint(ref)), (dims, perm, offset)
             assert out.guards_intact()
+
+
+@pytest.mark.parametrize("elem", [4, 8])
+@pytest.mark.parametrize("t0,t1,nreg", [(56, 32, 7), (58, 29, 7), (64, 40, 10), (47, 49, 10), (64, 56, 14), (59, 60, 14)])
+def test_slot_counts_between_the_powers(t0, t1, nreg, elem):
+    """7, 10 and 14 slots, filled to the last and with the last few empty: without masks, with masks and the loads
+    first, for large tensors, in line-aligned windows and accumulating, with edges on either dim and on both."""
+    ftype = np.float64 if elem == 8 else np.float32
+    tile = dict(kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1, vec2=1, align_out=1)
+    for i, (d0, d1) in enumerate([(t0, t1), (3 * t0 + 1, 2 * t1), (2 * t0, 2 * t1 - 1), (2 * t0 - 1, t1 + 1)]):
+        dims, perm = (d0, 3, d1), (2, 0, 1) if i % 2 else (2, 1, 0)
+        for policy in (1, 2, 3, 4):
+            info = _run(dims, perm, elem, **tile, cache_policy=policy, lds_buffers=1 + i % 2, lds_pad=(0, -1, -1, 1)[i], loads_first=1)
+            assert info.nreg == nreg and info.without_masks & 1 and info.large == 0
+            info = _run(dims, perm, elem, **tile, cache_policy=policy, large=1)
+            assert info.nreg == nreg and info.large == 1
+        info = _run(dims, perm, elem, **tile, loads_first=2)
+        assert info.nreg == nreg and info.loads_first == 1
+        plan = B.tperm_plan_create_ex(dims, perm, elem, **tile)
+        vol = d0 * 3 * d1
+        rng = np.random.default_rng(vol)
+        a, b = (rng.standard_normal(vol).astype(ftype) for _ in range(2))
+        a_dev, out = to_device(a), GuardedOut(vol, elem)
+        out.view().copy_(to_device(b))
+        B.tperm_execute_accumulate(plan, a_dev.data_ptr(), out.ptr, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert np.array_equal(np_uint(out.view().cpu().numpy()), np_uint(b + oracle.transpose(a, dims, perm)))
+        assert out.guards_intact()
+
+
+@pytest.mark.parametrize("elem,t0,t1,nreg", [(4, 28, 32, 7), (4, 24, 64, 10), (4, 39, 32, 10), (4, 56, 32, 14),
+                                             (8, 56, 16, 7), (8, 47, 32, 10), (8, 55, 48, 14)])
+def test_windows_of_the_slot_counts_between(elem, t0, t1, nreg):
+    """Windows read a line more along the output run than they write."""
+    line = 128 // elem
+    for d1 in (5 * line + 5, 2 * t1 + 1):
+        for policy in (1, 2, 3, 4):
+            info = _run((3 * t0 + 1, 3, d1), (2, 0, 1), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1,
+                        vec2=1, align_out=2, cache_policy=policy)
+            assert info.align_out == 1 and info.nreg == nreg
+
+
+@pytest.mark.parametrize("elem", [4, 8])
+def test_five_slots_from_the_size_of_masked_forms_on(elem):
+    for mb, nreg in ((39, 6), (41, 5)):
+        info = _run((61, 20, mb * 1_000_000 // elem // (61 * 20)), (1, 0, 2), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=61,
+                    k=1, tile_out=20, vec2=1)
+        assert info.nreg == nreg
