@@ -1,13 +1,15 @@
-"""Tensor contraction D += L * R through transposes and one GEMM (application layer).
+"""Tensor contraction D += L * R through transposes and one product (application layer).
 
 The use the paper makes of its transpose library (Section 3.4: the indirect, "transpose -
 transpose - GEMM - transpose" implementation of a binary tensor contraction): the left input is
 brought to the layout (uncontracted dims, contracted dims), the right input to (contracted dims,
-uncontracted dims), one matrix product gives the result in the layout (left uncontracted, right
-uncontracted), and a last transpose accumulates it into the destination.  The three transposes
-run through the tperm library (the last one with ``tperm_transpose_accumulate``); the matrix
-product is the vendor GEMM reached through ``torch.mm`` (hipBLASLt / rocBLAS).  Everything here
-is argument bookkeeping around those two.
+uncontracted dims), a matrix product gives the result in the layout (left uncontracted, right
+uncontracted), and that is transposed and accumulated into the destination.  The first two
+transposes run through the tperm library.  The last two steps are one kernel of it, which adds the
+product straight into the destination (``tperm_product_accumulate``), where its plan says that pays;
+else, and for operands it does not take, the product is the vendor GEMM reached through ``torch.mm``
+(hipBLASLt / rocBLAS) and the last step ``tperm_execute_accumulate``.  Everything here is argument
+bookkeeping around those.
 
 Conventions as everywhere in this package: a tensor is a flat buffer, the FIRST label / extent
 is the stride-1 dimension.  A contraction is given by three label strings, e.g.
