@@ -14,7 +14,8 @@ namespace tperm {
 // issue pay for it, so LDS-staged tiles of single elements have counts in between too (kNregSetSingle).
 // The same 50 tiles with the next larger count of kNregSet256 / with these, means: 12 -> 10 slots 1.08 (4-byte
 // elements; 1.00 to 1.12) and 1.02 (8-byte), 8 -> 7 1.03 and 1.01, 16 -> 14 1.05, 6 -> 5 1.04, above kLeanBytes only:
-// below, six slots run without masks and five do not.  The least 0.993.
+// below, six slots run without masks and five do not.  The least 0.993.  Accumulating (110 tiles) 1.06, 1.02, 1.04,
+// 1.00 (8-byte) and 1.02, the least 0.986; line-aligned windows of 8-byte elements (37) 1.03, 1.04 with 7, the least 0.999.
 // 20 slots lose against 24 (0.97, 4-byte elements above kLeanBytes); pairs and the row copy gain 0 to 2 %.
 static const int kNregSet256[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 static const int kNregSetSingle[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 24, 32};
