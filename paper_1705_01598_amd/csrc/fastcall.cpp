@@ -97,23 +97,33 @@ PyObject* product(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return PyLong_FromLong(st);
 }
 
-// The entries of a sequence as integers; up to TPERM_MAX_RANK of them (the library refuses longer ones
-// by their number alone).  Returns their number, -1 with an exception set.
+// The entries of an iterable as integers; up to TPERM_MAX_RANK of them (the library refuses longer ones
+// by their number alone).  Returns their number, -1 with an exception set.  A conversion may run Python
+// code, and so may change the iterable: a tuple stays as it is, anything else goes through its
+// iterator, which holds a reference to each entry and ends where the entries do.
 template <typename Int>
 Py_ssize_t entries(PyObject* o, Int* out) {
-    PyObject* seq = PySequence_Fast(o, "extents and permutation are sequences of integers");
-    if (seq == nullptr) return -1;
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        int64_t v;
-        if (!to_int64(PySequence_Fast_GET_ITEM(seq, i), &v)) {
-            Py_DECREF(seq);
-            return -1;
+    Py_ssize_t n = 0;
+    int64_t v;
+    if (PyTuple_CheckExact(o)) {
+        const Py_ssize_t size = PyTuple_GET_SIZE(o);
+        for (; n < size; ++n) {
+            if (!to_int64(PyTuple_GET_ITEM(o, n), &v)) return -1;
+            if (n < TPERM_MAX_RANK) out[n] = (Int)v;
         }
-        if (i < TPERM_MAX_RANK) out[i] = (Int)v;
+        return n;
     }
-    Py_DECREF(seq);
-    return n;
+    PyObject* it = PyObject_GetIter(o);
+    if (it == nullptr) return -1;
+    while (PyObject* item = PyIter_Next(it)) {
+        const bool ok = to_int64(item, &v);
+        Py_DECREF(item);
+        if (!ok) break;
+        if (n < TPERM_MAX_RANK) out[n] = (Int)v;
+        ++n;
+    }
+    Py_DECREF(it);
+    return PyErr_Occurred() ? -1 : n;
 }
 
 // dims, perm, element size, in, out, stream, accumulate

@@ -70,6 +70,33 @@ def test_one_call_interface_arguments():
         t((6, 5), (1, 0), 8, "A", O)
 
 
+@pytest.mark.parametrize("change,kept", [(lambda x: x.clear(), 1), (lambda x: x.__delitem__(slice(2, None)), 2),
+                                         (lambda x: x.extend([1] * 1000), 1013)])
+def test_a_list_that_changes_while_it_is_converted(change, kept):
+    """Converting an entry may run Python code: the entries are those that iterating the list gives."""
+    class Entry:
+        def __init__(self, owner, value):
+            self.owner, self.value = owner, value
+
+        def __int__(self):
+            if self.owner is not None:
+                change(self.owner)
+                self.owner = None
+            return self.value
+
+    def fresh(values):
+        entries = []
+        entries += [Entry(entries if i == 0 else None, v) for i, v in enumerate(values)]
+        return entries
+    rank = 13
+    for dims, perm, n, given in ((fresh([2] * rank), tuple(range(rank)), kept, rank), ((2,) * rank, fresh(range(rank)), rank, kept)):
+        if given > n:                                     # more permutation entries than extents
+            with pytest.raises(IndexError):
+                B.tperm_transpose(dims, perm, 8, A, A)
+        else:                                             # too many extents, or too few entries
+            assert _status(B.tperm_transpose, dims, perm, 8, A, A) == (B.ERR_RANK if n > 16 else B.ERR_PERM)
+
+
 def test_calls_from_several_threads(plan):
     seen = []
 
