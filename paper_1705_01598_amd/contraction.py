@@ -90,8 +90,9 @@ class Contraction:
 
     def __init__(self, d_labels: str, l_labels: str, r_labels: str, extents: Dict[str, int], dtype, device="cuda"):
         import torch
+        from torch.autograd.forward_ad import unpack_dual
         from . import binding as B
-        self._torch, self._B = torch, B
+        self._torch, self._B, self._unpack_dual = torch, B, unpack_dual
         self.lay = layout(d_labels, l_labels, r_labels, extents)
         if dtype not in (torch.float32, torch.float64):
             raise ValueError("float32 or float64 only")
@@ -146,14 +147,16 @@ class Contraction:
 
     def _in_one_kernel(self, l, r, d) -> bool:
         """Whether this call may add into d while it reads its operands.  Operands that are used in place
-        have to lie apart from d and on this object's device; what the library product refuses (operands
-        that require a gradient) goes there to be refused."""
+        have to be plain memory on this object's device, apart from d; the others go the way of the library
+        product, which reads a tensor that is negated lazily as such and refuses those that carry gradients
+        (backward or forward mode)."""
         if self._product is None:
             return False
         for (perm, _), t in zip(self._operands, (l, r)):
             if perm is None:
                 a, b = t.data_ptr(), d.data_ptr()
-                if t.device != self._device or (t.requires_grad and self._torch.is_grad_enabled()) or \
+                if t.device != self._device or t.is_neg() or (t.requires_grad and self._torch.is_grad_enabled()) or \
+                        self._unpack_dual(t).tangent is not None or \
                         (a < b + d.numel() * self.elem and b < a + t.numel() * self.elem):
                     return False
         return True

@@ -66,6 +66,41 @@ def test_arithmetic_intensity_formula():
         assert max(lay.m * lay.n, lay.m * lay.k, lay.k * lay.n) < 1 << 26
 
 
+def test_operands_that_the_library_product_has_to_see():
+    """An operand that is used in place reaches the one kernel by its address alone: what torch keeps beside
+    the memory (lazy negation, gradients of either mode) and what overlaps the destination goes to torch.mm."""
+    torch = pytest.importorskip("torch")
+    from torch.autograd import forward_ad
+    con = C.Contraction("ab", "ak", "kb", dict(a=6, k=6, b=6), torch.float64, "cpu")
+    assert con._product is not None and all(perm is None for perm, _ in con._operands)
+    both = lambda x: {con._in_one_kernel(x, y, d), con._in_one_kernel(y, x, d)}  # noqa: E731
+    mem = torch.rand(120, dtype=torch.float64)
+    x, y, d = mem[:36], torch.rand(36, dtype=torch.float64), torch.zeros(36, dtype=torch.float64)
+    assert both(x) == {True}
+    assert both(torch._neg_view(x)) == {False}
+    grad = x.clone().requires_grad_()
+    assert both(grad) == {False}
+    with torch.no_grad():
+        assert both(grad) == {True}
+    with forward_ad.dual_level():
+        assert both(x) == {True} and both(forward_ad.make_dual(x, y)) == {False}
+    assert con._in_one_kernel(x, y, mem[35:71]) is False and con._in_one_kernel(x, y, mem[36:72]) is True
+    one = C.Contraction("ab", "ak", "kb", dict(a=1, k=1, b=1), torch.float64, "cpu")
+    z = torch.ones(1, dtype=torch.complex128).conj().imag              # negated lazily, one element: contiguous
+    assert z.is_contiguous() and not one._in_one_kernel(z, y[:1], d[:1])
+
+
+@pytest.mark.gpu
+def test_gpu_contraction_of_lazily_negated_operands():
+    torch = pytest.importorskip("torch")
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x, y = (torch.rand(36, dtype=torch.float64, device="cuda", generator=g) for _ in range(2))
+    d = torch.ones(36, dtype=torch.float64, device="cuda")
+    C.Contraction("ab", "ak", "kb", dict(a=6, k=6, b=6), torch.float64).run(torch._neg_view(x), y, d)
+    want = 1 - y.view(6, 6) @ x.view(6, 6)                             # row-major views of column-major data
+    assert torch.allclose(d.view(6, 6), want, rtol=1e-13, atol=1e-14)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype_name", ["float64", "float32"])
 @pytest.mark.parametrize("d,l,r,ext", SMALL + [
