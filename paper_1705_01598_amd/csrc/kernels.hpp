@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include "plan.hpp"
+#include "product.hpp"
 
 namespace tperm {
 
@@ -29,5 +30,9 @@ hipError_t launch_accumulate_copy(const void* in, void* out, size_t nbytes, int 
 // Enqueue a plain copy of nbytes; elem is the guaranteed pointer alignment (4 or 8).
 hipError_t launch_copy(const void* in, void* out, size_t nbytes, int elem, int num_cu,
                        hipStream_t stream);
+
+// Enqueue the product and, with a split summed index, the sum of its pieces.  workspace: p.workspace
+// bytes, if any.
+hipError_t launch_product(const Product& p, const void* left, const void* right, void* out, void* workspace, int num_cu, hipStream_t stream);
 
 }  // namespace tperm

@@ -1,6 +1,5 @@
-// Matrix product whose result is added straight into a permuted tensor (see product.hip): host side.
+// Matrix product whose result is added straight into a permuted tensor (kernels in product.hip): host side.
 #pragma once
-#include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -8,6 +7,12 @@
 #include "tperm_desc.h"
 
 namespace tperm {
+
+constexpr int kDepth = 16;    // summed indices per stage
+// Workgroups per compute unit.  Smaller tiles and a third workgroup overlap the wait for memory of one
+// with the arithmetic of another; 128 x 64 tiles of fp64 and two workgroups are 10 % faster on 4096^3 but
+// 10 to 30 % slower where the destination has few columns.
+constexpr int kResident = 3;
 
 // One digit of a matrix index: the extent of the tensor dimension behind it and its stride (bytes)
 // in the destination.
@@ -42,8 +47,5 @@ struct Product {
 // Host only: checks the arguments (as tperm_product_create) and fills the descriptor.
 tperm_status_t build_product(Product* p, int rank, const int64_t* dims, const int* perm, int left_dims, int64_t k,
                              size_t elem, int left_k_first, int right_k_first);
-
-// workspace: p.workspace bytes, if any.
-hipError_t launch_product(const Product& p, const void* left, const void* right, void* out, void* workspace, int num_cu, hipStream_t stream);
 
 }  // namespace tperm

@@ -1,7 +1,8 @@
-// Host-only fuzz driver for the planner, meant to be built with AddressSanitizer and
-// UndefinedBehaviorSanitizer (see test_planner_host.py).  It links plan.cpp alone (the
-// planner has no HIP dependency), creates plans for random problems and options, and checks
-// every plan's index map for being a bijection of 0..vol-1.
+// Host-only fuzz driver for the planners, meant to be built with AddressSanitizer and
+// UndefinedBehaviorSanitizer (see test_planner_host.py).  It links plan.cpp, model.cpp and
+// product_plan.cpp alone (none has a HIP dependency), creates plans for random problems and options,
+// and checks every plan's index map for being a bijection of 0..vol-1, and every product's offsets
+// against the permutation.
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
@@ -10,6 +11,92 @@
 #include <vector>
 
 #include "../paper_1705_01598_amd/csrc/plan.hpp"
+#include "../paper_1705_01598_amd/csrc/product.hpp"
+
+// Byte offset of index i of one side, as the kernels compute it.
+static uint64_t digits_offset(const tperm::ProductDim* dim, uint32_t n, uint32_t i) {
+    uint64_t at = 0;
+    for (uint32_t z = 0; z < n; ++z) {
+        const uint32_t quot = tperm::fdiv(i, dim[z].div);
+        at += (uint64_t)(i - quot * dim[z].ext) * dim[z].stride;
+        i = quot;
+    }
+    return at;
+}
+
+// Plans of products: 0 = all right, else the iteration that is wrong.
+static int fuzz_products(int iters, int* made, int* rejected) {
+    std::mt19937_64 rng(54321);
+    for (int it = 1; it <= iters; ++it) {
+        const bool big = it % 8 == 0;  // up to and beyond the limits; only the ends of each index are checked
+        const int rank = 1 + (int)(rng() % (it % 5 == 0 ? 16 : 6));
+        int64_t dims[TPERM_MAX_RANK];
+        int perm[TPERM_MAX_RANK];
+        int64_t vol = 1;
+        const int64_t most = big ? (int64_t)1 << 31 : 1 << 16;
+        for (int z = 0; z < rank; ++z) {
+            dims[z] = 1 + (int64_t)(rng() % (big ? 4000 : (rank > 6 ? 4 : 40)));
+            if (vol * dims[z] > most) dims[z] = 1;
+            vol *= dims[z];
+            perm[z] = z;
+        }
+        for (int z = rank - 1; z > 0; --z) std::swap(perm[z], perm[rng() % (z + 1)]);
+        const int left = (int)(rng() % (rank + 1));
+        const size_t elem = rng() % 2 ? 4 : 8;
+        const int64_t k = it % 97 == 0 ? INT64_MAX >> (rng() % 40) : (int64_t)1 << (rng() % (big ? 31 : 14)) | (int64_t)(rng() % 64);
+        int64_t ext[2] = {1, 1};
+        for (int z = 0; z < rank; ++z) ext[z < left ? 0 : 1] *= dims[z];
+        tperm::Product p;
+        const tperm_status_t st = tperm::build_product(&p, rank, dims, perm, left, k, elem, (int)(rng() % 2), (int)(rng() % 2));
+        const int64_t limit = (((int64_t)1 << 32) - 256) / (int64_t)elem;
+        const bool fits = vol < limit && k < limit && ext[0] * k < limit && ext[1] * k < limit;
+        if (st != (fits ? TPERM_OK : TPERM_ERR_TOO_LARGE)) return it;
+        if (!fits) {
+            ++*rejected;
+            continue;
+        }
+        const tperm::ProductDesc& d = p.d;
+        const int fast = p.left_fast ? 0 : 1;
+        if (d.n_fast != (uint64_t)ext[fast] || d.n_slow != (uint64_t)ext[1 - fast] || d.k != (uint64_t)k) return it;
+        // the pieces start at whole stages, none is empty, together they are the summed index
+        if (d.splits < 1 || (uint64_t)(d.splits - 1) * d.k_split >= d.k || (uint64_t)d.splits * d.k_split < d.k ||
+            (d.splits > 1 && d.k_split % tperm::kDepth != 0))
+            return it;
+        const uint64_t tiles = (uint64_t)d.tiles_fast * d.tiles_slow;
+        const uint32_t tile_f = p.shape == 1 ? 16 : (p.shape == 2 ? 256 : 128);
+        const uint32_t tile_s = (uint32_t)(p.tile_bytes / elem / tile_f);
+        if (d.tiles_fast != (d.n_fast + tile_f - 1) / tile_f || d.tiles_slow != (d.n_slow + tile_s - 1) / tile_s) return it;
+        if ((uint64_t)d.per_xcd * 8 < tiles * d.splits || tiles * d.splits + 8 > UINT32_MAX) return it;
+        if (p.workspace != (d.splits > 1 ? tiles * d.splits * p.tile_bytes : 0)) return it;
+        // offsets, against strides computed one dimension at a time
+        uint64_t stride[TPERM_MAX_RANK], s = elem;
+        for (int j = 0; j < rank; ++j) {
+            stride[perm[j]] = s;
+            s *= (uint64_t)dims[perm[j]];
+        }
+        for (int side = 0; side < 2; ++side) {
+            const int of = side == 0 ? fast : 1 - fast;
+            const uint32_t n = (uint32_t)ext[of], step = big ? std::max(1u, n / 1000) : 1u;
+            const tperm::ProductDim* dim = side == 0 ? d.fast : d.slow;
+            const uint32_t n_dims = side == 0 ? d.fast_dims : d.slow_dims;
+            for (uint32_t i = 0; i < n; i = i + step < n || i == n - 1 ? i + step : n - 1) {
+                uint64_t want = 0, rem = i;
+                for (int z = of == 0 ? 0 : left; z < (of == 0 ? left : rank); ++z) {
+                    want += rem % (uint64_t)dims[z] * stride[z];
+                    rem /= (uint64_t)dims[z];
+                }
+                if (digits_offset(dim, n_dims, i) != want || want >= d.out_bytes) return it;
+                // neighbours that one access moves lie side by side
+                if (side == 0 && p.vec > 1 && i % (uint32_t)p.vec != 0 && step == 1 &&
+                    digits_offset(dim, n_dims, i - 1) + elem != want)
+                    return it;
+            }
+            if (side == 0 && n % (uint32_t)p.vec != 0) return it;
+        }
+        ++*made;
+    }
+    return 0;
+}
 
 int main(int argc, char** argv) {
     const int iters = argc > 1 ? atoi(argv[1]) : 400;
@@ -158,7 +245,13 @@ int main(int argc, char** argv) {
         delete p;
         ++made;
     }
-    std::printf("ok: %d plans checked (%d with line-aligned windows, %d of them in pairs, %d LDS images cut), %d option sets rejected\n", made, windows, pair_windows,
-                images, rejected);
+    int products = 0, too_large = 0;
+    const int wrong = fuzz_products(2 * iters, &products, &too_large);
+    if (wrong != 0) {
+        std::printf("a product's plan is wrong, iteration %d\n", wrong);
+        return 1;
+    }
+    std::printf("ok: %d plans checked (%d with line-aligned windows, %d of them in pairs, %d LDS images cut), %d option sets rejected; %d products, %d too large\n", made,
+                windows, pair_windows, images, rejected, products, too_large);
     return 0;
 }

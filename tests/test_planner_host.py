@@ -473,7 +473,8 @@ def test_selector_rules_fitted_to_measurements():
 
 def test_planner_under_address_and_ub_sanitizers(tmp_path):
     """The planner (pure host C++) is built with ASan + UBSan and driven with random problems
-    and options; every plan's index map must be a bijection and no sanitizer may fire."""
+    and options; every plan's index map must be a bijection and no sanitizer may fire.  The same for
+    the plans of products: offsets, pieces and tiles as the kernels compute them, sizes up to the limits."""
     import shutil
     import subprocess
     if shutil.which("g++") is None:
@@ -481,7 +482,8 @@ def test_planner_under_address_and_ub_sanitizers(tmp_path):
     exe = str(tmp_path / "planner_fuzz")
     src = [os.path.join(ROOT, "tests", "planner_fuzz.cpp"),
            os.path.join(ROOT, "paper_1705_01598_amd", "csrc", "plan.cpp"),
-           os.path.join(ROOT, "paper_1705_01598_amd", "csrc", "model.cpp")]
+           os.path.join(ROOT, "paper_1705_01598_amd", "csrc", "model.cpp"),
+           os.path.join(ROOT, "paper_1705_01598_amd", "csrc", "product_plan.cpp")]
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
                     "-fno-sanitize-recover=undefined", "-I" + os.path.join(ROOT, "include"),
                     *src, "-o", exe], check=True)
