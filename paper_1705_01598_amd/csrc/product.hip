@@ -25,10 +25,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-// A larger destination is read and written with nontemporal accesses (156 MB of fp64, K = 70: 89 -> 86
-// us); a smaller one may still lie in the 256 MB memory-side cache, or be wanted there (78 MB of fp32,
-// visited again after two others: 40 us cached, 47 nontemporal).
-constexpr uint32_t kCachedOutBytes = 128u << 20;
 // Lane offset beyond every tensor that is accepted: the buffer range check drops the access.
 constexpr uint32_t kDropped = 0xFFFFFF00u;
 
@@ -350,25 +346,25 @@ product_sum_kernel(const ProductDesc d, const T* __restrict__ part, T* __restric
 }
 
 template <typename T, typename S, bool FAST_K, bool SLOW_K>
-static const void* product_ptr(const Product& p) {
+static const void* product_ptr(const Product& p, const void* out) {
 #define TPERM_PRODUCT(VEC, NT, SPLIT) reinterpret_cast<const void*>(&product_kernel<T, S, FAST_K, SLOW_K, VEC, NT, SPLIT>)
     if (p.d.splits > 1u) return TPERM_PRODUCT(1, 0, true);
     if constexpr (S::CB == 1) {
         return TPERM_PRODUCT(1, 0, false);
     } else {
-        const bool nt = p.d.out_bytes > kCachedOutBytes;
+        // runs of whole lines hold whole 16-byte accesses
+        if (nontemporal_out(p, reinterpret_cast<uintptr_t>(out))) return TPERM_PRODUCT(16 / (int)sizeof(T), 2, false);
         if constexpr (sizeof(T) == 4)
-            if (p.vec == 4) return nt ? TPERM_PRODUCT(4, 2, false) : TPERM_PRODUCT(4, 0, false);
-        if (p.vec >= 2) return nt ? TPERM_PRODUCT(2, 2, false) : TPERM_PRODUCT(2, 0, false);
-        return nt ? TPERM_PRODUCT(1, 2, false) : TPERM_PRODUCT(1, 0, false);
+            if (p.vec == 4) return TPERM_PRODUCT(4, 0, false);
+        return p.vec >= 2 ? TPERM_PRODUCT(2, 0, false) : TPERM_PRODUCT(1, 0, false);
     }
 #undef TPERM_PRODUCT
 }
 
 template <typename T, typename S>
 static hipError_t launch_shape(const Product& p, const void* left, const void* right, void* out, void* workspace, int num_cu, hipStream_t stream) {
-    const void* f = p.fast_k_first ? (p.slow_k_first ? product_ptr<T, S, true, true>(p) : product_ptr<T, S, true, false>(p))
-                                   : (p.slow_k_first ? product_ptr<T, S, false, true>(p) : product_ptr<T, S, false, false>(p));
+    const void* f = p.fast_k_first ? (p.slow_k_first ? product_ptr<T, S, true, true>(p, out) : product_ptr<T, S, true, false>(p, out))
+                                   : (p.slow_k_first ? product_ptr<T, S, false, true>(p, out) : product_ptr<T, S, false, false>(p, out));
     ProductDesc d = p.d;
     const void* fast = p.left_fast ? left : right;
     const void* slow = p.left_fast ? right : left;

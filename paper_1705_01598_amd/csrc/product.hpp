@@ -37,12 +37,23 @@ struct Product {
     int elem = 0;
     bool left_fast = true;                // the left operand is the fast one
     bool fast_k_first = false, slow_k_first = false;  // layout of the operands: summed index first?
-    int vec = 1;                          // destination elements that lie side by side: 1, 2, 4
+    uint32_t run = 1;                     // neighbouring fast indices that lie side by side in the destination
+    int vec = 1;                          // of those, how many one access moves: 1, 2, 4
     int shape = 0;                        // 0 wide tiles, 1 few fast indices, 2 few slow ones
     size_t tile_bytes = 0;
     size_t workspace = 0;                 // bytes for the partial products, if any
     bool pays = false;                    // expected to be faster than a library product and a transpose
 };
+
+// Nontemporal accesses to the destination: only for whole lines, and only where it does not fit the 256 MB
+// memory-side cache with some room (78 MB of fp32, visited again after two others: 40 us cached, 47
+// nontemporal).  Time against cached, destinations of 139 to 535 MB: 59 in runs of whole lines 0.93
+// (0.81 to 1.02), 21 in longer runs of other lengths 1.16 (0.98 to 1.55).  Short runs lose most, since each
+// piece of a line then goes to memory by itself: 253 MB in runs of 12 bytes 218 us cached, 1299 nontemporal.
+constexpr uint32_t kCachedOutBytes = 128u << 20;
+inline bool nontemporal_out(const Product& p, uintptr_t out) {
+    return p.d.out_bytes > kCachedOutBytes && ((uint64_t)p.run * (uint64_t)p.elem | out) % 128u == 0;
+}
 
 // Host only: checks the arguments (as tperm_product_create) and fills the descriptor.
 tperm_status_t build_product(Product* p, int rank, const int64_t* dims, const int* perm, int left_dims, int64_t k,

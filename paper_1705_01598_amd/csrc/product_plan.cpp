@@ -105,8 +105,8 @@ tperm_status_t build_product(Product* p, int rank, const int64_t* dims, const in
     d.fast_bytes = (uint32_t)(ext[fast] * k * (int64_t)elem);
     d.slow_bytes = (uint32_t)(ext[slow] * k * (int64_t)elem);
     d.out_bytes = (uint32_t)(ext[0] * ext[1] * (int64_t)elem);
-    const uint32_t run = d.fast_dims > 0 && d.fast[0].stride == (uint32_t)elem ? d.fast[0].ext : 1u;
-    p->vec = run % 4 == 0 && elem == 4 ? 4 : (run % 2 == 0 ? 2 : 1);
+    p->run = d.fast_dims > 0 && d.fast[0].stride == (uint32_t)elem ? d.fast[0].ext : 1u;
+    p->vec = p->run % 4 == 0 && elem == 4 ? 4 : (p->run % 2 == 0 ? 2 : 1);
     choose_shape(p);
     if (p->shape == 1) p->vec = 1;  // a lane holds one element of a row there
     const uint64_t tiles = (uint64_t)d.tiles_fast * d.tiles_slow;

@@ -93,6 +93,14 @@ static int fuzz_products(int iters, int* made, int* rejected) {
             }
             if (side == 0 && n % (uint32_t)p.vec != 0) return it;
         }
+        // nontemporal accesses to whole lines of a large destination only
+        bool lines = d.out_bytes > tperm::kCachedOutBytes;
+        for (uint32_t i = 0; lines && i < std::min(d.n_fast, 4096u); ++i)
+            lines = i % (128u / (uint32_t)elem) == 0 ? digits_offset(d.fast, d.fast_dims, i) % 128 == 0
+                                                     : digits_offset(d.fast, d.fast_dims, i - 1) + elem == digits_offset(d.fast, d.fast_dims, i);
+        for (uint32_t i = 0; lines && i < std::min(d.n_slow, 4096u); ++i) lines = digits_offset(d.slow, d.slow_dims, i) % 128 == 0;
+        if (tperm::nontemporal_out(p, 4096) && !lines) return it;
+        if (tperm::nontemporal_out(p, 4096 + 64)) return it;
         ++*made;
     }
     return 0;
@@ -244,6 +252,20 @@ int main(int argc, char** argv) {
         if (p->align_out && p->vec2) ++pair_windows;
         delete p;
         ++made;
+    }
+    // 253 and 262 MB in runs of 12 and 16 bytes, 144 MB in runs of two lines and in runs a little longer
+    {
+        struct { int64_t dims[3]; size_t elem; bool lines; } const large[] = {
+            {{3, 6117, 3450}, 4, false}, {{2, 4372, 3744}, 8, false}, {{64, 640, 880}, 4, true}, {{66, 640, 880}, 4, false}, {{32, 640, 880}, 8, true}};
+        const int perm[3] = {0, 2, 1};
+        for (const auto& c : large) {
+            tperm::Product p;
+            if (tperm::build_product(&p, 3, c.dims, perm, 2, 9, c.elem, 0, 0) != TPERM_OK || p.d.out_bytes <= tperm::kCachedOutBytes ||
+                tperm::nontemporal_out(p, 1 << 20) != c.lines || tperm::nontemporal_out(p, (1 << 20) + 64)) {
+                std::printf("nontemporal accesses to a destination in runs of %d elements\n", (int)c.dims[0]);
+                return 1;
+            }
+        }
     }
     int products = 0, too_large = 0;
     const int wrong = fuzz_products(2 * iters, &products, &too_large);

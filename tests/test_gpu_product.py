@@ -122,6 +122,23 @@ def test_large_destination(dtype_name):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+@pytest.mark.parametrize("lines,extra,offset", [(1, 0, 0), (1, 0, 3), (3, 0, 0), (1, 1, 0), (0, 3, 0), (0, 2, 0)])
+def test_large_destination_in_runs(lines, extra, offset, dtype_name):
+    """More than 128 MiB in runs of whole lines (nontemporal accesses from an aligned pointer, else cached) and
+    of other lengths (cached), wide tiles and thin ones, both layouts of the fast operand."""
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    elem = torch.finfo(dtype).bits // 8
+    run = lines * 128 // elem + extra
+    for slow, k, lk in ((45, 5, 0), (13, 3, 1)):
+        mid = (136 << 20) // elem // run // slow // 3 + 1
+        info, got, ref, size = _run(torch, (run, 3, mid), (slow,), (0, 2, 3, 1), k, dtype, lk, 0, offset)
+        assert got.numel() * elem > 128 << 20 and info.pieces == 1
+        _check(torch, got, ref, size, k, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
 def test_special_values(dtype_name):
     """Subnormal products are not flushed; an infinity or a NaN reaches its own row or column only."""
     torch = pytest.importorskip("torch")
