@@ -294,7 +294,8 @@ tperm_status_t tperm_cache_clear(void);
  * is formed in the working precision (IEEE binary32 / binary64, elem_size 4 / 8), then added once.
  * left_k_first: 0 = left(i, k) lies at i + extent(i) * k, else at k + extent(k) * i; right_k_first:
  * 0 = right(k, j) lies at j + extent(j) * k, else at k + extent(k) * j.  Either index may have no
- * dimensions (left_dims 0 or rank: extent 1).
+ * dimensions (left_dims 0 or rank: extent 1).  Any order of the dims is right; the destination is
+ * reached in runs where out's stride-1 dimension comes first among its operand's.
  *
  * create: host only, no device memory.  Statuses of tperm_plan_create, RANK (left_dims outside
  * 0..rank), DIMS (k < 1), TOO_LARGE (an operand or out of 2^32 - 256 bytes or more).

@@ -22,7 +22,8 @@ struct ProductDim {
 };
 
 // Descriptor of the kernel, passed by value.  "Fast" is the operand that holds the destination's
-// stride-1 dimension: its index runs along the lanes of a wavefront.
+// stride-1 dimension: its index runs along the lanes of a wavefront.  Neighbouring lanes are neighbours
+// in the destination where that dimension comes first in its operand's index, else they are not.
 struct ProductDesc {
     uint32_t n_fast, n_slow, k;                  // extents of the product
     uint32_t splits, k_split;                    // the summed index in pieces of k_split

@@ -88,8 +88,13 @@ tperm_status_t build_product(Product* p, int rank, const int64_t* dims, const in
             digits[side][n++] = ProductDim{make_fastdiv((uint32_t)dims[z]), (uint32_t)dims[z], (uint32_t)stride[z]};
         }
     }
-    // fast side: the one that holds the destination's stride-1 dimension
-    p->left_fast = !(n_digits[1] > 0 && digits[1][0].stride == (uint32_t)elem);
+    // fast side: the one that holds the destination's stride-1 dimension, at whatever place
+    p->left_fast = true;
+    for (int j = 0; j < rank; ++j)
+        if (dims[perm[j]] > 1) {
+            p->left_fast = perm[j] < left_dims;
+            break;
+        }
     const int fast = p->left_fast ? 0 : 1, slow = 1 - fast;
     ProductDesc& d = p->d;
     p->elem = (int)elem;

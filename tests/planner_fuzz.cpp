@@ -68,6 +68,10 @@ static int fuzz_products(int iters, int* made, int* rejected) {
         if (d.tiles_fast != (d.n_fast + tile_f - 1) / tile_f || d.tiles_slow != (d.n_slow + tile_s - 1) / tile_s) return it;
         if ((uint64_t)d.per_xcd * 8 < tiles * d.splits || tiles * d.splits + 8 > UINT32_MAX) return it;
         if (p.workspace != (d.splits > 1 ? tiles * d.splits * p.tile_bytes : 0)) return it;
+        int owner = 0;  // of the destination's stride-1 dimension
+        for (int j = rank - 1; j >= 0; --j)
+            if (dims[perm[j]] > 1) owner = perm[j] < left ? 0 : 1;
+        if (fast != owner) return it;
         // offsets, against strides computed one dimension at a time
         uint64_t stride[TPERM_MAX_RANK], s = elem;
         for (int j = 0; j < rank; ++j) {

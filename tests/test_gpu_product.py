@@ -33,6 +33,9 @@ CASES = [
     ((300,), (70,), (0, 1), 1000),
     ((1,), (100,), (1, 0), 20),
     ((150, 40), (30, 25), (2, 0, 3, 1), 24),   # many tiles to a workgroup
+    ((130,), (7, 6), (2, 1, 0), 20),           # the stride-1 dimension is not the first one of its operand
+    ((9, 20), (33,), (1, 0, 2), 35),
+    ((5,), (3, 400), (2, 0, 1), 18),
 ]
 GUARD = 64
 
@@ -157,6 +160,16 @@ def test_special_values(dtype_name):
         return l, r, d
     _, got, ref, _ = _run(torch, (130,), (40,), (0, 1), 9, dtype, 0, 0, values=odd)
     assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+
+
+@pytest.mark.parametrize("dims,perm,left,left_fast", [
+    ((1024, 64, 64), (2, 1, 0), 1, 0), ((64, 64, 1024), (1, 0, 2), 2, 1), ((5, 3, 400), (2, 0, 1), 1, 0),   # not its first dimension
+    ((5, 1, 7), (1, 0, 2), 1, 1), ((1, 5, 7), (0, 2, 1), 1, 0), ((5, 7), (1, 0), 1, 0), ((5, 7), (0, 1), 1, 1),  # extents of 1 do not count
+    ((4, 5), (1, 0), 2, 1), ((4, 5), (1, 0), 0, 0), ((1, 1), (1, 0), 1, 1)])
+def test_the_fast_operand_owns_the_stride_1_dimension(dims, perm, left, left_fast):
+    for elem in (4, 8):
+        info = B.tperm_product_describe(B.tperm_product_create(dims, perm, left, 30, elem))
+        assert info.left_fast == left_fast
 
 
 def test_arguments():
