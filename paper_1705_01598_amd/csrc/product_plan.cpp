@@ -35,6 +35,48 @@ static double library_us(const ProductDesc& d, int elem) {
     return gemm + 2.0 * d.out_bytes / 4.5e6;
 }
 
+// A split product of wide fp64 tiles, closer than product_us: a stage costs what the fullest compute unit
+// takes for it, and the pieces are summed from memory.  95 seeded products: standard deviation 8 %.
+static double split_f64_us(double units, uint32_t depth) {
+    const double share = std::min((double)kResident, std::ceil(units / kComputeUnits));
+    const double rounds = std::ceil(units / (kComputeUnits * kResident));
+    return 3.3 + rounds * ((depth + kDepth - 1) / kDepth) * std::max(1.03, 0.69 * share) + 2.5 + 0.0147 * units;
+}
+
+// Whether the dimensions of one index are listed in the destination's order.
+static bool in_order(const ProductDim* dim, uint32_t n) {
+    for (uint32_t z = 1; z < n; ++z)
+        if (dim[z].stride < dim[z - 1].stride) return false;
+    return true;
+}
+
+// Whether the one kernel is expected to be faster than the library's product and an accumulating transpose
+// (us: its estimate).  Times are of the library's way / of the one kernel.
+//  - Not where the destination's stride-1 dimension is not the first of its operand: each lane then
+//    reaches a line of its own (121 seeded products: 24 slower, by up to 6 times).
+//  - Not in short runs of a larger destination where an operand's dimensions are listed in another order than
+//    the destination's: the pieces of a line come from different tiles (30 seeded products: 8 slower, by up to 3.8
+//    times; in order, 55 such: 1.14 at the least).
+//  - Not where fp64 products of few tiles fill the library's tiles: of seven slower contractions in 1270, six were
+//    fp64 in two to four pieces with both extents above 250 (0.82 to 0.90); they leave by the estimate above.
+//  - Else up to 256 summed indices, and beyond where the estimates say so.
+// 1450 seeded contractions with new seeds (extents of the workload families, any extents, plain matrices, first
+// extents of 2 to 8): 841 with K <= 128 2.19, all taken, 0.99 at the least; 106 of 107 up to 256 1.68, three below 0.97,
+// 0.89 at the least; beyond, 287 taken 2.46, 0.99 at the least, 215 not taken, of which 77 would be slower.
+constexpr uint32_t kAnyOrderRunBytes = 64, kAnyOrderOutBytes = 8u << 20, kLibraryTiles = 150;
+static bool one_kernel_pays(const Product& p, double us) {
+    const ProductDesc& d = p.d;
+    if (d.fast_dims > 0 && d.fast[0].stride != (uint32_t)p.elem) return false;
+    if (p.run * (uint32_t)p.elem < kAnyOrderRunBytes && d.out_bytes > kAnyOrderOutBytes &&
+        !(in_order(d.fast, d.fast_dims) && in_order(d.slow, d.slow_dims)))
+        return false;
+    const double library = library_us(d, p.elem);
+    if (p.elem == 8 && d.splits > 1 && std::min(d.n_fast, d.n_slow) >= kLibraryTiles &&
+        split_f64_us((double)d.tiles_fast * d.tiles_slow * d.splits, d.k_split) > 0.9 * library)
+        return false;
+    return d.k <= 256 || us <= library;
+}
+
 // Tile shape: wide tiles, or one of the thin ones where an index has so few values that wide tiles are
 // mostly padding.  Thin tiles read more per result, so their padded area counts double and more.  Over
 // 700 seeded contractions (time of the pick / best of the three, geometric mean): wide tiles always
@@ -129,11 +171,7 @@ tperm_status_t build_product(Product* p, int rank, const int64_t* dims, const in
     }
     p->workspace = d.splits > 1u ? (size_t)tiles * d.splits * p->tile_bytes : 0;
     d.per_xcd = (uint32_t)((tiles * d.splits + 7u) / 8u);
-    // Up to 256 summed indices the one kernel wins (334 of 700 seeded contractions: 1.9 to 2.3 times the
-    // speed up to 128, 1.3 to 1.5 up to 256, the slowest 0.87); beyond that it is taken where the
-    // estimates say so: one of the other 366 is slower then, by 13 %, the rest 1.5 times as fast together
-    // (always taken, 55 would be slower, by up to 28 %).
-    p->pays = d.k <= 256 || best <= library_us(d, p->elem);
+    p->pays = one_kernel_pays(*p, best);
     return TPERM_OK;
 }
 

@@ -207,6 +207,28 @@ def test_which_contractions_run_in_one_kernel():
     assert pays(80, 64, 115620, 8)                             # the library's product runs along the summed index
 
 
+@pytest.mark.parametrize("elem", [4, 8])
+def test_orders_in_which_one_kernel_does_not_pay(elem):
+    pays = lambda dims, perm, left, k=30: B.tperm_product_describe(B.tperm_product_create(dims, perm, left, k, elem)).pays  # noqa: E731
+    # the stride-1 dimension is not the first of its operand: lanes 512 and more bytes apart
+    assert not pays((1024, 64, 64), (2, 1, 0), 1) and not pays((64, 64, 1024), (1, 0, 2), 2)
+    assert pays((1024, 64, 64), (1, 2, 0), 1) and pays((64, 64, 1024), (0, 1, 2), 2)
+    # short runs: an operand whose dimensions are listed in another order than the destination's
+    short, long_ = 32 // elem, 64 // elem
+    n = (8 << 20) // elem // short // 30 + 1
+    assert pays((short, n, 6, 5), (0, 2, 3, 1), 2) and pays((short, n, 6, 5), (0, 2, 1, 3), 2)
+    assert not pays((short, n, 6, 5), (0, 3, 2, 1), 2)
+    assert not pays((short, 6, n, 5), (0, 3, 2, 1), 3)
+    assert pays((short, n - 1, 6, 5), (0, 3, 2, 1), 2)         # up to 8 MiB
+    assert pays((long_, n, 6, 5), (0, 3, 2, 1), 2)
+
+
+def test_small_fp64_products_that_fill_the_librarys_tiles():
+    pays = lambda m, n, k, elem: B.tperm_product_describe(B.tperm_product_create((m, n), (0, 1), 1, k, elem)).pays  # noqa: E731
+    assert not pays(297, 1579, 186, 8) and not pays(617, 703, 1046, 8)    # 18.0 us against 21.3, 30.2 against 36.4
+    assert pays(297, 1579, 186, 4) and pays(149, 1579, 186, 8)
+
+
 @pytest.mark.gpu
 def test_contraction_whose_operand_is_its_destination():
     """d += l r with d in place of l: the product is finished before d changes."""
