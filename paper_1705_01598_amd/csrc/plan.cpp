@@ -1044,7 +1044,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
 int tile_launch_policy(const Plan& plan, bool acc, bool sector_aligned_out, bool read_again) {
     int pol = plan.cache_policy;
     const int64_t bytes = plan.c.volume * plan.elem;
-    if (read_again && bytes < kReadAgainBytes && (pol != 3 || bytes >= kReadAgainBytes3)) return 1;
+    if (read_again && !plan.policy_given && bytes < kReadAgainBytes && (pol != 3 || bytes >= kReadAgainBytes3)) return 1;
     if (acc) return pol == 2 && sector_aligned_out && !plan.align_out ? 2 : 1;
     if (!sector_aligned_out && !plan.align_out) pol = (pol == 2 || pol == 4) ? 4 : 1;
     if (pol == 4 && (plan.loads_first || plan.threads != 256)) pol = 1;
@@ -1204,7 +1204,10 @@ tperm_status_t create_plan(Plan** out, int rank, const int64_t* dims, const int*
     st = build_tile_plan(p, chosen, bo);
     if (st != TPERM_OK) return fail(st);
     if (o.blocks_per_cu > 0) p->blocks_per_cu = o.blocks_per_cu;
-    if (o.cache_policy >= 1 && o.cache_policy <= 4) p->cache_policy = o.cache_policy;
+    if (o.cache_policy >= 1 && o.cache_policy <= 4) {
+        p->cache_policy = o.cache_policy;
+        p->policy_given = true;
+    }
     if (o.loads_first == 1 || o.loads_first == 2) p->loads_first = o.loads_first == 2;
     *out = p;
     return TPERM_OK;

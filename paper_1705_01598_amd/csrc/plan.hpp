@@ -105,6 +105,7 @@ struct Plan {
     bool vec2 = false;         // 4-byte elements move in pairs; needs 8-byte aligned pointers
     bool lean = false;         // small tensor: the variants of the kernel without masks (6 to 16 slots per thread, 24 for 4-byte elements)
     bool loads_first = false;  // next tile's loads are issued before this tile's stores
+    bool policy_given = false;  // the caller chose cache_policy
     int cache_policy = 1;    // 1 = cached, 2 = nontemporal loads and stores, 3 = nontemporal stores, 4 = nontemporal loads
     bool big = false;        // tensor of 4 GiB or more: tiles describe their buffers from their own origin
     // Slots beyond the tile write the last element of the LDS image (forms without masks).  With
@@ -138,7 +139,8 @@ inline bool runs_without_masks(const Plan& p, bool accumulate) {
 // turned into 4 by an odd base pointer -9 to +7 % (100 shapes, 0.72 to 1.14).
 // read_again: both tensors are read right behind the transpose (the self-checking execute).  As long as
 // they fit the memory-side cache together, or nearly, they had better stay there: cached up to
-// kReadAgainBytes, with policy 3 from kReadAgainBytes3 on (its loads are cached anyway).  Time of the
+// kReadAgainBytes, with policy 3 from kReadAgainBytes3 on (its loads are cached anyway), unless the caller
+// chose the policy.  Time of the
 // whole call under the policy / cached, geometric means over 134 seeded shapes; tensors of up to 32, 64,
 // 128, 160, 200, 260, 400 MB: policy 2 1.06 1.03 1.05 1.05 1.00 0.95 0.93; 4 1.04 1.04 1.07 1.05 - 1.01 0.98; 3 1.00 0.99 1.03 1.03 0.99
 // 0.95 0.93.

@@ -222,6 +222,20 @@ int main(int argc, char** argv) {
                 return 1;
             }
         }
+        // what is read again stays in the caches, unless the caller chose the policy (these tensors are small)
+        for (int pol = 0; pol <= 4; ++pol) {
+            tperm_plan_opts_t with = o;
+            with.cache_policy = pol;
+            tperm::Plan* q = nullptr;
+            if (it % 8 != 0 || tperm::create_plan(&q, rank, dims, perm, elem, &with) != TPERM_OK) break;
+            const int as_planned = tperm::tile_launch_policy(*q, false, true), again = tperm::tile_launch_policy(*q, false, true, true);
+            const bool cached = pol == 0 && q->cache_policy != 3;
+            delete q;
+            if (again != (cached ? 1 : as_planned)) {
+                std::printf("the self-checking execute takes the wrong cache policy, iteration %d\n", it);
+                return 1;
+            }
+        }
         if (p->use_lds && !p->align_out && p->tile.n_tile_dims > 0) {
             // The index map must refuse an image that ends one element too early: shrink it to what
             // the tile's first (full) instance needs and by one more.
