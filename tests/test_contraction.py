@@ -1,12 +1,13 @@
-"""Tensor contraction through transposes + GEMM (application layer on top of the library).
+"""Tensor contraction through transposes + product (application layer on top of the library).
 
 The checker is the oracle's direct loop nest (oracle.contract: one output element at a time,
 products summed in double precision in a fixed order; pinned in test_oracle_pins.py on a
 hand-computed case, the matrix product, nested Python loops and the transpose oracle).
 CPU part: the label bookkeeping is checked by emulating the four steps with the oracle's
-transposes and numpy's matrix product.  GPU part: the real path (tperm transposes, vendor GEMM
-through torch.mm, accumulating transpose) against the oracle; a GEMM sums in another order
-than the loop nest, so this comparison has a tolerance, unlike every transpose test: with K
+transposes and numpy's matrix product.  GPU part: both real paths (tperm transposes, then the
+product that is added straight into the destination, or the vendor GEMM through torch.mm and an
+accumulating transpose) against the oracle; a product sums in another order than the loop
+nest, so this comparison has a tolerance, unlike every transpose test: with K
 products per output element, each rounded in the working precision (unit roundoff eps), the
 error of either summation order is at most about K * eps * sum_k |l||r| (the standard bound
 for recursive summation), so |difference| <= 2 * 8 * K * eps * sum_k |l||r| + 8 * eps * |ref|
@@ -101,23 +102,20 @@ def test_gpu_contraction_of_lazily_negated_operands():
     assert torch.allclose(d.view(6, 6), want, rtol=1e-13, atol=1e-14)
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
-@pytest.mark.parametrize("d,l,r,ext", SMALL + [
+MORE = [
     ("ebfa", "cadb", "fdce", dict(a=30, b=14, c=12, d=9, e=20, f=16)),
     ("dabfec", "aghcbi", "efdghi", dict(a=4, b=6, c=5, d=3, e=4, f=3, g=7, h=2, i=5)),
-])
-def test_gpu_contraction_matches_the_oracle(d, l, r, ext, dtype_name):
+]
+
+
+def _against_the_oracle(con, dtype):
     torch = pytest.importorskip("torch")
-    dtype = getattr(torch, dtype_name)
-    lay = C.layout(d, l, r, ext)
+    lay = con.lay
     rng = np.random.default_rng(5)
     npdt = np.float64 if dtype == torch.float64 else np.float32
-    lv = (rng.random(math.prod(lay.dims(l))) * 2 - 1).astype(npdt)
-    rv = (rng.random(math.prod(lay.dims(r))) * 2 - 1).astype(npdt)
-    dv = (rng.random(math.prod(lay.dims(d))) * 2 - 1).astype(npdt)
+    values = lambda labels: (rng.random(math.prod(lay.dims(labels))) * 2 - 1).astype(npdt)  # noqa: E731
+    lv, rv, dv = values(lay.l_labels), values(lay.r_labels), values(lay.d_labels)
     d_dev = torch.from_numpy(dv.copy()).cuda()
-    con = C.Contraction(d, l, r, ext, dtype)
     con.run(torch.from_numpy(lv).cuda(), torch.from_numpy(rv).cuda(), d_dev)
     con.run(torch.from_numpy(lv).cuda(), torch.from_numpy(rv).cuda(), d_dev)      # accumulates twice
     torch.cuda.synchronize()
@@ -127,3 +125,58 @@ def test_gpu_contraction_matches_the_oracle(d, l, r, ext, dtype_name):
     eps = np.finfo(npdt).eps
     err = np.abs(d_dev.cpu().numpy().astype(np.float64) - ref)
     assert np.all(err <= 2 * 8 * lay.k * eps * bound + 8 * eps * np.abs(ref) + 1e-300), float(err.max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+@pytest.mark.parametrize("d,l,r,ext", SMALL + MORE)
+def test_gpu_contraction_matches_the_oracle(d, l, r, ext, dtype_name):
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    con = C.Contraction(d, l, r, ext, dtype)
+    assert con._product is not None
+    _against_the_oracle(con, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+@pytest.mark.parametrize("d,l,r,ext", SMALL + MORE)
+def test_gpu_library_path_matches_the_oracle(d, l, r, ext, dtype_name):
+    """The library product and the accumulating transpose, where the plan would take the one kernel."""
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    con = C.Contraction(d, l, r, ext, dtype)
+    con._product = None                       # the library path's buffers are made by the first call
+    _against_the_oracle(con, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name,d,l,r,ext", [
+    ("float64", "bcad", "akb", "dkc", dict(a=33, b=9, c=20, d=79, k=186)),        # 297 x 1580, in pieces: the library is faster
+    ("float32", "cab", "bkla", "klc", dict(a=21, b=41, c=1344, k=32, l=16)),       # 861 x 1344, K = 512
+])
+def test_gpu_contraction_that_takes_the_library_path(d, l, r, ext, dtype_name):
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    con = C.Contraction(d, l, r, ext, dtype)
+    assert con._product is None
+    _against_the_oracle(con, dtype)
+
+
+@pytest.mark.gpu
+def test_gpu_benchmark_names_the_path_of_every_row(monkeypatch, capsys):
+    """Figures of the one kernel (which has no time of the product alone, and two transposes) and of the library
+    path stand under names of their own; --library measures the latter everywhere."""
+    import json
+    pytest.importorskip("torch")
+    cases = [dict(name=str(i), seed=i, d="bcad", l="akb", r="dkc", extents=dict(a=33, b=9, c=20, d=79, k=k)) for i, k in enumerate((186, 30))]
+    monkeypatch.setattr(wl, "contraction_cases", lambda: cases)
+    for argv, paths in ((["--reps", "1"], ["library", "one kernel"]), (["--reps", "1", "--library"], ["library", "library"])):
+        C._bench(argv)
+        lines = [json.loads(x) for x in capsys.readouterr().out.splitlines()]
+        rows, summaries = lines[:2], lines[2:]
+        assert [x["path"] for x in rows] == paths and [x["path"] for x in summaries] == sorted(set(paths))
+        for x in rows:
+            assert ("gemm_gflops" in x, "transpose_share" in x, "transpose_d_ms" in x) == (x["path"] == "library",) * 3
+            assert ("product_gflops" in x, "operand_transpose_share" in x, "product_ms" in x) == (x["path"] == "one kernel",) * 3
+        assert sum(x["cases"] for x in summaries) == 2

@@ -162,6 +162,46 @@ def test_special_values(dtype_name):
     assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+@pytest.mark.parametrize("left,right,perm,k", [c for c in CASES if c[3] > 16])
+def test_whole_numbers_are_exact(left, right, perm, k, dtype_name):
+    """Whole numbers of -2 to 2: every sum is below 2^24 and exact in either type, in any order, so that a summed
+    index that is left out or taken twice (at the edge of a stage or of a piece) shows."""
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+
+    def whole(rand):
+        n, m = math.prod(right), math.prod(left)
+        return tuple((rand(*s) * 2.49).round() for s in ((m, k), (n, k), (m * n,)))
+    for lk, rk, offset in ((0, 0, 1), (0, 1, 0), (1, 0, 3), (1, 1, 0)):
+        _, got, ref, size = _run(torch, left, right, perm, k, dtype, lk, rk, offset, values=whole)
+        assert float(size.max()) < 1 << 24 and torch.equal(got.double(), ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype_name", ["float64", "float32"])
+@pytest.mark.parametrize("left,right,perm,k", [((131,), (37,), (0, 1), 41), ((37,), (131,), (1, 0), 50), ((13,), (301,), (0, 1), 43),
+                                               ((301,), (13,), (0, 1), 35), ((40,), (24,), (1, 0), 4096), ((300,), (70,), (0, 1), 1003)])
+def test_special_values_behind_a_vector(left, right, perm, k, dtype_name):
+    """Infinities and NaN where loads of several elements run past the end of a row (they fetch the start of the
+    next one), in the last stage and at the edges of pieces, in either layout: the rows and columns that hold
+    them, and no other, are infinite or NaN."""
+    torch = pytest.importorskip("torch")
+    dtype = getattr(torch, dtype_name)
+    inf, nan = float("inf"), float("nan")
+
+    def odd(rand):
+        l, r, d = rand(*left, k), rand(*right, k), rand(left[0] * right[0])
+        l[0, 1::7], l[1, 5], l[left[0] - 1, k - 1] = nan, inf, inf
+        r[0, 2::5], r[2, k - 1], r[right[0] - 1, 0] = nan, -inf, inf
+        return l, r, d
+    for lk, rk in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        info, got, ref, _ = _run(torch, left, right, perm, k, dtype, lk, rk, values=odd)
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf()) and (info.pieces > 1) == (k > 1000)
+        assert torch.equal(got[got.isinf()].sign(), ref[ref.isinf()].sign().to(dtype)) and bool(got.isfinite().any())
+
+
 @pytest.mark.parametrize("dims,perm,left,left_fast", [
     ((1024, 64, 64), (2, 1, 0), 1, 0), ((64, 64, 1024), (1, 0, 2), 2, 1), ((5, 3, 400), (2, 0, 1), 1, 0),   # not its first dimension
     ((5, 1, 7), (1, 0, 2), 1, 1), ((1, 5, 7), (0, 2, 1), 1, 0), ((5, 7), (1, 0), 1, 0), ((5, 7), (0, 1), 1, 1),  # extents of 1 do not count
@@ -230,14 +270,26 @@ def test_small_fp64_products_that_fill_the_librarys_tiles():
 
 
 @pytest.mark.gpu
-def test_contraction_whose_operand_is_its_destination():
-    """d += l r with d in place of l: the product is finished before d changes."""
+@pytest.mark.parametrize("library", [False, True])
+@pytest.mark.parametrize("d,l,r,ext", [("ab", "ak", "kb", dict(a=24, k=24, b=24)),      # operands in place
+                                       ("acb", "akc", "kb", dict(a=6, c=5, b=24, k=24)),  # one transposed first
+                                       ("bca", "kac", "kb", dict(a=6, c=5, b=24, k=24))])
+def test_contraction_whose_operand_is_its_destination(d, l, r, ext, library):
+    """d += l r with d in place of l: the operand is read, or the product finished, before d changes."""
     torch = pytest.importorskip("torch")
     from paper_1705_01598_amd.contraction import Contraction
-    con = Contraction("ab", "ak", "kb", dict(a=24, k=24, b=24), torch.float64)
+    con = Contraction(d, l, r, ext, torch.float64)
+    if library:
+        con._product = None
     g = torch.Generator(device="cuda").manual_seed(4)
-    x, y = (torch.rand(24 * 24, dtype=torch.float64, device="cuda", generator=g) for _ in range(2))
-    want = x.view(24, 24) + y.view(24, 24) @ x.view(24, 24)    # row-major views of column-major data
+    size = lambda s: math.prod(ext[c] for c in s)  # noqa: E731
+    x, y = (torch.rand(size(s), dtype=torch.float64, device="cuda", generator=g) for s in (l, r))
+    # row-major views of column-major data: labels in reverse
+    view = lambda t, s: t.cpu().reshape([ext[c] for c in reversed(s)])  # noqa: E731
+    prod = torch.einsum(f"{l[::-1]},{r[::-1]}->{d[::-1]}", view(x, l), view(y, r))
+    want = view(x, d) + prod
     t = {}
     con.run(x, y, x, t)
-    assert torch.allclose(x.view(24, 24), want, rtol=1e-13) and set(t) == {"transpose_l_ms", "transpose_r_ms", "gemm_ms", "transpose_d_ms", "total_ms"}
+    err = (view(x, d) - want).abs()
+    assert bool((err <= 2 * 24 * 2.3e-16 * want).all()), float((err / want).max())     # all terms are positive
+    assert set(t) == {"transpose_l_ms", "transpose_r_ms", "gemm_ms", "transpose_d_ms", "total_ms"}
