@@ -211,7 +211,9 @@ def contract(d_labels: str, l_labels: str, r_labels: str, extents: Dict[str, int
 
 def _bench(argv: Sequence[str] = None) -> None:
     """Times the seeded contraction sample: GFLOP/s and the share of time spent transposing,
-    against arithmetic intensity.  One JSON line per case, then a summary line."""
+    against arithmetic intensity.  One JSON line per case with the path it took, then a summary line for each
+    path: "library" (transposes, library product, accumulating transpose; --library takes it everywhere), or
+    "one kernel", whose product_ms covers the destination's update too and whose transposes are the operands' only."""
     import argparse
     import json
     import numpy as np
@@ -220,11 +222,14 @@ def _bench(argv: Sequence[str] = None) -> None:
     ap = argparse.ArgumentParser(description=_bench.__doc__)
     ap.add_argument("--dtype", choices=["f32", "f64"], default="f64")
     ap.add_argument("--reps", type=int, default=5)
+    ap.add_argument("--library", action="store_true", help="take the library product for every contraction")
     args = ap.parse_args(argv)
     dtype = torch.float64 if args.dtype == "f64" else torch.float32
-    rows = []
+    paths = {"library": [], "one kernel": []}
     for case in wl.contraction_cases():
         c = Contraction(case["d"], case["l"], case["r"], case["extents"], dtype)
+        if args.library:
+            c._product = None
         lay = c.lay
         g = torch.Generator(device="cuda").manual_seed(case["seed"])
         l = torch.rand(lay.m * lay.k, dtype=dtype, device="cuda", generator=g) * 2 - 1
@@ -237,23 +242,37 @@ def _bench(argv: Sequence[str] = None) -> None:
             c.run(l, r, d, t)
             if best is None or t["total_ms"] < best["total_ms"]:
                 best = t
-        tr = best["transpose_l_ms"] + best["transpose_r_ms"] + best["transpose_d_ms"]
-        row = {"case": case["name"], "d": case["d"], "l": case["l"], "r": case["r"], "m": lay.m, "n": lay.n, "k": lay.k,
+        one = c._in_one_kernel(l, r, d)
+        ops = best["transpose_l_ms"] + best["transpose_r_ms"]
+        row = {"case": case["name"], "path": "one kernel" if one else "library", "d": case["d"], "l": case["l"], "r": case["r"],
+               "m": lay.m, "n": lay.n, "k": lay.k,
                "arithmetic_intensity": round(lay.arithmetic_intensity, 1),
-               "gflops": round(lay.flops / best["total_ms"] / 1e6, 1),
-               "gemm_gflops": round(lay.flops / best["gemm_ms"] / 1e6, 1),
-               "transpose_share": round(tr / best["total_ms"], 4), **{k: round(v, 4) for k, v in best.items()}}
-        rows.append(row)
+               "gflops": round(lay.flops / best["total_ms"] / 1e6, 1)}
+        if one:
+            row.update(product_gflops=round(lay.flops / best["gemm_ms"] / 1e6, 1),
+                       operand_transpose_share=round(ops / best["total_ms"], 4),
+                       transpose_l_ms=round(best["transpose_l_ms"], 4), transpose_r_ms=round(best["transpose_r_ms"], 4),
+                       product_ms=round(best["gemm_ms"], 4), total_ms=round(best["total_ms"], 4))
+        else:
+            row.update(gemm_gflops=round(lay.flops / best["gemm_ms"] / 1e6, 1),
+                       transpose_share=round((ops + best["transpose_d_ms"]) / best["total_ms"], 4),
+                       **{k: round(v, 4) for k, v in best.items()})
+        paths[row["path"]].append(row)
         print(json.dumps(row), flush=True)
-    by = sorted(rows, key=lambda x: x["arithmetic_intensity"])
-    third = max(1, len(by) // 3)
-    summary = {"metric": "tensor contraction through transposes + GEMM", "dtype": args.dtype, "cases": len(rows),
-               "low_ai": {"ai_max": by[third - 1]["arithmetic_intensity"],
-                          "median_transpose_share": float(np.median([x["transpose_share"] for x in by[:third]]))},
-               "high_ai": {"ai_min": by[-third]["arithmetic_intensity"],
-                           "median_transpose_share": float(np.median([x["transpose_share"] for x in by[-third:]])),
-                           "median_gflops": float(np.median([x["gflops"] for x in by[-third:]]))}}
-    print(json.dumps(summary), flush=True)
+    for path, rows in paths.items():
+        if not rows:
+            continue
+        by = sorted(rows, key=lambda x: x["arithmetic_intensity"])
+        third = max(1, len(by) // 3)
+        share = "transpose_share" if path == "library" else "operand_transpose_share"
+        summary = {"metric": "tensor contraction through transposes + " + ("GEMM" if path == "library" else "product into the destination"),
+                   "path": path, "dtype": args.dtype, "cases": len(rows),
+                   "low_ai": {"ai_max": by[third - 1]["arithmetic_intensity"],
+                              "median_" + share: float(np.median([x[share] for x in by[:third]]))},
+                   "high_ai": {"ai_min": by[-third]["arithmetic_intensity"],
+                               "median_" + share: float(np.median([x[share] for x in by[-third:]])),
+                               "median_gflops": float(np.median([x["gflops"] for x in by[-third:]]))}}
+        print(json.dumps(summary), flush=True)
 
 
 if __name__ == "__main__":
