@@ -10,11 +10,13 @@ from __future__ import annotations
 import ctypes
 import functools
 import os
+import sysconfig
 from typing import Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtperm.so")
-FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
+# CPython extension; its name holds the ABI of the interpreter that it was built for
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 TPERM_MAX_RANK = 16
 

@@ -9,7 +9,9 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtperm.so")
-FASTCALL = os.path.join(HERE, "_fastcall.so")   # Python calls of the execute entry points (CPython extension)
+# Python calls of the execute entry points: a CPython extension, named after the interpreter's ABI, so that
+# another Python finds none instead of this one's
+FASTCALL = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 PROBE = os.path.join(HERE, "pattern_probe")
 LATENCY_PROBE = os.path.join(HERE, "latency_probe")
 SOURCES = ["plan.cpp", "model.cpp", "product_plan.cpp", "api.cpp", "cache.cpp", "kernels.hip", "verify.hip", "product.hip", "tile_inst_u64_256.hip", "tile_inst_u32_256.hip",

@@ -1,6 +1,10 @@
 """Argument conversion of the execute calls (the CPython extension behind binding.py): the same objects
 are taken and refused as by ctypes, statuses come back as TpermError.  Host only: every call here is
 refused before anything is launched."""
+import os
+import subprocess
+import sys
+import sysconfig
 import threading
 
 import numpy as np
@@ -95,6 +99,19 @@ def test_a_list_that_changes_while_it_is_converted(change, kept):
                 B.tperm_transpose(dims, perm, 8, A, A)
         else:                                             # too many extents, or too few entries
             assert _status(B.tperm_transpose, dims, perm, 8, A, A) == (B.ERR_RANK if n > 16 else B.ERR_PERM)
+
+
+def test_the_extension_belongs_to_this_interpreter():
+    """Its file name holds the interpreter's ABI; where there is none for this one, loading says so."""
+    from paper_1705_01598_amd import _fastcall, build
+    assert B.FASTCALL_PATH == build.FASTCALL == _fastcall.__file__
+    assert os.path.basename(B.FASTCALL_PATH) == "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX") != "_fastcall.so"
+    src = ("from paper_1705_01598_amd import binding as B\n"
+           "B.FASTCALL_PATH = B.FASTCALL_PATH.replace('cpython-', 'cpython-0')\n"
+           "try:\n    B.lib()\nexcept FileNotFoundError as e:\n    print(e)\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", src], capture_output=True, text=True, cwd=root)
+    assert out.returncode == 0 and "paper_1705_01598_amd.build" in out.stdout
 
 
 def test_calls_from_several_threads(plan):
