@@ -550,7 +550,7 @@ def test_plan_cache_is_thread_safe():
         pytest.skip("a GPU is present: covered by the GPU tests")
     import threading
     B.tperm_cache_clear()
-    a = np.zeros(64, dtype=np.int64)
+    a = np.zeros(39 * 3 * 2, dtype=np.int64)    # the largest problem: arrays that lie side by side do not overlap
     b = np.zeros_like(a)
     errors = []
 
