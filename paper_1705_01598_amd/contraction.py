@@ -100,37 +100,42 @@ class Contraction:
         self.elem = 4 if dtype == torch.float32 else 8
         self._device = torch.empty(0, dtype=dtype, device=device).device
         self._t = None
-        self._product, operands = self._one_kernel()
+        self._product, operands, n = self._one_kernel()
         if self._product is not None:
             self._operands = self._buffers(operands)
-            n = B.tperm_product_describe(self._product).workspace_bytes
             self._workspace = torch.empty(n // self.elem, dtype=dtype, device=self._device) if n else None
         else:
             self._library_buffers()
 
     def _one_kernel(self):
-        """The product that adds into the destination, and the permutations its operands need: None
-        where an operand is in either of the two matrix layouts already."""
-        lay, best = self.lay, None
+        """The product that adds into the destination, the permutations its operands need (None where an
+        operand is in either of the two matrix layouts already) and its workspace in bytes."""
+        lay = self.lay
         if not 1 <= len(lay.d_labels) <= self._B.TPERM_MAX_RANK:
-            return None, None
-        for summed in (lay.summed, "".join(c for c in lay.r_labels if c in lay.l_labels)):
-            ops = []
-            for labels, free in ((lay.l_labels, lay.free_l), (lay.r_labels, lay.free_r)):
-                if labels in (free + summed, summed + free):
-                    ops.append((None, labels != free + summed, 0))
-                else:
-                    ops.append((tuple(labels.index(c) for c in free + summed), False, math.prod(lay.dims(labels))))
-            if best is None or ops[0][2] + ops[1][2] < best[0][2] + best[1][2]:
-                best = ops
+            return None, None, 0
+
+        def place(labels, free, summed):    # (permutation, summed index first)
+            if labels == free + summed:
+                return None, False
+            if labels == summed + free:
+                return None, True
+            return tuple(map(labels.index, free + summed)), False
+
+        best = least = None
+        for summed in dict.fromkeys((lay.summed, "".join(c for c in lay.r_labels if c in lay.l_labels))):
+            ops = place(lay.l_labels, lay.free_l, summed), place(lay.r_labels, lay.free_r, summed)
+            moved = (lay.m if ops[0][0] else 0) + (lay.n if ops[1][0] else 0)    # times k
+            if best is None or moved < least:
+                best, least = ops, moved
         try:
             product = self._B.tperm_product_create(lay.dims(lay.free_l + lay.free_r), lay.t_perm, len(lay.free_l),
                                                    lay.k, self.elem, best[0][1], best[1][1])
         except self._B.TpermError:    # tensors of 4 GiB and more
-            return None, None
-        if not self._B.tperm_product_describe(product).pays:
-            return None, None
-        return product, (best[0][0], best[1][0])
+            return None, None, 0
+        info = self._B.tperm_product_describe(product)
+        if not info.pays:
+            return None, None, 0
+        return product, (best[0][0], best[1][0]), info.workspace_bytes
 
     def _buffers(self, perms):
         """(permutation, buffer) of either operand; inputs already in matrix layout are used in place."""
