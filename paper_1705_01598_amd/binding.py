@@ -169,7 +169,7 @@ def _marshalled(dims: tuple, perm: tuple):
 def _marshal(dims: Sequence[int], perm: Sequence[int]):
     # Calls that plan and tune; the execute calls convert theirs in the extension.  The C side only reads
     # the two arrays, so calls (and threads) that name the same problem, by value, share them: building
-    # them takes 3 of the 46 us of a contraction that is planned again for each call.
+    # them takes 3 of the 40 us of a contraction that is planned again for each call.
     len(dims)  # extents come as a sequence: an iterator is a TypeError
     return _marshalled(tuple(map(int, dims)), tuple(map(int, perm)))
 

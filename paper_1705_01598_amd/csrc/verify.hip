@@ -32,8 +32,8 @@ static_assert(sizeof(MultisetPartial) == kVerifyPartialBytes, "partial result si
 
 // A chunk is digested by 1024 threads with all their 16-byte loads (four or eight each) in flight
 // at once.  What bounds it: memory for large tensors; one round trip to memory plus the reductions
-// for small ones.  Measured on MI355X, both tensors of a transpose just made, with the verdict, in
-// microseconds (with one word per load, a workgroup of 256 threads and a launch per tensor before):
+// for small ones.  Measured on MI355X, both tensors of a transpose just made (by tperm_execute; behind the
+// cached step of tperm_execute_verified 44 instead of 49), with the verdict, in microseconds (with one word per load, a workgroup of 256 threads and a launch per tensor before):
 // 2 x 134 MB of 4-byte words 49 (96), 2 x 500 MB 171 (343), 2 x 0.26 MB 7.5 (41); 8-byte words 49 (91),
 // 169 (215), 8.5 (43).  512 threads are level on large tensors, 256 are up to 10 % behind.
 constexpr int kPartialThreads = 1024;
