@@ -14,6 +14,8 @@ const void* tile_kernel_u64_64(int nreg, bool use_lds, int nt, bool align, bool 
 const void* tile_kernel_u32_64(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
 const void* tile_kernel_lean_u64(int nreg, int nt);
 const void* tile_kernel_lean_u32(int nreg, int nt);
+const void* tile_kernel_tab_u32(int nreg, int nt, bool acc, bool vec2, bool lean);
+const void* tile_kernel_tab_u64(int nreg, int nt, bool acc, bool vec2, bool lean);
 const void* tile_kernel_big_u64(int nreg, int nt, bool align, bool acc, bool vec2);
 const void* tile_kernel_big_u32(int nreg, int nt, bool align, bool acc, bool vec2);
 
@@ -88,6 +90,9 @@ static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_align
     const int pol = tile_launch_policy(plan, acc, sector_aligned_out, read_again);
     const int nt = pol == 2 ? 2 : (pol == 3 ? 1 : (pol == 4 ? 3 : 0));  // template parameter NT
     const bool align = plan.align_out;
+    if (runs_with_tables(plan, acc))
+        return plan.elem == 8 ? tile_kernel_tab_u64(plan.nreg, nt, acc, plan.vec2, runs_lean(plan, acc))
+                              : tile_kernel_tab_u32(plan.nreg, nt, acc, plan.vec2, runs_lean(plan, acc));
     if (runs_lean(plan, acc))
         return plan.elem == 8 ? tile_kernel_lean_u64(plan.nreg, nt) : tile_kernel_lean_u32(plan.nreg, nt);
     if (plan.big) {
@@ -109,8 +114,7 @@ bool tile_kernel_exists(const Plan& plan, bool acc) {
 hipError_t tile_blocks_per_cu(const Plan& plan, int* blocks) {
     const void* f = tile_kernel_for(plan, false, true);
     if (f == nullptr) return hipErrorInvalidValue;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, plan.threads,
-                                                        (size_t)plan.lds_bytes * plan.tile.lds_buffers);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, plan.threads, launch_lds_bytes(plan));
 }
 
 hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t stream, int grid,
@@ -121,8 +125,8 @@ hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t 
     // large tensors: the range one buffer description covers from a tile's origin
     uint32_t nbytes = plan.big ? TPERM_BIG_RANGE : (uint32_t)((uint64_t)plan.c.volume * (uint64_t)plan.elem);
     void* args[] = {(void*)&d, (void*)&in, (void*)&out, (void*)&nbytes};
-    return hipLaunchKernel(f, dim3((unsigned)grid), dim3((unsigned)plan.threads), args,
-                           (size_t)plan.lds_bytes * plan.tile.lds_buffers, stream);
+    return hipLaunchKernel(f, dim3((unsigned)grid), dim3((unsigned)plan.threads), args, launch_lds_bytes(plan),
+                           stream);
 }
 
 hipError_t launch_naive(const Plan& plan, const void* in, void* out, hipStream_t stream,

@@ -604,6 +604,36 @@ static uint32_t set_lds_strides(TileDesc* d, const int* dim_of_in, const int* di
     return cum;
 }
 
+// Position tables of both sides, where they pay and fit the LDS of a workgroup.  The number of dims in front
+// goes by what one wavefront spends on the larger of its two tables.
+// Where they pay: filling them costs a pass over a part of the dims, two barriers and a trip through the LDS; a
+// look-up takes 40 cycles per slot and side, without them it is 60 per dim (less for the first two, whose constants are
+// there early).  Time without / with, geometric mean (least, most) over 184 seeded tensors of 2 to 600 MB, same
+// tiles: two dims 0.96 with 3 slots, 0.99 to 1.00 with more; three dims 1.005 (0.96, 1.05) with 3 slots, 1.02 (0.99,
+// 1.08) with 4 to 11; four 1.04 (1.00, 1.10) with 3 and 4, 1.05 (1.01, 1.17) with more; five and six 1.03 (0.99, 1.10)
+// with 3 and 4, 1.08 (1.00, 1.20) with more.  (10 x 10 x 4 x 10 x 10 x 2 x 6 x 7 x 3 of 4-byte elements, 12 slots of
+// five dims: 26.2 -> 22.9 us.)
+static void set_tables(TileDesc* d, int nreg) {
+    if (d->n_tile_dims < 3u || nreg * ((int)d->n_tile_dims - 1) < 8) return;
+    int64_t entries = 0;
+    for (int side = 0; side < 2; ++side) {
+        const TileDim* dims = side == 0 ? d->in_order : d->out_order;
+        const int64_t vol = side == 1 && d->oa.enabled ? d->oa.total_slots : d->tile_vol;
+        PosTable best{0, 0, 0, 0};
+        int64_t least = 0, low = 1;
+        for (uint32_t s = 1; s <= d->n_tile_dims; ++s) {
+            low *= dims[s - 1].ext;
+            const int64_t high = vol / low, work = std::max(ceil_div(low, 64) * s, ceil_div(high, 64) * (d->n_tile_dims - s));
+            if (least != 0 && work >= least) continue;
+            least = work;
+            best = PosTable{s, (uint32_t)low, (uint32_t)high, low > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)low - 1) / (uint64_t)low) : 0u};
+        }
+        d->table[side] = best;
+        entries += (int64_t)best.low + best.high;
+    }
+    d->tables = entries * (int64_t)sizeof(PosEntry) <= kMaxLdsBytes && d->table[0].low > 1 && d->table[1].low > 1 ? 1u : 0u;
+}
+
 tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuildOpts& opts) {
     const int lds_pad = opts.lds_pad, grid_mode = opts.grid_mode, window_in = opts.window_in,
               window_out = opts.window_out, threads = opts.threads, lds_buffers = opts.lds_buffers;
@@ -992,6 +1022,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
     if (plan->spare && !padded) ++lds_elems;
     d.lds_elems = lds_elems;
     d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)lds_elems * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;
+    if (tile_form_with_tables(nreg_final, threads, cand.use_lds, align_out, false, opts.big)) set_tables(&d, nreg_final);
     plan->tile = d;
     plan->cand = cand;
     plan->kclass = cand.kclass;
@@ -1275,6 +1306,24 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
     // set of tiles, use a small one that still exercises the iteration arithmetic
     const uint32_t grid = d.grid_mode != 0u ? 16u : 7u;
     std::vector<char> tile_seen(d.num_tiles, 0);
+    if (d.tables != 0u) {
+        // the kernel adds up two table entries per position
+        if (launch_lds_bytes(plan) > (size_t)kMaxLdsBytes) return TPERM_ERR_INTERNAL;
+        for (int side = 0; side < 2; ++side) {
+            const PosTable& t = d.table[side];
+            const TileDim* dims = side == 0 ? d.in_order : d.out_order;
+            const uint32_t vol = side == 1 && d.oa.enabled ? d.oa.total_slots : d.tile_vol;
+            for (uint32_t k = 0; k < slots; ++k) {
+                uint32_t low, high;
+                pos_entries_of(t, k, &low, &high);
+                if (low >= t.low || high < t.low || high - t.low >= t.high) return TPERM_ERR_INTERNAL;
+                if (k >= vol) continue;
+                const PosEntry a = pos_entry(dims, 0u, t.split, low), b = pos_entry(dims, t.split, d.n_tile_dims, high - t.low);
+                const Slot s = tile_slot(dims, d.n_tile_dims, k);
+                if (a.goff + b.goff != s.goff || a.loff + b.loff != s.loff || a.coord + b.coord != (s.xa | s.xb << 16)) return TPERM_ERR_INTERNAL;
+            }
+        }
+    }
     for (uint32_t block = 0; block < grid; ++block)
         for (uint32_t it = 0;; ++it) {
             const uint32_t b = tile_of(d, block, grid, it);

@@ -118,6 +118,18 @@ struct Plan {
     int max_blocks = 0;
 };
 
+// The kernel that runs the plan takes its positions from tables.
+inline bool runs_with_tables(const Plan& p, bool accumulate) {
+    return p.tile.tables != 0u && tile_form_with_tables(p.nreg, p.threads, p.use_lds, p.align_out, p.loads_first && !accumulate, p.big);
+}
+
+// LDS of a workgroup: the images, or the position tables that are there before the first of them.
+inline size_t launch_lds_bytes(const Plan& p) {
+    const size_t images = (size_t)p.lds_bytes * p.tile.lds_buffers;
+    const size_t tables = p.tile.tables == 0u ? 0u : ((size_t)p.tile.table[0].low + p.tile.table[0].high + p.tile.table[1].low + p.tile.table[1].high) * sizeof(PosEntry);
+    return images > tables ? images : tables;
+}
+
 // The variant for small tensors runs the plan / the kernel that runs it has no masks.
 inline bool runs_lean(const Plan& p, bool accumulate) { return p.lean && !accumulate && !p.loads_first; }
 inline bool runs_without_masks(const Plan& p, bool accumulate) {

@@ -3,7 +3,8 @@
 //
 // Tile kernel, per workgroup (256 threads = 4 wavefronts of 64):
 //   prologue  every thread evaluates, once, the minor positions (Eqs. (4)-(6)) of the
-//             NREG tile slots it owns and keeps them in registers;
+//             NREG tile slots it owns, dim by dim or from tables that the workgroup fills in the
+//             LDS first, and keeps them in registers;
 //   per tile  the major offsets (Eqs. (2),(3)) are evaluated lane-parallel: lane j of a
 //             16-lane DPP row holds term j, a row_shr scan adds them, v_readlane moves the
 //             sum into scalar registers (the wave64 form of the paper's Algorithm 1);
@@ -209,6 +210,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
 // the tile kernel
 // ---------------------------------------------------------------------------------------
 
+// TAB: positions inside the tile from tables (PosTable), for tiles of several dims.
 // BIG: tensors of 4 GiB and more.  A tile's origin (its major offset) no longer fits the 32-bit
 // scalar offset of a buffer access, so it goes into the base address instead: every tile
 // describes its buffers anew, starting at its own origin, and the scalar offset stays zero.  The
@@ -216,7 +218,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
 // and the dropped-offset masking work as before; nbytes is then TPERM_BIG_RANGE, the range one
 // such description covers.  With line-aligned windows the halo origin in front of the tensors
 // moves along with the tile's.  LDS-staged tiles in every form, stores first.
-template <typename T, int NREG, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST, bool VEC2, bool BIG = false, bool LEAN = false>
+template <typename T, int NREG, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST, bool VEC2, bool BIG = false, bool LEAN = false, bool TAB = false>
 __global__ void __launch_bounds__(THREADS)
 tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_arg, uint32_t nbytes_arg) {
     static_assert(!BIG || (USE_LDS && !LOADS_FIRST), "large tensors: LDS-staged tiles, stores first");
@@ -260,6 +262,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // not instantiated.  Hence without masks: 32 slots, and 24 of 8-byte elements, always; 24 of
     // 4-byte elements accumulating below 4 GiB; and the LEAN variants for small tensors.
     constexpr bool NO_MASKS = tile_form_without_masks((int)sizeof(T), NREG, THREADS, USE_LDS, ALIGN, ACC, VEC2, BIG, LEAN);
+    static_assert(!TAB || tile_form_with_tables(NREG, THREADS, USE_LDS, ALIGN, LOADS_FIRST, BIG), "no positions from tables in this form");
     static_assert(!LEAN || NO_MASKS, "the lean form is a plain LDS-staged one of 256 threads");
     typedef typename std::conditional<sizeof(T) == 4, uint64_t, Pair64>::type pair_t;
     typedef Elem<typename std::conditional<VEC2, pair_t, T>::type, NT> io;
@@ -295,6 +298,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     uint32_t lds_buffers = d.lds_buffers, pair_lstride = d.pair_lstride, pair_a_split = d.pair_a_split;
     if constexpr (PIN) {
         for (int i = 0; i < 2; ++i) {
+            if (TAB) break;
             keep_tile_dim(first_out[i]);
             if (USE_LDS) keep_tile_dim(first_in[i]);
         }
@@ -330,7 +334,67 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
                              // read on the write side
     uint32_t wr_aux[NREG];   // ALIGN: unshifted tile coordinate along the shifted dim |
                              // phase of the row start << 16
-    {
+    // TAB: from tables.  Each wavefront fills one of the four, then a slot's position is
+    // two entries added up, whatever the number of tile dims.  The write side's wait until the first
+    // tile's loads are under way.  Worked out dim by dim (below), a slot and side cost some 60 cycles
+    // per dim, all of them before the first load: 1.5 to 2.5 us of kernels of 7 to 15 us with 3 or 4
+    // slots, 3 to 5.6 us of 25 to 32 with 10 or 12 slots of rank-4 and rank-5 tiles.
+    PosEntry* const tab = reinterpret_cast<PosEntry*>(smem_raw);
+    PosTable tab_rd = {}, tab_wr = {};
+    // entries of position k of a side whose tables start at `first`
+    auto look_up = [&](const PosTable& t, uint32_t first, uint32_t k) {
+        uint32_t low, high;
+        pos_entries_of(t, k, &low, &high);
+        const PosEntry a = tab[first + low], b = tab[first + high];
+        return PosEntry{a.goff + b.goff, a.loff + b.loff, a.coord + b.coord, 0u};
+    };
+    auto write_side = [&]() {
+#pragma unroll
+        for (int j = 0; j < NREG; ++j) {
+            const uint32_t k = tid + (uint32_t)j * THREADS;
+            const bool used = k < tile_vol;
+            const PosEntry e = look_up(tab_wr, tab_rd.low + tab_rd.high, k);
+            wr_aux[j] = 0;
+            wr_off[j] = used ? e.goff : (NO_MASKS ? kDroppedOffset : 0u);
+            wr_mask[j] = used ? e.coord : 0xFFFFFFFFu;
+            lds_pos[j] |= (used ? e.loff : 0u) << 16;
+        }
+    };
+    if constexpr (TAB) {
+        tab_rd = d.table[0];
+        tab_wr = d.table[1];
+        // one of the four wavefronts per table
+        const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+        const bool wr = part >= 2u, high = (part & 1u) != 0u;
+        const PosTable t = wr ? tab_wr : tab_rd;
+        const uint32_t count = high ? t.high : t.low, n = high ? n_tile_dims - t.split : t.split;
+        const TileDim* const dims = (wr ? d.out_order : d.in_order) + (high ? t.split : 0u);
+        PosEntry* const to = tab + (wr ? tab_rd.low + tab_rd.high : 0u) + (high ? t.low : 0u);
+        // the first two dims in one batch of loads (a tile has 13 dims at most, the array 16)
+        TileDim dim0 = dims[0], dim1 = dims[1];
+        keep_tile_dim(dim0);
+        keep_tile_dim(dim1);
+        for (uint32_t e = tid & 63u; e < count; e += 64u) {
+            PosEntry x = {0u, 0u, 0u, 0u};
+            uint32_t rem = e;
+            if (n > 0u) pos_digit(dim0, &rem, &x);
+            if (n > 1u) pos_digit(dim1, &rem, &x);
+            for (uint32_t i = 2; i < n; ++i) pos_digit(dims[i], &rem, &x);
+            x.goff *= (uint32_t)sizeof(T);
+            to[e] = x;
+        }
+        __syncthreads();
+        const uint32_t spare = NO_MASKS ? lds_elems - 1u : 0u;
+#pragma unroll
+        for (int j = 0; j < NREG; ++j) {
+            const uint32_t k = tid + (uint32_t)j * THREADS;
+            const bool used = k < tile_vol;
+            const PosEntry e = look_up(tab_rd, 0u, k);
+            rd_off[j] = used ? e.goff : (NO_MASKS ? kDroppedOffset : 0u);
+            rd_mask[j] = used ? e.coord : 0xFFFFFFFFu;
+            lds_pos[j] = used ? e.loff : spare;
+        }
+    } else {
         // Slots walk the tile dims in groups of up to four (5 of 5 and 10 slots, 7 of 7 and 14): each dim's
         // constants are fetched once per group (scalar loads) and the group's independent digit steps
         // overlap, instead of one dependent chain per slot that waits for the same loads again.
@@ -491,6 +555,10 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
 #pragma unroll
         for (int j = 0; j < NREG; ++j)  // distinct offsets, or the compiler folds them into one
             io::store(nothing, rsrc_out_whole, kDroppedOffset + (LOADS_FIRST ? 0u : 4u * (uint32_t)j), 0u);
+    }
+    if constexpr (TAB) {
+        write_side();
+        __syncthreads();  // the first image goes where the tables are
     }
     // the position of the tile after this one is worked out while the loads are in flight
     uint32_t bn = tile_of(walk, block, grid, it + 1);
@@ -691,6 +759,78 @@ static const void* tile_kernel_ptr(int nreg) {
     }
 #undef TPERM_CASE
     return nullptr;
+}
+
+// Kernel pointer of a form with positions from tables; as above.
+template <typename T, int NT, bool ACC, bool VEC2, bool LEAN>
+static const void* tile_kernel_tab_ptr(int nreg) {
+    switch (nreg) {
+#define TPERM_CASE(N) \
+    case N:           \
+        return reinterpret_cast<const void*>(&tile_kernel<T, N, 256, true, NT, false, ACC, false, VEC2, false, LEAN, true>);
+        TPERM_CASE(8)
+        TPERM_CASE(12)
+        TPERM_CASE(16)
+        TPERM_CASE(6)
+        default:
+            break;
+    }
+    if constexpr (!LEAN) {
+        switch (nreg) {
+            TPERM_CASE(3)
+            TPERM_CASE(4)
+            TPERM_CASE(24)
+            TPERM_CASE(32)
+            default:
+                break;
+        }
+    }
+    if constexpr (LEAN && sizeof(T) == 4) {
+        switch (nreg) {
+            TPERM_CASE(24)
+            default:
+                break;
+        }
+    }
+    if constexpr (!LEAN && !VEC2) {
+        switch (nreg) {
+            TPERM_CASE(5)
+            default:
+                break;
+        }
+    }
+    if constexpr (!VEC2) {
+        switch (nreg) {
+            TPERM_CASE(7)
+            TPERM_CASE(10)
+            TPERM_CASE(14)
+            default:
+                break;
+        }
+    }
+#undef TPERM_CASE
+    return nullptr;
+}
+
+template <typename T, bool ACC, bool VEC2, bool LEAN>
+static const void* tile_kernel_tab_policy(int nreg, int nt) {
+    switch (nt) {
+        case 0: return tile_kernel_tab_ptr<T, 0, ACC, VEC2, LEAN>(nreg);
+        case 2: return tile_kernel_tab_ptr<T, 2, ACC, VEC2, LEAN>(nreg);
+        default: break;
+    }
+    if constexpr (!ACC) {
+        if (nt == 1) return tile_kernel_tab_ptr<T, 1, ACC, VEC2, LEAN>(nreg);
+        if (nt == 3) return tile_kernel_tab_ptr<T, 3, ACC, VEC2, LEAN>(nreg);
+    }
+    return nullptr;
+}
+
+template <typename T>
+static const void* tile_kernel_tab_select(int nreg, int nt, bool acc, bool vec2, bool lean) {
+    if (acc) return vec2 || lean ? nullptr : tile_kernel_tab_policy<T, true, false, false>(nreg, nt);
+    if (vec2) return lean ? nullptr : tile_kernel_tab_policy<T, false, true, false>(nreg, nt);
+    return lean ? tile_kernel_tab_policy<T, false, false, true>(nreg, nt) : tile_kernel_tab_policy<T, false, false, false>(nreg, nt);
 }
 
 // nt: 0 = cached, 1 = nontemporal stores, 2 = nontemporal loads and stores, 3 = nontemporal

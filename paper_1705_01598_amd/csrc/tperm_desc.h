@@ -85,6 +85,21 @@ struct OutAlign {
     uint32_t in_halo_elems;  // input elements between the tensor base and the halo origin
 };
 
+// How a workgroup works out the positions inside its tile (Eqs. (4)-(6)): position k of a side is the sum
+// of an entry for k % low and one for k / low, low the product of the side's first `split` tile dims.  The
+// wavefronts tabulate both in the LDS at the start of the kernel.
+struct PosTable {
+    uint32_t split;
+    uint32_t low, high;  // entries of the two parts
+    uint32_t magic;      // ceil(2^32 / low): k / low == (k * magic) >> 32 for k, low <= 2^13
+};
+struct PosEntry {
+    uint32_t goff;   // bytes from the tile's origin in global memory
+    uint32_t loff;   // elements in the LDS image
+    uint32_t coord;  // coordinates along split dims A | B << 16
+    uint32_t unused;
+};
+
 // Descriptor of the generic tile kernel (Tiled, Packed, PackedSplit and the LDS-free
 // row-copy all reduce to it).
 struct TileDesc {
@@ -92,6 +107,8 @@ struct TileDesc {
     uint32_t tile_vol;      // vol(M_mk) with split dims at their tile extent
     uint32_t n_tile_dims;
     uint32_t n_major;       // terms in use in `major` (the rest are neutral)
+    uint32_t tables;        // 1: positions had better come from tables (see set_tables)
+    PosTable table[2];      // read side, write side
     uint32_t split_ext[2];  // full extent d of split dim A / B (0 if none)
     uint32_t split_tile[2]; // tile extent of split dim A / B
     uint32_t split_step[2]; // distance of consecutive chunk origins (= split_tile unless the
@@ -163,6 +180,14 @@ constexpr bool tile_form_without_masks(int elem, int nreg, int threads, bool use
            (lean || nreg >= 32 || (nreg == 24 && (elem == 8 || (acc && !big))));
 }
 
+// Whether a kernel of the tile family can take its positions from tables.  Not with one or two slots, where
+// they never pay, and not in line-aligned windows, whose tiles have two or three dims and whose registers
+// come out worse with them (a 13953 x 13953 matrix of 4-byte elements 292 -> 314 us).  A kernel of its own: one
+// that chose at run time cost tiles of two dims 1 % (up to 4).
+constexpr bool tile_form_with_tables(int nreg, int threads, bool use_lds, bool align, bool loads_first, bool big) {
+    return use_lds && threads == 256 && !align && !loads_first && !big && nreg >= 3;
+}
+
 // Per-thread, per-slot minor position for the read side (Eq. (4) and the LDS store slot).
 // k is the position inside the tile in input order.  xa/xb are the coordinates along the
 // split dims, used to mask ragged edge tiles.
@@ -188,6 +213,31 @@ TPERM_HD Slot tile_slot(const TileDim* dims, uint32_t n, uint32_t k) {
         if (dims[i].sel == 2u) s.xb = x << dims[i].xshift;
     }
     return s;
+}
+
+// One tile dim's part of a table entry (goff in elements here): the next digit of rem.
+TPERM_HD void pos_digit(const TileDim& t, uint32_t* rem, PosEntry* x) {
+    const uint32_t q = fdiv(*rem, t.div);
+    const uint32_t c = *rem - q * t.ext;
+    *rem = q;
+    x->goff += c * t.gstride;
+    x->loff += c * t.lstride;
+    if (t.sel != 0u) x->coord |= c << (t.sel == 2u ? 16u + t.xshift : t.xshift);
+}
+
+// Entry e of a table over tile dims i0 .. i1 - 1.
+TPERM_HD PosEntry pos_entry(const TileDim* dims, uint32_t i0, uint32_t i1, uint32_t e) {
+    PosEntry x = {0u, 0u, 0u, 0u};
+    for (uint32_t i = i0; i < i1; ++i) pos_digit(dims[i], &e, &x);
+    return x;
+}
+
+// The two entries of position k, counted from the start of a side's tables.  Positions beyond the tile
+// get entries of the tables too.
+TPERM_HD void pos_entries_of(const PosTable& t, uint32_t k, uint32_t* low, uint32_t* high) {
+    const uint32_t q = (uint32_t)(((uint64_t)k * t.magic) >> 32);
+    *low = k - q * t.low;
+    *high = t.low + (q < t.high ? q : t.high - 1u);
 }
 
 // Term `lane` of the major sums for tile b: coordinate along that major dim.
