@@ -122,6 +122,7 @@ hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t 
     const void* f = tile_kernel_for(plan, accumulate, (reinterpret_cast<uintptr_t>(out) & 31u) == 0, read_again);
     if (f == nullptr || grid < 1) return hipErrorInvalidValue;
     TileDesc d = plan.tile;
+    set_turns(plan, (uint32_t)grid, &d);
     // large tensors: the range one buffer description covers from a tile's origin
     uint32_t nbytes = plan.big ? TPERM_BIG_RANGE : (uint32_t)((uint64_t)plan.c.volume * (uint64_t)plan.elem);
     void* args[] = {(void*)&d, (void*)&in, (void*)&out, (void*)&nbytes};

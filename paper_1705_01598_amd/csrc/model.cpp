@@ -90,7 +90,7 @@ tperm_status_t model_plan(const Plan& plan, tperm_model_t* out) {
     const uint32_t elem = (uint32_t)plan.elem;
     const uint32_t per_slot = d.vec2 ? 2u : 1u;  // elements moved by one slot
     const OutAlign& oa = d.oa;
-    const bool windows = plan.use_lds && oa.enabled != 0u;
+    const bool windows = plan.use_lds && oa.line_elems != 0u;
     LineTally rd(15), wr(15);  // up to 8192 slots of up to 16 bytes: at most 2 lines each
     // Tiles are sampled, as in the paper; one per equal stretch of the tile index, at a position
     // inside the stretch that moves by the golden ratio from one stretch to the next, so the

@@ -604,6 +604,32 @@ static uint32_t set_lds_strides(TileDesc* d, const int* dim_of_in, const int* di
     return cum;
 }
 
+// Workgroup w takes tiles w, w + grid, w + 2 grid, ...  (see tile_of).  Where the grid and the leading counters of the walk
+// have factors in common, it meets the same few chunks, and the same few memory channels, in every round:
+// some workgroups get the ragged or slow tiles throughout and finish last (10 x 4 x 5 x 10 x 5 x 3 x 3 x 4 x 3 x 6 x 4 x 3 of 8-byte
+// elements: workgroups end 20 us apart on average, of 290).  So they change places from round to round, by
+// kTurn at a time, such that the last, incomplete round falls to the first ones again: they started first (without
+// that, tensors of a few rounds lose 3 to 12 %).
+// Time in place / changing places, geometric mean (least, most) over 230 seeded and regular tensors, LDS-staged tiles of
+// twelve rounds and more: a single counter 1.03 (0.97, 1.10); line-aligned on both sides 1.03 (0.97, 1.10; 96^4 of 8-byte elements,
+// index order reversed 267 -> 262 us, 8192 x 8192 200 -> 196); gcd(grid, product of the first two counters) of 8 and more 1.03
+// (0.98, 1.17).  The others 0.996 (0.97, 1.02): there the workgroups drift apart anyway, and neighbours share fewer lines.
+// Row copies gain and lose 2 %; line-aligned windows have no registers for it (13953 x 13953 of 4-byte elements +1 %).
+// Below twelve rounds it gains and loses alike (67 MB of 4-byte elements in 8 and 10.7 rounds: 0.94 to 1.07).
+constexpr uint32_t kTurnRounds = 12;
+void set_turns(const Plan& plan, uint32_t grid, TileDesc* d) {
+    d->turns = 0u;
+    d->turn_wrap = 0xFFFFFFFFu;
+    const uint32_t rounds = grid != 0u ? (uint32_t)ceil_div(d->num_tiles, grid) : 0u;
+    if (grid <= kTurn || grid % 8u != 0u || rounds < kTurnRounds) return;
+    if (!plan.use_lds || plan.align_out) return;
+    const int64_t two = (int64_t)d->major.ext[0] * (plan.n_major > 1u ? d->major.ext[1] : 1u);
+    if (plan.n_major != 1u && !plan.cand.aligned && gcd64(grid, two) < 8) return;
+    const uint32_t first_place = (uint32_t)((grid - (uint64_t)(rounds - 1u) * kTurn % grid) % grid);
+    d->turns = 1u | first_place;
+    d->turn_wrap = grid - first_place;
+}
+
 // Position tables of both sides, where they pay and fit the LDS of a workgroup.  The number of dims in front
 // goes by what one wavefront spends on the larger of its two tables.
 // Where they pay: filling them costs a pass over a part of the dims, two barriers and a trip through the LDS; a
@@ -613,25 +639,25 @@ static uint32_t set_lds_strides(TileDesc* d, const int* dim_of_in, const int* di
 // 1.08) with 4 to 11; four 1.04 (1.00, 1.10) with 3 and 4, 1.05 (1.01, 1.17) with more; five and six 1.03 (0.99, 1.10)
 // with 3 and 4, 1.08 (1.00, 1.20) with more.  (10 x 10 x 4 x 10 x 10 x 2 x 6 x 7 x 3 of 4-byte elements, 12 slots of
 // five dims: 26.2 -> 22.9 us.)
-static void set_tables(TileDesc* d, int nreg) {
-    if (d->n_tile_dims < 3u || nreg * ((int)d->n_tile_dims - 1) < 8) return;
+static bool set_tables(TileDesc* d, int nreg) {
+    if (d->n_tile_dims < 3u || nreg * ((int)d->n_tile_dims - 1) < 8) return false;
     int64_t entries = 0;
     for (int side = 0; side < 2; ++side) {
         const TileDim* dims = side == 0 ? d->in_order : d->out_order;
-        const int64_t vol = side == 1 && d->oa.enabled ? d->oa.total_slots : d->tile_vol;
-        PosTable best{0, 0, 0, 0};
+        const int64_t vol = side == 1 && d->oa.line_elems != 0u ? d->oa.total_slots : d->tile_vol;
+        PosTable best{0, 0};
         int64_t least = 0, low = 1;
         for (uint32_t s = 1; s <= d->n_tile_dims; ++s) {
             low *= dims[s - 1].ext;
             const int64_t high = vol / low, work = std::max(ceil_div(low, 64) * s, ceil_div(high, 64) * (d->n_tile_dims - s));
             if (least != 0 && work >= least) continue;
             least = work;
-            best = PosTable{s, (uint32_t)low, (uint32_t)high, low > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)low - 1) / (uint64_t)low) : 0u};
+            best = PosTable{s | (uint32_t)low << 4 | (uint32_t)high << 18, low > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint64_t)low - 1) / (uint64_t)low) : 0u};
         }
         d->table[side] = best;
-        entries += (int64_t)best.low + best.high;
+        entries += best.entries();
     }
-    d->tables = entries * (int64_t)sizeof(PosEntry) <= kMaxLdsBytes && d->table[0].low > 1 && d->table[1].low > 1 ? 1u : 0u;
+    return entries * (int64_t)sizeof(PosEntry) <= kMaxLdsBytes && d->table[0].low() > 1 && d->table[1].low() > 1;
 }
 
 tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuildOpts& opts) {
@@ -872,14 +898,13 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
                 }
             }
         }
-    d.n_major = lane;
+    plan->n_major = lane;
     if (cum >= ((uint64_t)1 << 31)) return TPERM_ERR_KERNEL;
     d.num_tiles = (uint32_t)cum;  // includes the non-existent combinations of split counters
 
     std::memset(&d.oa, 0, sizeof(d.oa));
     if (align_out) {
-        d.oa.enabled = 1;
-        d.oa.line_elems = (uint32_t)line_elems;
+            d.oa.line_elems = (uint32_t)line_elems;
         d.oa.total_slots = (uint32_t)cand.tile_vol;
         d.oa.in_halo_elems = (uint32_t)(line_elems * sI[q0]);
     }
@@ -944,7 +969,6 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
     // every XCD should get at least 8 groups, or the XCDs run out of balance
     while (d.grid_mode == 2u && d.group_log2 > 0u && d.num_tiles < ((64u << d.group_log2)))
         --d.group_log2;
-    d.tiles_per_xcd = (uint32_t)ceil_div((int64_t)d.num_tiles, 8);
 
     // Pairs of 4-byte elements (vec2).  A transposing tile of 4-byte elements can read two
     // neighbours along input dim 0 with one 8-byte load and write two neighbours along output
@@ -1022,7 +1046,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
     if (plan->spare && !padded) ++lds_elems;
     d.lds_elems = lds_elems;
     d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)lds_elems * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;
-    if (tile_form_with_tables(nreg_final, threads, cand.use_lds, align_out, false, opts.big)) set_tables(&d, nreg_final);
+    plan->tables = tile_form_with_tables(nreg_final, threads, cand.use_lds, align_out, false, opts.big) && set_tables(&d, nreg_final);
     plan->tile = d;
     plan->cand = cand;
     plan->kclass = cand.kclass;
@@ -1304,28 +1328,30 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
         if (runs_without_masks(plan, acc) && slots > d.tile_vol && !plan.spare) return TPERM_ERR_INTERNAL;
     // visit tiles the way a launch with `grid` workgroups would; any grid gives the same
     // set of tiles, use a small one that still exercises the iteration arithmetic
-    const uint32_t grid = d.grid_mode != 0u ? 16u : 7u;
+    const uint32_t grid = d.num_tiles >= kTurnRounds * 96u ? 96u : (d.grid_mode != 0u ? 16u : 7u);
+    TileDesc launched = d;
+    set_turns(plan, grid, &launched);
     std::vector<char> tile_seen(d.num_tiles, 0);
-    if (d.tables != 0u) {
+    if (plan.tables) {
         // the kernel adds up two table entries per position
         if (launch_lds_bytes(plan) > (size_t)kMaxLdsBytes) return TPERM_ERR_INTERNAL;
         for (int side = 0; side < 2; ++side) {
             const PosTable& t = d.table[side];
             const TileDim* dims = side == 0 ? d.in_order : d.out_order;
-            const uint32_t vol = side == 1 && d.oa.enabled ? d.oa.total_slots : d.tile_vol;
+            const uint32_t vol = side == 1 && d.oa.line_elems ? d.oa.total_slots : d.tile_vol;
             for (uint32_t k = 0; k < slots; ++k) {
                 uint32_t low, high;
                 pos_entries_of(t, k, &low, &high);
-                if (low >= t.low || high < t.low || high - t.low >= t.high) return TPERM_ERR_INTERNAL;
+                if (low >= t.low() || high < t.low() || high - t.low() >= t.high()) return TPERM_ERR_INTERNAL;
                 if (k >= vol) continue;
-                const PosEntry a = pos_entry(dims, 0u, t.split, low), b = pos_entry(dims, t.split, d.n_tile_dims, high - t.low);
+                const PosEntry a = pos_entry(dims, 0u, t.split(), low), b = pos_entry(dims, t.split(), d.n_tile_dims, high - t.low());
                 const Slot s = tile_slot(dims, d.n_tile_dims, k);
                 if (a.goff + b.goff != s.goff || a.loff + b.loff != s.loff || a.coord + b.coord != (s.xa | s.xb << 16)) return TPERM_ERR_INTERNAL;
             }
         }
     }
-    for (uint32_t block = 0; block < grid; ++block)
-        for (uint32_t it = 0;; ++it) {
+    for (uint32_t workgroup = 0; workgroup < grid; ++workgroup)
+        for (uint32_t it = 0, block = first_turn(workgroup, launched.turns, launched.turn_wrap);; ++it, block = next_turn(block, grid, launched.turns)) {
             const uint32_t b = tile_of(d, block, grid, it);
             if (b >= d.num_tiles) break;
             if (tile_seen[b]) return TPERM_ERR_INTERNAL;
@@ -1340,7 +1366,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
             }
             uint32_t rem_a = 0, rem_b = 0, lo_b = 0;
             tile_remaining(d, [&](uint32_t l) { return coord[l]; }, &rem_a, &rem_b, &lo_b);
-            if (plan.use_lds && d.vec2 && d.oa.enabled) {
+            if (plan.use_lds && d.vec2 && d.oa.line_elems) {
                 // pairs of 4-byte elements in line-aligned windows: read pairs along input dim
                 // 0 (halo included), written pairs along the shifted window
                 const OutAlign& oa = d.oa;
@@ -1399,7 +1425,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
                         out_to_in[go] = lds[li];
                     }
                 }
-            } else if (plan.use_lds && d.oa.enabled) {
+            } else if (plan.use_lds && d.oa.line_elems) {
                 // line-aligned output windows: the read side covers the halo, every row of
                 // the write side shifts its window by its own phase
                 const OutAlign& oa = d.oa;
@@ -1468,7 +1494,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
 tperm_status_t index_map(const Plan& plan, int64_t* out_to_in) {
     const tperm_status_t st = index_map_at_phase(plan, out_to_in, 0u);
     if (st != TPERM_OK) return st;
-    if (plan.kclass != TPERM_KERNEL_COPY && plan.kclass != TPERM_KERNEL_NAIVE && plan.tile.oa.enabled) {
+    if (plan.kclass != TPERM_KERNEL_COPY && plan.kclass != TPERM_KERNEL_NAIVE && plan.tile.oa.line_elems) {
         // which tile writes an element depends on the phase of the output pointer; the
         // element map must not
         std::vector<int64_t> other((size_t)plan.c.volume);

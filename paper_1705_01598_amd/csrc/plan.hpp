@@ -112,21 +112,26 @@ struct Plan {
     // padded rows that is padding; an image without any is one element longer than the tile.  It
     // stays within kMaxLdsBytes: there are fewer elements than slots, and all slots fit.
     bool spare = false;
+    uint32_t n_major = 0;    // terms in use in tile.major (the rest are neutral)
+    bool tables = false;     // positions had better come from tables (see set_tables)
     TileDesc tile;
     NaiveDesc naive;
     // launch geometry, resolved on first execute (needs the device); 0 = not yet
     int max_blocks = 0;
 };
 
+// The places that workgroups take in the rounds of tiles of a launch with this grid.
+void set_turns(const Plan& plan, uint32_t grid, TileDesc* d);
+
 // The kernel that runs the plan takes its positions from tables.
 inline bool runs_with_tables(const Plan& p, bool accumulate) {
-    return p.tile.tables != 0u && tile_form_with_tables(p.nreg, p.threads, p.use_lds, p.align_out, p.loads_first && !accumulate, p.big);
+    return p.tables && tile_form_with_tables(p.nreg, p.threads, p.use_lds, p.align_out, p.loads_first && !accumulate, p.big);
 }
 
 // LDS of a workgroup: the images, or the position tables that are there before the first of them.
 inline size_t launch_lds_bytes(const Plan& p) {
     const size_t images = (size_t)p.lds_bytes * p.tile.lds_buffers;
-    const size_t tables = p.tile.tables == 0u ? 0u : ((size_t)p.tile.table[0].low + p.tile.table[0].high + p.tile.table[1].low + p.tile.table[1].high) * sizeof(PosEntry);
+    const size_t tables = !p.tables ? 0u : (size_t)(p.tile.table[0].entries() + p.tile.table[1].entries()) * sizeof(PosEntry);
     return images > tables ? images : tables;
 }
 

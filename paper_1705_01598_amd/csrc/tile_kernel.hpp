@@ -73,7 +73,8 @@ __device__ __forceinline__ TileWalk pinned_tile_walk(const TileDesc& d) {
         keep_scalar(w.pair[s].count);
     }
     keep_scalar(w.grid_mode);
-    keep_scalar(w.tiles_per_xcd);
+    keep_scalar(w.turns);
+    keep_scalar(w.turn_wrap);
     keep_scalar(w.group_log2);
     keep_scalar(w.lane_a);
     keep_scalar(w.lane_b);
@@ -363,7 +364,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
         for (int j = 0; j < NREG; ++j) {
             const uint32_t k = tid + (uint32_t)j * THREADS;
             const bool used = k < tile_vol;
-            const PosEntry e = look_up(tab_wr, tab_rd.low + tab_rd.high, k);
+            const PosEntry e = look_up(tab_wr, tab_rd.entries(), k);
             wr_aux[j] = 0;
             wr_off[j] = used ? e.goff : (NO_MASKS ? kDroppedOffset : 0u);
             wr_mask[j] = used ? e.coord : 0xFFFFFFFFu;
@@ -378,9 +379,9 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
         const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
         const bool wr = part >= 2u, high = (part & 1u) != 0u;
         const PosTable t = wr ? tab_wr : tab_rd;
-        const uint32_t count = high ? t.high : t.low, n = high ? n_tile_dims - t.split : t.split;
-        const TileDim* const dims = (wr ? d.out_order : d.in_order) + (high ? t.split : 0u);
-        PosEntry* const to = tab + (wr ? tab_rd.low + tab_rd.high : 0u) + (high ? t.low : 0u);
+        const uint32_t count = high ? t.high() : t.low(), n = high ? n_tile_dims - t.split() : t.split();
+        const TileDim* const dims = (wr ? d.out_order : d.in_order) + (high ? t.split() : 0u);
+        PosEntry* const to = tab + (wr ? tab_rd.entries() : 0u) + (high ? t.low() : 0u);
         // the first two dims in one batch of loads (a tile has 13 dims at most, the array 16)
         TileDim dim0 = dims[0], dim1 = dims[1];
         keep_tile_dim(dim0);
@@ -505,8 +506,9 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
         }
     }
 
-    const uint32_t grid = gridDim.x, block = blockIdx.x;
-    uint32_t it = 0;
+    const uint32_t grid = gridDim.x;
+    constexpr bool TURNS = USE_LDS && !ALIGN;   // the others keep their places, see set_turns
+    uint32_t block = TURNS ? first_turn(blockIdx.x, walk.turns, walk.turn_wrap) : blockIdx.x, it = 0;
     uint32_t b = tile_of(walk, block, grid, it);
     reg_t v[NREG];
     MajorPos pos, nxt;
@@ -573,6 +575,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
         __syncthreads();  // the first image goes where the tables are
     }
     // the position of the tile after this one is worked out while the loads are in flight
+    if (TURNS) block = next_turn(block, grid, walk.turns);
     uint32_t bn = tile_of(walk, block, grid, it + 1);
     const MajorPos no_tile = nxt;  // all zero: no slot is valid
     if (bn < walk.num_tiles) nxt = major_position<NO_MASKS>(walk, ml, bn);
@@ -724,6 +727,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
         b = bn;
         pos = nxt;
         ++it;
+        if (TURNS) block = next_turn(block, grid, walk.turns);
         bn = tile_of(walk, block, grid, it + 1);
         nxt = no_tile;
         if (bn < walk.num_tiles) nxt = major_position<NO_MASKS>(walk, ml, bn);

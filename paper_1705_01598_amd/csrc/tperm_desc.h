@@ -7,6 +7,7 @@
 // dimensions) are enumerated by the tile index b; "major" offsets depend on b only
 // (Eqs. (2),(3)), "minor" offsets on the position k inside the tile (Eqs. (4)-(6)).
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 #if defined(__HIPCC__) || defined(__HIP__)
@@ -78,8 +79,7 @@ struct SplitPair {
 // That dimension is always split dim B here; its tile coordinate x stands for the output
 // coordinate c t - line_elems + x, valid when lo <= x < remaining (see tile_remaining).
 struct OutAlign {
-    uint32_t enabled;
-    uint32_t line_elems;     // elements per 128-byte line (the halo width)
+    uint32_t line_elems;     // elements per 128-byte line (the halo width); 0: no windows
     uint32_t total_slots;    // write-side slots of a tile: rows * t
     uint32_t lstride_b;      // LDS stride of the shifted dimension
     uint32_t in_halo_elems;  // input elements between the tensor base and the halo origin
@@ -89,9 +89,12 @@ struct OutAlign {
 // of an entry for k % low and one for k / low, low the product of the side's first `split` tile dims.  The
 // wavefronts tabulate both in the LDS at the start of the kernel.
 struct PosTable {
-    uint32_t split;
-    uint32_t low, high;  // entries of the two parts
-    uint32_t magic;      // ceil(2^32 / low): k / low == (k * magic) >> 32 for k, low <= 2^13
+    uint32_t shape;  // split | low << 4 | high << 18: entries of the two parts, 13 bits and one more each
+    uint32_t magic;  // ceil(2^32 / low): k / low == (k * magic) >> 32 for k, low <= 2^13
+    TPERM_HD uint32_t split() const { return shape & 15u; }
+    TPERM_HD uint32_t low() const { return shape >> 4 & 0x3FFFu; }
+    TPERM_HD uint32_t high() const { return shape >> 18; }
+    TPERM_HD uint32_t entries() const { return low() + high(); }
 };
 struct PosEntry {
     uint32_t goff;   // bytes from the tile's origin in global memory
@@ -106,9 +109,7 @@ struct TileDesc {
     uint32_t num_tiles;     // vol(M-bar_mk) times the chunk counts of the split dims
     uint32_t tile_vol;      // vol(M_mk) with split dims at their tile extent
     uint32_t n_tile_dims;
-    uint32_t n_major;       // terms in use in `major` (the rest are neutral)
-    uint32_t tables;        // 1: positions had better come from tables (see set_tables)
-    PosTable table[2];      // read side, write side
+    uint32_t turn_wrap;     // see turns
     uint32_t split_ext[2];  // full extent d of split dim A / B (0 if none)
     uint32_t split_tile[2]; // tile extent of split dim A / B
     uint32_t split_step[2]; // distance of consecutive chunk origins (= split_tile unless the
@@ -124,7 +125,7 @@ struct TileDesc {
     uint32_t pair_a_split;  // vec2 in line-aligned windows: 1 if input dim 0, along which the read
                             // pairs run, is split dim A (its remaining extent may then be odd)
     uint32_t grid_mode;     // how workgroups walk the tiles, see tile_of()
-    uint32_t tiles_per_xcd; // grid_mode 1: ceil(num_tiles / 8)
+    uint32_t turns;         // set for a launch: places in the rounds of tiles, see set_turns()
     uint32_t group_log2;    // grid_mode 2: log2 of the tile group dealt to one XCD
     uint32_t lane_a;        // lane of `major` holding the chunk counter of split A (if any)
     uint32_t lane_b;        // same for split B
@@ -135,7 +136,12 @@ struct TileDesc {
     TileDim out_order[TPERM_DESC_MAX_DIMS];  // the same dims, output order
     MajorDims major;
     OutAlign oa;
+    PosTable table[2];      // positions from tables: read side, write side
 };
+// The kernel reads the descriptor from the kernel-argument segment a 64-byte line at a time, every line for the first
+// time in a launch: the walk takes two lines, the tile dims start on lines of their own, and the pointers and the grid behind
+// the descriptor share its last one (off by 8 bytes or 36, kernels of 4 to 10 us take 0.1 to 0.2 us longer).
+static_assert(offsetof(TileDesc, in_order) == 128 && sizeof(TileDesc) % 64 == 32, "lines of the descriptor");
 
 // The fields of TileDesc that say which tile comes next and what is left of the split dims in
 // it (tile_of, tile_remaining), under the same names.  The kernel copies them out of the
@@ -146,7 +152,7 @@ struct TileDesc {
 struct TileWalk {
     uint32_t num_tiles;
     uint32_t split_ext[2], split_tile[2], split_step[2], split_halo[2];
-    uint32_t grid_mode, tiles_per_xcd, group_log2;
+    uint32_t grid_mode, turns, turn_wrap, group_log2;
     uint32_t lane_a, lane_b;
     uint32_t chunk_pair[2];
     SplitPair pair[2];
@@ -165,7 +171,8 @@ TPERM_HD TileWalk tile_walk_of(const D& d) {
         w.pair[s] = d.pair[s];
     }
     w.grid_mode = d.grid_mode;
-    w.tiles_per_xcd = d.tiles_per_xcd;
+    w.turns = d.turns;
+    w.turn_wrap = d.turn_wrap;
     w.group_log2 = d.group_log2;
     w.lane_a = d.lane_a;
     w.lane_b = d.lane_b;
@@ -236,8 +243,8 @@ TPERM_HD PosEntry pos_entry(const TileDim* dims, uint32_t i0, uint32_t i1, uint3
 // get entries of the tables too.
 TPERM_HD void pos_entries_of(const PosTable& t, uint32_t k, uint32_t* low, uint32_t* high) {
     const uint32_t q = (uint32_t)(((uint64_t)k * t.magic) >> 32);
-    *low = k - q * t.low;
-    *high = t.low + (q < t.high ? q : t.high - 1u);
+    *low = k - q * t.low();
+    *high = t.low() + (q < t.high() ? q : t.high() - 1u);
 }
 
 // Term `lane` of the major sums for tile b: coordinate along that major dim.
@@ -290,8 +297,9 @@ TPERM_HD uint32_t tile_of(const D& d, uint32_t block, uint32_t grid, uint32_t i)
     if (d.grid_mode == 1u) {
         const uint32_t xcd = block & 7u, slot = block >> 3, per = grid >> 3;
         const uint32_t local = slot + i * per;
-        if (local >= d.tiles_per_xcd) return d.num_tiles;
-        const uint32_t b = xcd * d.tiles_per_xcd + local;
+        const uint32_t share = (d.num_tiles + 7u) / 8u;
+        if (local >= share) return d.num_tiles;
+        const uint32_t b = xcd * share + local;
         return b < d.num_tiles ? b : d.num_tiles;
     }
     if (d.grid_mode == 2u) {
@@ -303,6 +311,16 @@ TPERM_HD uint32_t tile_of(const D& d, uint32_t block, uint32_t grid, uint32_t i)
     }
     const uint64_t b = (uint64_t)block + (uint64_t)i * grid;
     return b < d.num_tiles ? (uint32_t)b : d.num_tiles;
+}
+
+// Workgroups may change places from round to round of tiles (set_turns in plan.cpp): the place that workgroup `block`
+// starts at, and the one it takes after `block`.  Multiples of 8 places, so that it stays on its XCD.  The first
+// place does without the grid, which the kernel has to fetch from a line of its own.
+constexpr uint32_t kTurn = 88;   // eleven places on each of 8 XCDs
+TPERM_HD uint32_t first_turn(uint32_t block, uint32_t turns, uint32_t wrap) { return block >= wrap ? block - wrap : block + (turns & ~1u); }
+TPERM_HD uint32_t next_turn(uint32_t block, uint32_t grid, uint32_t turns) {
+    block += (turns & 1u) * kTurn;
+    return block >= grid ? block - grid : block;
 }
 
 // Descriptor of the naive gather kernel: one thread per output element.
