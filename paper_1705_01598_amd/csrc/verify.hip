@@ -32,7 +32,7 @@ static_assert(sizeof(MultisetPartial) == kVerifyPartialBytes, "partial result si
 
 // A chunk is digested by 1024 threads with all their 16-byte loads (four or eight each) in flight
 // at once.  What bounds it: memory for large tensors; one round trip to memory plus the reductions
-// for small ones.  Measured on MI355X, both tensors of a transpose just made (by tperm_execute; behind the
+// for small ones.  Measured on MI355X (sums across lanes by shuffles, see Triple), both tensors of a transpose just made (by tperm_execute; behind the
 // cached step of tperm_execute_verified 44 instead of 49), with the verdict, in microseconds (with one word per load, a workgroup of 256 threads and a launch per tensor before):
 // 2 x 134 MB of 4-byte words 49 (96), 2 x 500 MB 171 (343), 2 x 0.26 MB 7.5 (41); 8-byte words 49 (91),
 // 169 (215), 8.5 (43).  512 threads are level on large tensors, 256 are up to 10 % behind.
@@ -50,33 +50,65 @@ __device__ __forceinline__ uint64_t image(uint64_t e) {
 }
 constexpr uint64_t kScrambleFactor = 0xBF58476D1CE4E5B9ull;
 
-// Adds up three 64-bit values over the threads of a workgroup; the totals end up in thread 0.
-// Shuffles inside the wavefronts, one LDS exchange between them.
+// One step of a sum across lanes: x of the lane that the DPP control names, 0 where there is none.
+template <int CTRL>
+__device__ __forceinline__ uint64_t from_lane(uint64_t x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, 0xF, 0xF, true);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Totals of three values over 16 lanes, in the last lane of each row, and over the wavefront, in lane 63.  In registers
+// (DPP row shifts and broadcasts): through the LDS (shuffles), the sixteen wavefronts of a workgroup queue for
+// 36 passes each, a microsecond of kernels that take four to seven.  Self-checking execute with shuffles / with these, in
+// microseconds: 2 x 0.23 MB 11.7 / 9.6, 2 x 2.1 MB 10.8 / 8.8, 2 x 24 MB 26.4 / 24.4, 2 x 64 MB 51.2 / 49.3, 2 x 159 MB 129.9 / 127.1.
+struct Triple {
+    uint64_t s, x, m;
+    template <int CTRL> __device__ __forceinline__ void step() {
+        s += from_lane<CTRL>(s);
+        x ^= from_lane<CTRL>(x);
+        m += from_lane<CTRL>(m);
+    }
+    __device__ __forceinline__ void row_total() {
+        step<0x111>();  // row_shr:1, 2, 4, 8
+        step<0x112>();
+        step<0x114>();
+        step<0x118>();
+    }
+    __device__ __forceinline__ void wave_total() {
+        row_total();
+        // lane 15 of a row into the row after it, then lane 31 into the upper half (other rows get values of no use)
+        step<0x142>();
+        step<0x143>();
+    }
+};
+
+// Adds up three 64-bit values over the threads of a workgroup of at most 16 wavefronts; the totals end up in
+// every thread of its first wavefront.
 template <int THREADS>
 __device__ __forceinline__ void block_reduce3(uint64_t* s, uint64_t* x, uint64_t* m) {
-    constexpr int kWaves = THREADS / 64;
-    static_assert(kWaves >= 1 && kWaves <= 64, "one wavefront adds up the others");
+    constexpr uint32_t kWaves = THREADS / 64;
+    static_assert(kWaves >= 1 && kWaves <= 16, "one row of lanes adds up the wavefronts");
     __shared__ uint64_t red[3][kWaves];
-    auto wave_reduce = [&](int width) {
-        for (int d = width / 2; d > 0; d >>= 1) {
-            *s += __shfl_down(*s, d, 64);
-            *x ^= __shfl_down(*x, d, 64);
-            *m += __shfl_down(*m, d, 64);
-        }
-    };
-    wave_reduce(64);
+    Triple t = {*s, *x, *m};
+    t.wave_total();
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    if (lane == 0) {
-        red[0][wave] = *s;
-        red[1][wave] = *x;
-        red[2][wave] = *m;
+    if (lane == 63u) {
+        red[0][wave] = t.s;
+        red[1][wave] = t.x;
+        red[2][wave] = t.m;
     }
     __syncthreads();
     if (wave == 0) {
-        *s = lane < kWaves ? red[0][lane] : 0;
-        *x = lane < kWaves ? red[1][lane] : 0;
-        *m = lane < kWaves ? red[2][lane] : 0;
-        wave_reduce(64);
+        t = {lane < kWaves ? red[0][lane] : 0, lane < kWaves ? red[1][lane] : 0, lane < kWaves ? red[2][lane] : 0};
+        t.row_total();
+        auto total = [](uint64_t v) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 15), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 15);
+            return ((uint64_t)hi << 32) | lo;
+        };
+        *s = total(t.s);
+        *x = total(t.x);
+        *m = total(t.m);
     }
 }
 
