@@ -121,6 +121,17 @@ typedef struct {
 } tperm_model_t;
 tperm_status_t tperm_plan_model(tperm_plan_t plan, tperm_model_t *model);
 
+/* How a launch of the plan with `workgroups` workgroups runs, beyond what tperm_plan_describe says (the plan
+ * that it describes, or with accumulate != 0 the one that accumulates).  Host only; plans of the copy and naive
+ * classes and workgroups < 1 give TPERM_ERR_KERNEL.  The layout may grow between versions. */
+typedef struct {
+    int tables;      /* 1: positions inside a tile come from tables that a workgroup fills in its LDS first */
+    int lds_bytes;   /* LDS a workgroup asks for: the image or images of tperm_plan_info_t.lds_bytes, or the *
+                      * tables in their place where those are larger                                        */
+    int turns;       /* places by which workgroups move on from round to round of tiles; 0: they keep theirs */
+} tperm_launch_info_t;
+tperm_status_t tperm_plan_launch_info(tperm_plan_t plan, int accumulate, int workgroups, tperm_launch_info_t *info);
+
 /* What the current HIP device reports about itself, for the benchmark's record next to the
  * vendor's 8 TB/s figure that Section 3's STREAM-style normalisation is replaced by here: memory
  * bus width in bits, peak memory clock in kHz, compute units.  Any pointer may be NULL.

@@ -40,7 +40,7 @@ EXPORTS = ["tperm_plan_create", "tperm_plan_create_forced", "tperm_plan_create_m
            "tperm_product_destroy"]
 # include/tperm_tuning.h
 TUNING_EXPORTS = ["tperm_plan_create_ex", "tperm_plan_candidate_count", "tperm_plan_create_candidate",
-                  "tperm_plan_index_map", "tperm_plan_model", "tperm_multiset_compare",
+                  "tperm_plan_index_map", "tperm_plan_model", "tperm_plan_launch_info", "tperm_multiset_compare",
                   "tperm_device_memory_info"]
 
 
@@ -77,6 +77,11 @@ class PlanInfo(ctypes.Structure):
                 ("align_out", ctypes.c_int), ("paired", ctypes.c_int),
                 ("loads_first", ctypes.c_int), ("vec2", ctypes.c_int), ("large", ctypes.c_int),
                 ("without_masks", ctypes.c_int)]
+
+
+class LaunchInfo(ctypes.Structure):
+    """tperm_launch_info_t"""
+    _fields_ = [("tables", ctypes.c_int), ("lds_bytes", ctypes.c_int), ("turns", ctypes.c_int)]
 
 
 class ProductInfo(ctypes.Structure):
@@ -127,6 +132,7 @@ def lib() -> ctypes.CDLL:
         L.tperm_plan_describe.argtypes = [vp, ctypes.POINTER(PlanInfo)]
         L.tperm_plan_index_map.argtypes = [vp, i64p]
         L.tperm_plan_model.argtypes = [vp, ctypes.POINTER(Model)]
+        L.tperm_plan_launch_info.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.POINTER(LaunchInfo)]
         L.tperm_device_memory_info.argtypes = [ip, ip, ip]
         L.tperm_plan_destroy.argtypes = [vp]
         L.tperm_copy_bytes.argtypes = [vp, vp, ctypes.c_size_t, vp]
@@ -371,6 +377,14 @@ def tperm_plan_model(plan: Plan) -> Model:
     if st != OK:
         raise TpermError(st, "tperm_plan_model")
     return m
+
+
+def tperm_plan_launch_info(plan: Plan, accumulate: bool = False, workgroups: int = 512) -> LaunchInfo:
+    info = LaunchInfo()
+    st = lib().tperm_plan_launch_info(plan.handle, int(accumulate), workgroups, ctypes.byref(info))
+    if st != OK:
+        raise TpermError(st, "tperm_plan_launch_info")
+    return info
 
 
 def tperm_transpose(dims: Sequence[int], perm: Sequence[int], elem_size: int, in_ptr: int,

@@ -472,6 +472,19 @@ tperm_status_t tperm_plan_model(tperm_plan_t plan, tperm_model_t* model) {
     return tperm::model_plan(plan->wide.p ? *plan->wide.p : *plan->base.p, model);
 }
 
+tperm_status_t tperm_plan_launch_info(tperm_plan_t plan, int accumulate, int workgroups, tperm_launch_info_t* info) {
+    if (plan == nullptr || info == nullptr) return TPERM_ERR_NULL;
+    const Plan& p = plan->wide.p && accumulate == 0 ? *plan->wide.p : *plan->base.p;
+    std::memset(info, 0, sizeof(*info));
+    if (workgroups < 1 || p.kclass == TPERM_KERNEL_COPY || p.kclass == TPERM_KERNEL_NAIVE) return TPERM_ERR_KERNEL;
+    tperm::TileDesc d = p.tile;
+    tperm::set_turns(p, (uint32_t)workgroups, &d);
+    info->tables = tperm::runs_with_tables(p, accumulate != 0) ? 1 : 0;
+    info->lds_bytes = (int)tperm::launch_lds_bytes(p, accumulate != 0);
+    info->turns = d.turns != 0u ? (int)tperm::kTurn : 0;
+    return TPERM_OK;
+}
+
 tperm_status_t tperm_plan_index_map(tperm_plan_t plan, int64_t* out_to_in) {
     if (plan == nullptr || out_to_in == nullptr) return TPERM_ERR_NULL;
     if (plan->wide.p == nullptr) return tperm::index_map(*plan->base.p, out_to_in);

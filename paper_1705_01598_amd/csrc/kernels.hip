@@ -114,7 +114,7 @@ bool tile_kernel_exists(const Plan& plan, bool acc) {
 hipError_t tile_blocks_per_cu(const Plan& plan, int* blocks) {
     const void* f = tile_kernel_for(plan, false, true);
     if (f == nullptr) return hipErrorInvalidValue;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, plan.threads, launch_lds_bytes(plan));
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, plan.threads, launch_lds_bytes(plan, false));
 }
 
 hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t stream, int grid,
@@ -126,8 +126,8 @@ hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t 
     // large tensors: the range one buffer description covers from a tile's origin
     uint32_t nbytes = plan.big ? TPERM_BIG_RANGE : (uint32_t)((uint64_t)plan.c.volume * (uint64_t)plan.elem);
     void* args[] = {(void*)&d, (void*)&in, (void*)&out, (void*)&nbytes};
-    return hipLaunchKernel(f, dim3((unsigned)grid), dim3((unsigned)plan.threads), args, launch_lds_bytes(plan),
-                           stream);
+    return hipLaunchKernel(f, dim3((unsigned)grid), dim3((unsigned)plan.threads), args,
+                           launch_lds_bytes(plan, accumulate), stream);
 }
 
 hipError_t launch_naive(const Plan& plan, const void* in, void* out, hipStream_t stream,

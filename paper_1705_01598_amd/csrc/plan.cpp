@@ -1335,7 +1335,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
     std::vector<char> tile_seen(d.num_tiles, 0);
     if (plan.tables) {
         // the kernel adds up two table entries per position
-        if (launch_lds_bytes(plan) > (size_t)kMaxLdsBytes) return TPERM_ERR_INTERNAL;
+        if (launch_lds_bytes(plan, false) > (size_t)kMaxLdsBytes || launch_lds_bytes(plan, true) > (size_t)kMaxLdsBytes) return TPERM_ERR_INTERNAL;
         for (int side = 0; side < 2; ++side) {
             const PosTable& t = d.table[side];
             const TileDim* dims = side == 0 ? d.in_order : d.out_order;

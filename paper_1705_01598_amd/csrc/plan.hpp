@@ -129,9 +129,9 @@ inline bool runs_with_tables(const Plan& p, bool accumulate) {
 }
 
 // LDS of a workgroup: the images, or the position tables that are there before the first of them.
-inline size_t launch_lds_bytes(const Plan& p) {
+inline size_t launch_lds_bytes(const Plan& p, bool accumulate) {
     const size_t images = (size_t)p.lds_bytes * p.tile.lds_buffers;
-    const size_t tables = !p.tables ? 0u : (size_t)(p.tile.table[0].entries() + p.tile.table[1].entries()) * sizeof(PosEntry);
+    const size_t tables = !runs_with_tables(p, accumulate) ? 0u : (size_t)(p.tile.table[0].entries() + p.tile.table[1].entries()) * sizeof(PosEntry);
     return images > tables ? images : tables;
 }
 

@@ -98,3 +98,24 @@ def test_workgroups_of_small_tensors(n, tile_in, workgroups):
     info = B.tperm_plan_create_ex((32, 32, n), (1, 0, 2), 8, kernel_class=B.KERNEL_TILED, m=1, tile_in=tile_in, k=1,
                                   tile_out=16, align_out=1, vec2=1).describe()
     assert info.blocks_per_cu == workgroups, B.info_dict(info)
+
+
+@pytest.mark.parametrize("elem", [4, 8])
+def test_a_launch_asks_for_the_lds_of_the_kernel_that_runs(elem):
+    """A tile of 3 x 5 x 333 elements: its tables are larger than its image of 4-byte elements.  Loads first has no kernel
+    with tables, so such a launch asks for the image alone; accumulation runs stores first, with tables."""
+    def plan(**kw):
+        return B.tperm_plan_create_ex((2, 3, 700, 5), (2, 1, 3, 0), elem, kernel_class=B.KERNEL_PACKED, m=2, tile_in=3, k=1, tile_out=333,
+                                      align_out=1, vec2=1, pair_elems=1, **kw)
+    p = plan(loads_first=1)
+    image = p.describe().lds_bytes
+    info, acc = (B.tperm_plan_launch_info(p, accumulate=a) for a in (False, True))
+    assert info.tables == acc.tables == 1 and info.lds_bytes == acc.lds_bytes >= image
+    assert info.lds_bytes > image or elem == 8
+    p = plan(loads_first=2)
+    info, acc = (B.tperm_plan_launch_info(p, accumulate=a) for a in (False, True))
+    assert (info.tables, info.lds_bytes) == (0, image) and acc.tables == 1
+    assert acc.lds_bytes > image or elem == 8
+    assert B.tperm_plan_launch_info(plan(lds_buffers=2, loads_first=2)).lds_bytes == 2 * image
+    with pytest.raises(B.TpermError):
+        B.tperm_plan_launch_info(B.tperm_plan_create((8, 8), (0, 1), elem))    # a copy has no tiles
