@@ -129,6 +129,7 @@ typedef struct {
     int lds_bytes;   /* LDS a workgroup asks for: the image or images of tperm_plan_info_t.lds_bytes, or the *
                       * tables in their place where those are larger                                        */
     int turns;       /* places by which workgroups move on from round to round of tiles; 0: they keep theirs */
+    int steady;      /* 1: they keep theirs in a kernel that has no code for moving on                      */
 } tperm_launch_info_t;
 tperm_status_t tperm_plan_launch_info(tperm_plan_t plan, int accumulate, int workgroups, tperm_launch_info_t *info);
 

@@ -81,7 +81,8 @@ class PlanInfo(ctypes.Structure):
 
 class LaunchInfo(ctypes.Structure):
     """tperm_launch_info_t"""
-    _fields_ = [("tables", ctypes.c_int), ("lds_bytes", ctypes.c_int), ("turns", ctypes.c_int)]
+    _fields_ = [("tables", ctypes.c_int), ("lds_bytes", ctypes.c_int), ("turns", ctypes.c_int),
+                ("steady", ctypes.c_int)]
 
 
 class ProductInfo(ctypes.Structure):

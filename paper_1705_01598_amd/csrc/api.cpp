@@ -478,10 +478,11 @@ tperm_status_t tperm_plan_launch_info(tperm_plan_t plan, int accumulate, int wor
     std::memset(info, 0, sizeof(*info));
     if (workgroups < 1 || p.kclass == TPERM_KERNEL_COPY || p.kclass == TPERM_KERNEL_NAIVE) return TPERM_ERR_KERNEL;
     tperm::TileDesc d = p.tile;
-    tperm::set_turns(p, (uint32_t)workgroups, &d);
+    tperm::set_turns(p, (uint32_t)workgroups, accumulate != 0, &d);
     info->tables = tperm::runs_with_tables(p, accumulate != 0) ? 1 : 0;
     info->lds_bytes = (int)tperm::launch_lds_bytes(p, accumulate != 0);
     info->turns = d.turns != 0u ? (int)tperm::kTurn : 0;
+    info->steady = tperm::runs_steady(p, accumulate != 0, d.turns != 0u) ? 1 : 0;
     return TPERM_OK;
 }
 

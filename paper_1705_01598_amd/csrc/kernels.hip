@@ -8,8 +8,8 @@
 
 namespace tperm {
 
-const void* tile_kernel_u64_256(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
-const void* tile_kernel_u32_256(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
+const void* tile_kernel_u64_256(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2, bool steady);
+const void* tile_kernel_u32_256(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2, bool steady);
 const void* tile_kernel_u64_64(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
 const void* tile_kernel_u32_64(int nreg, bool use_lds, int nt, bool align, bool acc, bool loads_first, bool vec2);
 const void* tile_kernel_lean_u64(int nreg, int nt);
@@ -86,7 +86,8 @@ accumulate_kernel(const F* __restrict__ in, F* __restrict__ out, uint64_t n) {
 // dispatch
 // ---------------------------------------------------------------------------------------
 
-static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_aligned_out, bool read_again = false) {
+// turning: workgroups change places in this launch (set_turns)
+static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_aligned_out, bool turning, bool read_again = false) {
     const int pol = tile_launch_policy(plan, acc, sector_aligned_out, read_again);
     const int nt = pol == 2 ? 2 : (pol == 3 ? 1 : (pol == 4 ? 3 : 0));  // template parameter NT
     const bool align = plan.align_out;
@@ -100,29 +101,33 @@ static const void* tile_kernel_for(const Plan& plan, bool acc, bool sector_align
         return plan.elem == 8 ? tile_kernel_big_u64(plan.nreg, nt, align, acc, plan.vec2)
                               : tile_kernel_big_u32(plan.nreg, nt, align, acc, plan.vec2);
     }
+    const bool steady = runs_steady(plan, acc, turning);
     if (plan.elem == 8)
         return plan.threads == 64 ? tile_kernel_u64_64(plan.nreg, plan.use_lds, nt, align, acc, plan.loads_first, plan.vec2)
-                                  : tile_kernel_u64_256(plan.nreg, plan.use_lds, nt, align, acc, plan.loads_first, plan.vec2);
+                                  : tile_kernel_u64_256(plan.nreg, plan.use_lds, nt, align, acc, plan.loads_first, plan.vec2, steady);
     return plan.threads == 64 ? tile_kernel_u32_64(plan.nreg, plan.use_lds, nt, align, acc, plan.loads_first, plan.vec2)
-                              : tile_kernel_u32_256(plan.nreg, plan.use_lds, nt, align, acc, plan.loads_first, plan.vec2);
+                              : tile_kernel_u32_256(plan.nreg, plan.use_lds, nt, align, acc, plan.loads_first, plan.vec2, steady);
 }
 
 bool tile_kernel_exists(const Plan& plan, bool acc) {
-    return tile_kernel_for(plan, acc, true) != nullptr && tile_kernel_for(plan, acc, false) != nullptr;
+    for (int of = 0; of < 4; ++of)
+        if (tile_kernel_for(plan, acc, (of & 1) != 0, (of & 2) != 0) == nullptr) return false;
+    return true;
 }
 
 hipError_t tile_blocks_per_cu(const Plan& plan, int* blocks) {
-    const void* f = tile_kernel_for(plan, false, true);
+    const void* f = tile_kernel_for(plan, false, true, true);
     if (f == nullptr) return hipErrorInvalidValue;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, plan.threads, launch_lds_bytes(plan, false));
 }
 
 hipError_t launch_tile(const Plan& plan, const void* in, void* out, hipStream_t stream, int grid,
                        bool accumulate, bool read_again) {
-    const void* f = tile_kernel_for(plan, accumulate, (reinterpret_cast<uintptr_t>(out) & 31u) == 0, read_again);
-    if (f == nullptr || grid < 1) return hipErrorInvalidValue;
+    if (grid < 1) return hipErrorInvalidValue;
     TileDesc d = plan.tile;
-    set_turns(plan, (uint32_t)grid, &d);
+    set_turns(plan, (uint32_t)grid, accumulate, &d);
+    const void* f = tile_kernel_for(plan, accumulate, (reinterpret_cast<uintptr_t>(out) & 31u) == 0, d.turns != 0u, read_again);
+    if (f == nullptr) return hipErrorInvalidValue;
     // large tensors: the range one buffer description covers from a tile's origin
     uint32_t nbytes = plan.big ? TPERM_BIG_RANGE : (uint32_t)((uint64_t)plan.c.volume * (uint64_t)plan.elem);
     void* args[] = {(void*)&d, (void*)&in, (void*)&out, (void*)&nbytes};

@@ -615,15 +615,15 @@ static uint32_t set_lds_strides(TileDesc* d, const int* dim_of_in, const int* di
 // index order reversed 267 -> 262 us, 8192 x 8192 200 -> 196); gcd(grid, product of the first two counters) of 8 and more 1.03
 // (0.98, 1.17).  The others 0.996 (0.97, 1.02): there the workgroups drift apart anyway, and neighbours share fewer lines.
 // Row copies gain and lose 2 %; line-aligned windows have no registers for it (13953 x 13953 of 4-byte elements +1 %),
-// nor has one form of sixteen slots (TURNS in tile_kernel.hpp).
+// nor has one form of sixteen slots (tile_form_with_turns).
 // Below twelve rounds it gains and loses alike (67 MB of 4-byte elements in 8 and 10.7 rounds: 0.94 to 1.07).
 constexpr uint32_t kTurnRounds = 12;
-void set_turns(const Plan& plan, uint32_t grid, TileDesc* d) {
+void set_turns(const Plan& plan, uint32_t grid, bool accumulate, TileDesc* d) {
     d->turns = 0u;
     d->turn_wrap = 0xFFFFFFFFu;
     const uint32_t rounds = grid != 0u ? (uint32_t)ceil_div(d->num_tiles, grid) : 0u;
     if (grid <= kTurn || grid % 8u != 0u || rounds < kTurnRounds) return;
-    if (!plan.use_lds || plan.align_out) return;
+    if (!tile_form_with_turns(plan.elem, plan.nreg, plan.use_lds, plan.align_out, plan.vec2, runs_lean(plan, accumulate))) return;
     const int64_t two = (int64_t)d->major.ext[0] * (plan.n_major > 1u ? d->major.ext[1] : 1u);
     if (plan.n_major != 1u && !plan.cand.aligned && gcd64(grid, two) < 8) return;
     const uint32_t first_place = (uint32_t)((grid - (uint64_t)(rounds - 1u) * kTurn % grid) % grid);
@@ -1331,7 +1331,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
     // set of tiles, use a small one that still exercises the iteration arithmetic
     const uint32_t grid = d.num_tiles >= kTurnRounds * 96u ? 96u : (d.grid_mode != 0u ? 16u : 7u);
     TileDesc launched = d;
-    set_turns(plan, grid, &launched);
+    set_turns(plan, grid, false, &launched);
     std::vector<char> tile_seen(d.num_tiles, 0);
     if (plan.tables) {
         // the kernel adds up two table entries per position

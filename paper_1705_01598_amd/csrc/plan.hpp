@@ -121,11 +121,16 @@ struct Plan {
 };
 
 // The places that workgroups take in the rounds of tiles of a launch with this grid.
-void set_turns(const Plan& plan, uint32_t grid, TileDesc* d);
+void set_turns(const Plan& plan, uint32_t grid, bool accumulate, TileDesc* d);
 
 // The kernel that runs the plan takes its positions from tables.
 inline bool runs_with_tables(const Plan& p, bool accumulate) {
     return p.tables && tile_form_with_tables(p.nreg, p.threads, p.use_lds, p.align_out, p.loads_first && !accumulate, p.big);
+}
+
+// The kernel that runs the plan has no code for turns although the form has (see tile_form_with_steady_twin).
+inline bool runs_steady(const Plan& p, bool accumulate, bool turning) {
+    return !turning && !runs_with_tables(p, accumulate) && tile_form_with_steady_twin(p.nreg, p.threads, p.use_lds, p.align_out, p.big);
 }
 
 // LDS of a workgroup: the images, or the position tables that are there before the first of them.

@@ -10,29 +10,29 @@ const void* tile_kernel_big_u32(int nreg, int nt, bool align, bool acc, bool vec
     typedef uint32_t T;
     if (acc) {
         if (vec2) return nullptr;
-        if (align) return nt == 0 ? tile_kernel_ptr<T, 256, true, 0, true, true, false, false, true>(nreg) : nullptr;
+        if (align) return nt == 0 ? tile_kernel_ptr<T, 256, false, true, 0, true, true, false, false, true>(nreg) : nullptr;
         switch (nt) {
-            case 0: return tile_kernel_ptr<T, 256, true, 0, false, true, false, false, true>(nreg);
-            case 2: return tile_kernel_ptr<T, 256, true, 2, false, true, false, false, true>(nreg);
+            case 0: return tile_kernel_ptr<T, 256, false, true, 0, false, true, false, false, true>(nreg);
+            case 2: return tile_kernel_ptr<T, 256, false, true, 2, false, true, false, false, true>(nreg);
             default: return nullptr;
         }
     }
     if (vec2 && align) {
         // pairs of 4-byte elements inside the windows
         switch (nt) {
-            case 0: return tile_kernel_ptr<T, 256, true, 0, true, false, false, true, true>(nreg);
-            case 1: return tile_kernel_ptr<T, 256, true, 1, true, false, false, true, true>(nreg);
-            case 2: return tile_kernel_ptr<T, 256, true, 2, true, false, false, true, true>(nreg);
-            case 3: return tile_kernel_ptr<T, 256, true, 3, true, false, false, true, true>(nreg);
+            case 0: return tile_kernel_ptr<T, 256, false, true, 0, true, false, false, true, true>(nreg);
+            case 1: return tile_kernel_ptr<T, 256, false, true, 1, true, false, false, true, true>(nreg);
+            case 2: return tile_kernel_ptr<T, 256, false, true, 2, true, false, false, true, true>(nreg);
+            case 3: return tile_kernel_ptr<T, 256, false, true, 3, true, false, false, true, true>(nreg);
             default: return nullptr;
         }
     }
 #define TPERM_BIG_POLICIES(ALIGN_, VEC2_)                                                              \
     switch (nt) {                                                                                      \
-        case 0: return tile_kernel_ptr<T, 256, true, 0, ALIGN_, false, false, VEC2_, true>(nreg);      \
-        case 1: return tile_kernel_ptr<T, 256, true, 1, ALIGN_, false, false, VEC2_, true>(nreg);      \
-        case 2: return tile_kernel_ptr<T, 256, true, 2, ALIGN_, false, false, VEC2_, true>(nreg);      \
-        case 3: return tile_kernel_ptr<T, 256, true, 3, ALIGN_, false, false, VEC2_, true>(nreg);      \
+        case 0: return tile_kernel_ptr<T, 256, false, true, 0, ALIGN_, false, false, VEC2_, true>(nreg);      \
+        case 1: return tile_kernel_ptr<T, 256, false, true, 1, ALIGN_, false, false, VEC2_, true>(nreg);      \
+        case 2: return tile_kernel_ptr<T, 256, false, true, 2, ALIGN_, false, false, VEC2_, true>(nreg);      \
+        case 3: return tile_kernel_ptr<T, 256, false, true, 3, ALIGN_, false, false, VEC2_, true>(nreg);      \
         default: return nullptr;                                                                       \
     }
     if (vec2) { TPERM_BIG_POLICIES(false, true) }

@@ -58,6 +58,7 @@ __device__ __forceinline__ void keep_tile_dim(TileDim& t) {
     keep_scalar(t.xshift);
 }
 
+template <bool TURNS>
 __device__ __forceinline__ TileWalk pinned_tile_walk(const TileDesc& d) {
     TileWalk w = tile_walk_of(d);
     keep_scalar(w.num_tiles);
@@ -73,8 +74,10 @@ __device__ __forceinline__ TileWalk pinned_tile_walk(const TileDesc& d) {
         keep_scalar(w.pair[s].count);
     }
     keep_scalar(w.grid_mode);
-    keep_scalar(w.turns);
-    keep_scalar(w.turn_wrap);
+    if (TURNS) {
+        keep_scalar(w.turns);
+        keep_scalar(w.turn_wrap);
+    }
     keep_scalar(w.group_log2);
     keep_scalar(w.lane_a);
     keep_scalar(w.lane_b);
@@ -82,9 +85,9 @@ __device__ __forceinline__ TileWalk pinned_tile_walk(const TileDesc& d) {
 }
 
 // The tile-walk fields as the kernel uses them: a pinned copy, or the descriptor itself.
-template <bool PIN>
+template <bool PIN, bool TURNS>
 __device__ __forceinline__ typename std::conditional<PIN, TileWalk, const TileDesc&>::type tile_walk_source(const TileDesc& d) {
-    if constexpr (PIN) return pinned_tile_walk(d);
+    if constexpr (PIN) return pinned_tile_walk<TURNS>(d);
     else return d;
 }
 
@@ -212,6 +215,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
 // ---------------------------------------------------------------------------------------
 
 // TAB: positions inside the tile from tables (PosTable), for tiles of several dims.
+// TURNS: the code by which workgroups change places from round to round of tiles (tile_form_with_turns).
 // BIG: tensors of 4 GiB and more.  A tile's origin (its major offset) no longer fits the 32-bit
 // scalar offset of a buffer access, so it goes into the base address instead: every tile
 // describes its buffers anew, starting at its own origin, and the scalar offset stays zero.  The
@@ -219,7 +223,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
 // and the dropped-offset masking work as before; nbytes is then TPERM_BIG_RANGE, the range one
 // such description covers.  With line-aligned windows the halo origin in front of the tensors
 // moves along with the tile's.  LDS-staged tiles in every form, stores first.
-template <typename T, int NREG, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST, bool VEC2, bool BIG = false, bool LEAN = false, bool TAB = false>
+template <typename T, int NREG, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST, bool VEC2, bool BIG = false, bool LEAN = false, bool TAB = false,
+          bool TURNS = tile_form_with_turns((int)sizeof(T), NREG, USE_LDS, ALIGN, VEC2, LEAN)>
 __global__ void __launch_bounds__(THREADS)
 tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_arg, uint32_t nbytes_arg) {
     static_assert(!BIG || (USE_LDS && !LOADS_FIRST), "large tensors: LDS-staged tiles, stores first");
@@ -294,7 +299,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     constexpr bool PIN = !ALIGN;
     TileDim first_out[2] = {d.out_order[0], d.out_order[1]};
     TileDim first_in[2] = {d.in_order[0], d.in_order[1]};
-    typename std::conditional<PIN, const TileWalk, const TileDesc&>::type walk = tile_walk_source<PIN>(d);
+    typename std::conditional<PIN, const TileWalk, const TileDesc&>::type walk = tile_walk_source<PIN, TURNS>(d);
     uint32_t n_tile_dims = d.n_tile_dims, tile_vol = d.tile_vol, lds_elems = d.lds_elems;
     uint32_t lds_buffers = d.lds_buffers, pair_lstride = d.pair_lstride, pair_a_split = d.pair_a_split;
     if constexpr (PIN) {
@@ -507,11 +512,6 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     }
 
     const uint32_t grid = gridDim.x;
-    // The others keep their places, see set_turns.  Sixteen slots of 8 bytes with masks: the scalars that turns keep over
-    // the loop push others out to lanes of a vector register, which come back between the last stores and the next loads;
-    // tiles of three dims and more lose 2 to 9 % to that even where no places change (14 x 56 x 146 x 78 x 11, index
-    // order 4 2 0 1 3: 311 us at first, 323 with turns, 297 without); 25 seeded tensors of 80 to 400 us: 1.015 (0.99, 1.09).
-    constexpr bool TURNS = USE_LDS && !ALIGN && !(sizeof(T) == 8 && NREG == 16 && !VEC2 && !LEAN);
     uint32_t block = TURNS ? first_turn(blockIdx.x, walk.turns, walk.turn_wrap) : blockIdx.x, it = 0;
     uint32_t b = tile_of(walk, block, grid, it);
     reg_t v[NREG];
@@ -742,8 +742,26 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
 // Kernel pointer for one element type and workgroup size; nullptr if the combination is
 // not instantiated.  Accumulating kernels (ACC) exist for 256 threads: cached, and nontemporal
 // loads and stores; with line-aligned windows cached only.
-template <typename T, int THREADS, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST = false, bool VEC2 = false, bool BIG = false>
+template <typename T, int THREADS, bool STEADY, bool USE_LDS, int NT, bool ALIGN, bool ACC, bool LOADS_FIRST = false, bool VEC2 = false, bool BIG = false>
 static const void* tile_kernel_ptr(int nreg) {
+    if constexpr (STEADY) {
+        // these forms only
+        if constexpr (tile_form_with_steady_twin(1, THREADS, USE_LDS, ALIGN, BIG)) {
+            switch (nreg) {
+#define TPERM_CASE(N) \
+    case N:           \
+        return reinterpret_cast<const void*>(&tile_kernel<T, N, THREADS, USE_LDS, NT, ALIGN, ACC, LOADS_FIRST, VEC2, BIG, false, false, false>);
+                TPERM_CASE(1)
+                TPERM_CASE(2)
+                TPERM_CASE(3)
+                TPERM_CASE(4)
+#undef TPERM_CASE
+                default:
+                    break;
+            }
+        }
+        return nullptr;
+    }
     switch (nreg) {
 #define TPERM_CASE(N) \
     case N:           \
@@ -857,7 +875,8 @@ static const void* tile_kernel_tab_select(int nreg, int nt, bool acc, bool vec2,
 // loads.  The 64-thread variants exist for policies 0 and 2 only (1 runs as 2).
 // loads_first: order of the next tile's loads and this tile's stores (see the kernel); both
 // orders exist for the plain 256-thread kernels, elsewhere stores go first.
-template <typename T, int THREADS>
+// STEADY: kernels without the code for turns, where there are any.
+template <typename T, int THREADS, bool STEADY = false>
 static const void* tile_kernel_select(int nreg, bool use_lds, int nt, bool align, bool acc,
                                       bool loads_first, bool vec2) {
     if constexpr (THREADS == 256) {
@@ -866,10 +885,10 @@ static const void* tile_kernel_select(int nreg, bool use_lds, int nt, bool align
             if constexpr (sizeof(T) == 4) {
                 if (!use_lds || acc) return nullptr;
                 switch (nt) {
-                    case 0: return tile_kernel_ptr<T, 256, true, 0, true, false, false, true>(nreg);
-                    case 1: return tile_kernel_ptr<T, 256, true, 1, true, false, false, true>(nreg);
-                    case 2: return tile_kernel_ptr<T, 256, true, 2, true, false, false, true>(nreg);
-                    default: return tile_kernel_ptr<T, 256, true, 3, true, false, false, true>(nreg);
+                    case 0: return tile_kernel_ptr<T, 256, STEADY, true, 0, true, false, false, true>(nreg);
+                    case 1: return tile_kernel_ptr<T, 256, STEADY, true, 1, true, false, false, true>(nreg);
+                    case 2: return tile_kernel_ptr<T, 256, STEADY, true, 2, true, false, false, true>(nreg);
+                    default: return tile_kernel_ptr<T, 256, STEADY, true, 3, true, false, false, true>(nreg);
                 }
             } else {
                 return nullptr;
@@ -878,60 +897,60 @@ static const void* tile_kernel_select(int nreg, bool use_lds, int nt, bool align
         if (nt == 3) {
             // nontemporal loads only: plain stores-first forms
             if (acc || loads_first) return nullptr;
-            if (vec2) return use_lds && !align ? tile_kernel_ptr<T, 256, true, 3, false, false, false, true>(nreg) : nullptr;
-            if (align) return use_lds ? tile_kernel_ptr<T, 256, true, 3, true, false>(nreg) : nullptr;
-            return use_lds ? tile_kernel_ptr<T, 256, true, 3, false, false>(nreg)
-                           : tile_kernel_ptr<T, 256, false, 3, false, false>(nreg);
+            if (vec2) return use_lds && !align ? tile_kernel_ptr<T, 256, STEADY, true, 3, false, false, false, true>(nreg) : nullptr;
+            if (align) return use_lds ? tile_kernel_ptr<T, 256, STEADY, true, 3, true, false>(nreg) : nullptr;
+            return use_lds ? tile_kernel_ptr<T, 256, STEADY, true, 3, false, false>(nreg)
+                           : tile_kernel_ptr<T, 256, STEADY, false, 3, false, false>(nreg);
         }
         // pairs of elements: LDS-staged, stores first
         if (vec2) {
             if (!use_lds || align || acc) return nullptr;
-            if (nt == 1) return tile_kernel_ptr<T, 256, true, 1, false, false, false, true>(nreg);
-            return nt != 0 ? tile_kernel_ptr<T, 256, true, 2, false, false, false, true>(nreg)
-                           : tile_kernel_ptr<T, 256, true, 0, false, false, false, true>(nreg);
+            if (nt == 1) return tile_kernel_ptr<T, 256, STEADY, true, 1, false, false, false, true>(nreg);
+            return nt != 0 ? tile_kernel_ptr<T, 256, STEADY, true, 2, false, false, false, true>(nreg)
+                           : tile_kernel_ptr<T, 256, STEADY, true, 0, false, false, false, true>(nreg);
         }
     }
     if (vec2) return nullptr;
     if constexpr (THREADS == 256) {
         if (align && !use_lds) return nullptr;
         if (acc) {
-            if (align) return nt == 0 ? tile_kernel_ptr<T, 256, true, 0, true, true>(nreg) : nullptr;
+            if (align) return nt == 0 ? tile_kernel_ptr<T, 256, STEADY, true, 0, true, true>(nreg) : nullptr;
             switch (nt) {
                 case 0:
-                    return use_lds ? tile_kernel_ptr<T, 256, true, 0, false, true>(nreg)
-                                   : tile_kernel_ptr<T, 256, false, 0, false, true>(nreg);
+                    return use_lds ? tile_kernel_ptr<T, 256, STEADY, true, 0, false, true>(nreg)
+                                   : tile_kernel_ptr<T, 256, STEADY, false, 0, false, true>(nreg);
                 case 2:
-                    return use_lds ? tile_kernel_ptr<T, 256, true, 2, false, true>(nreg)
-                                   : tile_kernel_ptr<T, 256, false, 2, false, true>(nreg);
+                    return use_lds ? tile_kernel_ptr<T, 256, STEADY, true, 2, false, true>(nreg)
+                                   : tile_kernel_ptr<T, 256, STEADY, false, 2, false, true>(nreg);
                 default: return nullptr;
             }
         }
         if (align) {
-            if (nt == 1) return tile_kernel_ptr<T, 256, true, 1, true, false>(nreg);
-            return nt != 0 ? tile_kernel_ptr<T, 256, true, 2, true, false>(nreg)
-                           : tile_kernel_ptr<T, 256, true, 0, true, false>(nreg);
+            if (nt == 1) return tile_kernel_ptr<T, 256, STEADY, true, 1, true, false>(nreg);
+            return nt != 0 ? tile_kernel_ptr<T, 256, STEADY, true, 2, true, false>(nreg)
+                           : tile_kernel_ptr<T, 256, STEADY, true, 0, true, false>(nreg);
         }
         if (loads_first) {
             if (nt == 1)
-                return use_lds ? tile_kernel_ptr<T, 256, true, 1, false, false, true>(nreg)
-                               : tile_kernel_ptr<T, 256, false, 1, false, false, true>(nreg);
+                return use_lds ? tile_kernel_ptr<T, 256, STEADY, true, 1, false, false, true>(nreg)
+                               : tile_kernel_ptr<T, 256, STEADY, false, 1, false, false, true>(nreg);
             if (use_lds)
-                return nt != 0 ? tile_kernel_ptr<T, 256, true, 2, false, false, true>(nreg)
-                               : tile_kernel_ptr<T, 256, true, 0, false, false, true>(nreg);
-            return nt != 0 ? tile_kernel_ptr<T, 256, false, 2, false, false, true>(nreg)
-                           : tile_kernel_ptr<T, 256, false, 0, false, false, true>(nreg);
+                return nt != 0 ? tile_kernel_ptr<T, 256, STEADY, true, 2, false, false, true>(nreg)
+                               : tile_kernel_ptr<T, 256, STEADY, true, 0, false, false, true>(nreg);
+            return nt != 0 ? tile_kernel_ptr<T, 256, STEADY, false, 2, false, false, true>(nreg)
+                           : tile_kernel_ptr<T, 256, STEADY, false, 0, false, false, true>(nreg);
         }
         if (nt == 1)
-            return use_lds ? tile_kernel_ptr<T, 256, true, 1, false, false>(nreg)
-                           : tile_kernel_ptr<T, 256, false, 1, false, false>(nreg);
+            return use_lds ? tile_kernel_ptr<T, 256, STEADY, true, 1, false, false>(nreg)
+                           : tile_kernel_ptr<T, 256, STEADY, false, 1, false, false>(nreg);
     } else {
         if (acc || align) return nullptr;
     }
     if (use_lds)
-        return nt != 0 ? tile_kernel_ptr<T, THREADS, true, 2, false, false>(nreg)
-                       : tile_kernel_ptr<T, THREADS, true, 0, false, false>(nreg);
-    return nt != 0 ? tile_kernel_ptr<T, THREADS, false, 2, false, false>(nreg)
-                   : tile_kernel_ptr<T, THREADS, false, 0, false, false>(nreg);
+        return nt != 0 ? tile_kernel_ptr<T, THREADS, STEADY, true, 2, false, false>(nreg)
+                       : tile_kernel_ptr<T, THREADS, STEADY, true, 0, false, false>(nreg);
+    return nt != 0 ? tile_kernel_ptr<T, THREADS, STEADY, false, 2, false, false>(nreg)
+                   : tile_kernel_ptr<T, THREADS, STEADY, false, 0, false, false>(nreg);
 }
 
 }  // namespace tperm

@@ -195,6 +195,25 @@ constexpr bool tile_form_with_tables(int nreg, int threads, bool use_lds, bool a
     return use_lds && threads == 256 && !align && !loads_first && !big && nreg >= 3;
 }
 
+// Whether a kernel of the tile family has the code by which workgroups change places from round to round (set_turns in
+// plan.cpp).  The others keep their places.  Sixteen slots of 8 bytes with masks: the scalars that turns keep over
+// the loop push others out to lanes of a vector register, which come back between the last stores and the next loads;
+// tiles of three dims and more lose 2 to 9 % to that even where no places change (14 x 56 x 146 x 78 x 11, index
+// order 4 2 0 1 3: 311 us at first, 323 with turns, 297 without); 25 seeded tensors of 80 to 400 us: 1.015 (0.99, 1.09).
+constexpr bool tile_form_with_turns(int elem, int nreg, bool use_lds, bool align, bool vec2, bool lean) {
+    return use_lds && !align && !(elem == 8 && nreg == 16 && !vec2 && !lean);
+}
+
+// Forms of which there is a kernel without that code besides, for launches in which no places change.  Such kernels take
+// 2 to 9 us, and the code costs 30 to 100 ns of that: five scalar instructions in front of the first tile's position, and two
+// more scalars, for which the compiler fetched the pointers in a second round trip to the kernel arguments.  238 seeded
+// tensors of up to 75 MB, time with that code / without (least, most): 1 slot 1.012 (0.99, 1.05), 2 slots 1.020 (1.00, 1.04),
+// 3 slots 1.011 (1.00, 1.03), 4 slots 1.007 (1.00, 1.03); 10 x 14 x 14 x 14 x 14 of 8-byte elements 4.83 / 4.64 us.  Five slots
+// 1.000 (8 tensors).
+constexpr bool tile_form_with_steady_twin(int nreg, int threads, bool use_lds, bool align, bool big) {
+    return use_lds && threads == 256 && !align && !big && nreg <= 4;
+}
+
 // Per-thread, per-slot minor position for the read side (Eq. (4) and the LDS store slot).
 // k is the position inside the tile in input order.  xa/xb are the coordinates along the
 // split dims, used to mask ragged edge tiles.
