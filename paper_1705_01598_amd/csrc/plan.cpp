@@ -1047,7 +1047,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
     if (plan->spare && !padded) ++lds_elems;
     d.lds_elems = lds_elems;
     d.lds_buffers = (cand.use_lds && lds_buffers == 2 && (int64_t)lds_elems * elem * 2 <= kMaxLdsBytes) ? 2u : 1u;
-    plan->tables = tile_form_with_tables(nreg_final, threads, cand.use_lds, align_out, false, opts.big) && set_tables(&d, nreg_final);
+    plan->tables = tile_form_with_tables(elem, nreg_final, threads, cand.use_lds, align_out, false, false, opts.big) && set_tables(&d, nreg_final);
     plan->tile = d;
     plan->cand = cand;
     plan->kclass = cand.kclass;

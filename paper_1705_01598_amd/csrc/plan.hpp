@@ -125,7 +125,8 @@ void set_turns(const Plan& plan, uint32_t grid, bool accumulate, TileDesc* d);
 
 // The kernel that runs the plan takes its positions from tables.
 inline bool runs_with_tables(const Plan& p, bool accumulate) {
-    return p.tables && tile_form_with_tables(p.nreg, p.threads, p.use_lds, p.align_out, p.loads_first && !accumulate, p.big);
+    return p.tables && tile_form_with_tables(p.elem, p.nreg, p.threads, p.use_lds, p.align_out, accumulate,
+                                             p.loads_first && !accumulate, p.big);
 }
 
 // The kernel that runs the plan has no code for turns although the form has (see tile_form_with_steady_twin).

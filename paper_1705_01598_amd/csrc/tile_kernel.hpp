@@ -268,7 +268,7 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
     // not instantiated.  Hence without masks: 32 slots, and 24 of 8-byte elements, always; 24 of
     // 4-byte elements accumulating below 4 GiB; and the LEAN variants for small tensors.
     constexpr bool NO_MASKS = tile_form_without_masks((int)sizeof(T), NREG, THREADS, USE_LDS, ALIGN, ACC, VEC2, BIG, LEAN);
-    static_assert(!TAB || tile_form_with_tables(NREG, THREADS, USE_LDS, ALIGN, LOADS_FIRST, BIG), "no positions from tables in this form");
+    static_assert(!TAB || tile_form_with_tables((int)sizeof(T), NREG, THREADS, USE_LDS, ALIGN, ACC, LOADS_FIRST, BIG), "no positions from tables in this form");
     static_assert(!LEAN || NO_MASKS, "the lean form is a plain LDS-staged one of 256 threads");
     typedef typename std::conditional<sizeof(T) == 4, uint64_t, Pair64>::type pair_t;
     typedef Elem<typename std::conditional<VEC2, pair_t, T>::type, NT> io;
@@ -818,6 +818,12 @@ static const void* tile_kernel_tab_ptr(int nreg) {
             TPERM_CASE(3)
             TPERM_CASE(4)
             TPERM_CASE(24)
+            default:
+                break;
+        }
+    }
+    if constexpr (!LEAN && !(ACC && sizeof(T) == 4)) {
+        switch (nreg) {
             TPERM_CASE(32)
             default:
                 break;

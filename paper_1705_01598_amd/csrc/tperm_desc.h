@@ -191,8 +191,13 @@ constexpr bool tile_form_without_masks(int elem, int nreg, int threads, bool use
 // they never pay, and not in line-aligned windows, whose tiles have two or three dims and whose registers
 // come out worse with them (a 13953 x 13953 matrix of 4-byte elements 292 -> 314 us).  A kernel of its own: one
 // that chose at run time cost tiles of two dims 1 % (up to 4).
-constexpr bool tile_form_with_tables(int nreg, int threads, bool use_lds, bool align, bool loads_first, bool big) {
-    return use_lds && threads == 256 && !align && !loads_first && !big && nreg >= 3;
+// Nor 32 slots of 4-byte elements when accumulating: with tables the kernel takes 511 registers and spills, without 322
+// (one workgroup per compute unit either way), and 30 seeded tensors of 80 to 490 us are 1.08 (1.01, 1.22) times as fast without
+// (248 x 23 x 13 x 15 x 107, index order 4 1 2 0 3: 444 / 369 us).  Accumulating with other counts gains by tables: 24 slots
+// of 4-byte elements 1.024 (1.00, 1.10), 24 and 32 of 8-byte elements 1.003 and 1.034 (0.99, 1.16), fewer slots 1.023 (0.98, 1.25;
+// 220 tensors).  Not accumulating, 32 slots of 4-byte elements are level, 1.002 (0.96, 1.05; 69 tensors).
+constexpr bool tile_form_with_tables(int elem, int nreg, int threads, bool use_lds, bool align, bool acc, bool loads_first, bool big) {
+    return use_lds && threads == 256 && !align && !loads_first && !big && nreg >= 3 && !(acc && elem == 4 && nreg == 32);
 }
 
 // Whether a kernel of the tile family has the code by which workgroups change places from round to round (set_turns in

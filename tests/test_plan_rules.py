@@ -119,3 +119,14 @@ def test_a_launch_asks_for_the_lds_of_the_kernel_that_runs(elem):
     assert B.tperm_plan_launch_info(plan(lds_buffers=2, loads_first=2)).lds_bytes == 2 * image
     with pytest.raises(B.TpermError):
         B.tperm_plan_launch_info(B.tperm_plan_create((8, 8), (0, 1), elem))    # a copy has no tiles
+
+
+@pytest.mark.parametrize("tile_out,slots", [(9, 6), (37, 24), (43, 32)])
+@pytest.mark.parametrize("elem", [4, 8])
+def test_accumulating_32_slots_of_4_byte_elements_take_no_tables(tile_out, slots, elem):
+    """They lose 8 % by them (up to 22); every other count and the 8-byte form keep theirs."""
+    plan = B.tperm_plan_create_ex((31, 16, 7, 5, 2 * tile_out - 1), (4, 3, 0, 2, 1), elem, kernel_class=B.KERNEL_PACKED, m=2, tile_in=5,
+                                  k=1, tile_out=tile_out, align_out=1, vec2=1, pair_elems=1)
+    assert plan.describe().nreg == slots
+    for acc in (False, True):
+        assert B.tperm_plan_launch_info(plan, accumulate=acc).tables == int(not (acc and elem == 4 and slots == 32))
