@@ -615,7 +615,7 @@ static uint32_t set_lds_strides(TileDesc* d, const int* dim_of_in, const int* di
 // index order reversed 267 -> 262 us, 8192 x 8192 200 -> 196); gcd(grid, product of the first two counters) of 8 and more 1.03
 // (0.98, 1.17).  The others 0.996 (0.97, 1.02): there the workgroups drift apart anyway, and neighbours share fewer lines.
 // Row copies gain and lose 2 %; line-aligned windows have no registers for it (13953 x 13953 of 4-byte elements +1 %),
-// nor has one form of sixteen slots (tile_form_with_turns).
+// nor has one form of sixteen slots, and 24 slots of 8 bytes lose (tile_form_with_turns).
 // Below twelve rounds it gains and loses alike (67 MB of 4-byte elements in 8 and 10.7 rounds: 0.94 to 1.07).
 constexpr uint32_t kTurnRounds = 12;
 void set_turns(const Plan& plan, uint32_t grid, bool accumulate, TileDesc* d) {

@@ -205,8 +205,11 @@ constexpr bool tile_form_with_tables(int elem, int nreg, int threads, bool use_l
 // the loop push others out to lanes of a vector register, which come back between the last stores and the next loads;
 // tiles of three dims and more lose 2 to 9 % to that even where no places change (14 x 56 x 146 x 78 x 11, index
 // order 4 2 0 1 3: 311 us at first, 323 with turns, 297 without); 25 seeded tensors of 80 to 400 us: 1.015 (0.99, 1.09).
+// 24 slots of 8 bytes lose by the turns themselves, in place / changing places 0.990 over 36 tensors of 125 to 410 us (0.95,
+// 1.11), 0.988 over 22 accumulating ones (0.94, 1.03); the other counts gain or are level (24 slots of 4 bytes 1.001 over 72, 32 slots
+// 1.015 over 66, the rest 1.013 over 218).
 constexpr bool tile_form_with_turns(int elem, int nreg, bool use_lds, bool align, bool vec2, bool lean) {
-    return use_lds && !align && !(elem == 8 && nreg == 16 && !vec2 && !lean);
+    return use_lds && !align && !(elem == 8 && ((nreg == 16 && !vec2 && !lean) || nreg == 24));
 }
 
 // Forms of which there is a kernel without that code besides, for launches in which no places change.  Such kernels take
