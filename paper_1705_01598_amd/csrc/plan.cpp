@@ -645,7 +645,7 @@ static bool set_tables(TileDesc* d, int nreg) {
     int64_t entries = 0;
     for (int side = 0; side < 2; ++side) {
         const TileDim* dims = side == 0 ? d->in_order : d->out_order;
-        const int64_t vol = side == 1 && d->oa.line_elems != 0u ? d->oa.total_slots : d->tile_vol;
+        const int64_t vol = d->tile_vol;
         PosTable best{0, 0};
         int64_t least = 0, low = 1;
         for (uint32_t s = 1; s <= d->n_tile_dims; ++s) {
@@ -905,7 +905,7 @@ tperm_status_t build_tile_plan(Plan* plan, const Candidate& cand, const TileBuil
 
     std::memset(&d.oa, 0, sizeof(d.oa));
     if (align_out) {
-            d.oa.line_elems = (uint32_t)line_elems;
+        d.oa.line_elems = (uint32_t)line_elems;
         d.oa.total_slots = (uint32_t)cand.tile_vol;
         d.oa.in_halo_elems = (uint32_t)(line_elems * sI[q0]);
     }
@@ -1339,12 +1339,11 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
         for (int side = 0; side < 2; ++side) {
             const PosTable& t = d.table[side];
             const TileDim* dims = side == 0 ? d.in_order : d.out_order;
-            const uint32_t vol = side == 1 && d.oa.line_elems ? d.oa.total_slots : d.tile_vol;
             for (uint32_t k = 0; k < slots; ++k) {
                 uint32_t low, high;
                 pos_entries_of(t, k, &low, &high);
                 if (low >= t.low() || high < t.low() || high - t.low() >= t.high()) return TPERM_ERR_INTERNAL;
-                if (k >= vol) continue;
+                if (k >= d.tile_vol) continue;
                 const PosEntry a = pos_entry(dims, 0u, t.split(), low), b = pos_entry(dims, t.split(), d.n_tile_dims, high - t.low());
                 const Slot s = tile_slot(dims, d.n_tile_dims, k);
                 if (a.goff + b.goff != s.goff || a.loff + b.loff != s.loff || a.coord + b.coord != (s.xa | s.xb << 16)) return TPERM_ERR_INTERNAL;

@@ -773,10 +773,16 @@ static const void* tile_kernel_ptr(int nreg) {
         TPERM_CASE(8)
         TPERM_CASE(12)
         TPERM_CASE(16)
-        TPERM_CASE(24)
-        TPERM_CASE(32)
         default:
             break;
+    }
+    if constexpr (!VEC2) {  // a tile has at most 8192 elements: 16 pairs per thread
+        switch (nreg) {
+            TPERM_CASE(24)
+            TPERM_CASE(32)
+            default:
+                break;
+        }
     }
     if constexpr (THREADS == 256) {
         switch (nreg) {
@@ -820,12 +826,19 @@ static const void* tile_kernel_tab_ptr(int nreg) {
         switch (nreg) {
             TPERM_CASE(3)
             TPERM_CASE(4)
+            default:
+                break;
+        }
+    }
+    if constexpr (!LEAN && !VEC2) {
+        switch (nreg) {
+            TPERM_CASE(5)
             TPERM_CASE(24)
             default:
                 break;
         }
     }
-    if constexpr (!LEAN && !(ACC && sizeof(T) == 4)) {
+    if constexpr (!LEAN && !VEC2 && !(ACC && sizeof(T) == 4)) {
         switch (nreg) {
             TPERM_CASE(32)
             default:
@@ -835,13 +848,6 @@ static const void* tile_kernel_tab_ptr(int nreg) {
     if constexpr (LEAN && sizeof(T) == 4) {
         switch (nreg) {
             TPERM_CASE(24)
-            default:
-                break;
-        }
-    }
-    if constexpr (!LEAN && !VEC2) {
-        switch (nreg) {
-            TPERM_CASE(5)
             default:
                 break;
         }
