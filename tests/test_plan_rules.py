@@ -132,13 +132,13 @@ def test_accumulating_32_slots_of_4_byte_elements_take_no_tables(tile_out, slots
         assert B.tperm_plan_launch_info(plan, accumulate=acc).tables == int(not (acc and elem == 4 and slots == 32))
 
 
-@pytest.mark.parametrize("elem,t0,t1,align_out", [(4, 128, 64, 1), (8, 90, 90, 1), (4, 64, 96, 2)])
-def test_largest_tiles_of_pairs_have_16_slots(elem, t0, t1, align_out):
+@pytest.mark.parametrize("elem,t0,t1,align_out,slots", [(4, 128, 64, 1, 16), (8, 64, 90, 1, 12), (4, 64, 96, 2, 16)])
+def test_largest_tiles_of_pairs_have_16_slots(elem, t0, t1, align_out, slots):
     """A tile has at most 8192 elements, with the halo of line-aligned windows; larger slot counts are not instantiated for pairs."""
     def info(t1):
         return B.tperm_plan_create_ex((3 * t0, 5, 4 * t1), (2, 1, 0), elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=t0, k=1, tile_out=t1,
                                       align_out=align_out, vec2=2).describe()
     i = info(t1)
-    assert (i.nreg, i.vec2, i.align_out) == (16, 1, align_out - 1)
+    assert (i.nreg, i.vec2, i.align_out) == (slots, 1, align_out - 1)
     with pytest.raises(B.TpermError):
         info(t1 + 32)
