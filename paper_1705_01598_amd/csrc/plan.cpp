@@ -1329,7 +1329,7 @@ static tperm_status_t index_map_at_phase(const Plan& plan, int64_t* out_to_in, u
         if (runs_without_masks(plan, acc) && slots > d.tile_vol && !plan.spare) return TPERM_ERR_INTERNAL;
     // visit tiles the way a launch with `grid` workgroups would; any grid gives the same
     // set of tiles, use a small one that still exercises the iteration arithmetic
-    const uint32_t grid = d.num_tiles >= kTurnRounds * 96u ? 96u : (d.grid_mode != 0u ? 16u : 7u);
+    const uint32_t grid = d.num_tiles > (kTurnRounds - 1u) * 96u ? 96u : (d.grid_mode != 0u ? 16u : 7u);
     TileDesc launched = d;
     set_turns(plan, grid, false, &launched);
     std::vector<char> tile_seen(d.num_tiles, 0);

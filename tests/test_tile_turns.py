@@ -8,25 +8,30 @@ import oracle
 from paper_1705_01598_amd import binding as B
 
 
-@pytest.mark.parametrize("rows", [12 * 96 * 16, 12 * 96 * 16 + 1, 13 * 96 * 16 - 16, 20 * 96 * 16 + 95 * 16, 12 * 96 * 16 - 16])
-@pytest.mark.parametrize("kw", [dict(), dict(grid_mode=-1), dict(grid_mode=1), dict(grid_mode=3), dict(cache_policy=2)],
+@pytest.mark.parametrize("rows,turns", [(12 * 96 * 16, 88), (12 * 96 * 16 + 1, 88), (13 * 96 * 16 - 16, 88), (20 * 96 * 16 + 95 * 16, 88),
+                                        (12 * 96 * 16 - 16, 88), (11 * 96 * 16 + 1, 88), (11 * 96 * 16, 0)])
+@pytest.mark.parametrize("kw", [dict(), dict(grid_mode=-1), dict(grid_mode=1), dict(grid_mode=3)],
                          ids=lambda k: "-".join("%s%s" % x for x in k.items()) or "default")
-def test_every_tile_once_when_workgroups_change_places(rows, kw):
+def test_every_tile_once_when_workgroups_change_places(rows, turns, kw):
     for elem in (4, 8):
         dims, perm = (16, rows), (1, 0)                         # a single counter of rows / 16 tiles, and more
-        tile_out = 128 // elem if kw.get("align_out") == 2 else 16
-        plan = B.tperm_plan_create_ex(dims, perm, elem, kernel_class=B.KERNEL_TILED, m=1, tile_in=16, k=1, tile_out=tile_out, vec2=1,
-                                      **{**dict(align_out=1), **kw})
-        assert plan.describe().num_tiles == -(-rows // tile_out)
+        plan = B.tperm_plan_create_ex(dims, perm, elem, kernel_class=B.KERNEL_TILED, m=1, tile_in=16, k=1, tile_out=16, vec2=1, align_out=1, **kw)
+        assert plan.describe().num_tiles == -(-rows // 16)
+        assert B.tperm_plan_launch_info(plan, workgroups=96).turns == turns
         ref = oracle.transpose(np.arange(16 * rows, dtype=np.int64), dims, perm)
         assert np.array_equal(B.tperm_plan_index_map(plan), ref)
 
 
 @pytest.mark.parametrize("elem", [4, 8])
-def test_every_tile_once_under_counters_in_step_with_the_grid(elem):
-    dims, perm = (9, 4, 6, 5, 70), (3, 1, 4, 2, 0)
-    plan = B.tperm_plan_create_ex(dims, perm, elem, kernel_class=B.KERNEL_PACKED, m=1, tile_in=5, k=1, tile_out=2, align_out=1)
+@pytest.mark.parametrize("dims,perm,m,tile_in,k,tile_out,turns", [
+    ((4, 9, 11, 108, 13), (4, 1, 0, 2, 3), 2, 5, 2, 5, 88),      # counters 2 and 1188: gcd(96, 2376) = 24
+    ((9, 4, 6, 5, 70), (3, 1, 4, 2, 0), 1, 5, 1, 2, 0),          # 2 and 3: gcd(96, 6) = 6 is below 8
+])
+def test_every_tile_once_under_counters_in_step_with_the_grid(dims, perm, m, tile_in, k, tile_out, turns, elem):
+    plan = B.tperm_plan_create_ex(dims, perm, elem, kernel_class=B.KERNEL_PACKED, m=m, tile_in=tile_in, k=k, tile_out=tile_out, align_out=1,
+                                  vec2=1)
     assert plan.describe().num_tiles >= 12 * 96
+    assert B.tperm_plan_launch_info(plan, workgroups=96).turns == turns
     ref = oracle.transpose(np.arange(int(np.prod(dims)), dtype=np.int64), dims, perm)
     assert np.array_equal(B.tperm_plan_index_map(plan), ref)
 
