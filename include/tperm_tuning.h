@@ -123,7 +123,7 @@ tperm_status_t tperm_plan_model(tperm_plan_t plan, tperm_model_t *model);
 
 /* How a launch of the plan with `workgroups` workgroups runs, beyond what tperm_plan_describe says (the plan
  * that it describes, or with accumulate != 0 the one that accumulates).  Host only; plans of the copy and naive
- * classes and workgroups < 1 give TPERM_ERR_KERNEL.  The layout may grow between versions. */
+ * classes, plans that cannot accumulate and workgroups < 1 give TPERM_ERR_KERNEL.  The layout may grow between versions. */
 typedef struct {
     int tables;      /* 1: positions inside a tile come from tables that a workgroup fills in its LDS first */
     int lds_bytes;   /* LDS a workgroup asks for: the image or images of tperm_plan_info_t.lds_bytes, or the *

@@ -477,6 +477,7 @@ tperm_status_t tperm_plan_launch_info(tperm_plan_t plan, int accumulate, int wor
     const Plan& p = plan->wide.p && accumulate == 0 ? *plan->wide.p : *plan->base.p;
     std::memset(info, 0, sizeof(*info));
     if (workgroups < 1 || p.kclass == TPERM_KERNEL_COPY || p.kclass == TPERM_KERNEL_NAIVE) return TPERM_ERR_KERNEL;
+    if (accumulate != 0 && (p.vec2 || p.threads != 256)) return TPERM_ERR_KERNEL;  // as when it is executed
     tperm::TileDesc d = p.tile;
     tperm::set_turns(p, (uint32_t)workgroups, accumulate != 0, &d);
     info->tables = tperm::runs_with_tables(p, accumulate != 0) ? 1 : 0;

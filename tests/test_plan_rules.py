@@ -119,6 +119,9 @@ def test_a_launch_asks_for_the_lds_of_the_kernel_that_runs(elem):
     assert B.tperm_plan_launch_info(plan(lds_buffers=2, loads_first=2)).lds_bytes == 2 * image
     with pytest.raises(B.TpermError):
         B.tperm_plan_launch_info(B.tperm_plan_create((8, 8), (0, 1), elem))    # a copy has no tiles
+    with pytest.raises(B.TpermError):
+        B.tperm_plan_launch_info(B.tperm_plan_create_ex((64, 640), (1, 0), elem, vec2=2, align_out=1, tile_in=32, tile_out=32, m=1, k=1,
+                                                        kernel_class=B.KERNEL_TILED), accumulate=True)
 
 
 @pytest.mark.parametrize("tile_out,slots", [(9, 6), (37, 24), (43, 32)])
