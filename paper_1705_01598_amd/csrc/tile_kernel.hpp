@@ -358,9 +358,12 @@ tile_kernel(const TileDesc d, const T* __restrict__ in_arg, T* __restrict__ out_
         return PosEntry{a.goff + b.goff, a.loff + b.loff, a.coord + b.coord, 0u};
     };
     // 24 slots: a look-up's results are settled at once, and four slots looked up at a time.  Left to itself the
-    // compiler has all look-ups in flight and keeps what it derives from them for the loop: 278 registers, one
-    // workgroup per compute unit; settled 182, two (a ragged rank-12 tensor of 4-byte elements, 157 MB, 78.8 -> 72.8 us).
-    // Other counts lose by it, up to 12 slots 2 to 7 %, 32 slots 15 % (two workgroups of 29 KB tiles instead of one).
+    // compiler has all look-ups in flight and keeps what it derives from them for the loop: 278 registers (4-byte elements without
+    // masks; 302 of 8 bytes), one workgroup per compute unit; settled 182 (251), two (a ragged rank-12 tensor of 4-byte elements,
+    // 157 MB, 78.8 -> 72.8 us).  Up to 12 slots lose 2 to 7 % by it.  32 slots of 4-byte elements come down from 441 registers to 239,
+    // and two workgroups fit: 49 tensors of 52 to 460 us run 1.04 times as fast on average, but between 0.89 (231 x 23 x 62 x 11 x 37,
+    // index order 3 1 4 2 0: 244 / 273 us) and 1.44, and nothing in the plan was found to tell them apart; held at one workgroup
+    // both take the same, 1.002 (30 tensors).
     constexpr bool SETTLE = NREG == 24;
     auto settle = [](int j, uint32_t& off, uint32_t& mask, uint32_t& at) {
         if (!SETTLE) return;
