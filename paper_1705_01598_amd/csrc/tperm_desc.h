@@ -195,7 +195,8 @@ constexpr bool tile_form_without_masks(int elem, int nreg, int threads, bool use
 // (one workgroup per compute unit either way), and 30 seeded tensors of 80 to 490 us are 1.08 (1.01, 1.22) times as fast without
 // (248 x 23 x 13 x 15 x 107, index order 4 1 2 0 3: 444 / 369 us).  Accumulating with other counts gains by tables: 24 slots
 // of 4-byte elements 1.024 (1.00, 1.10), 24 and 32 of 8-byte elements 1.003 and 1.034 (0.99, 1.16), fewer slots 1.023 (0.98, 1.25;
-// 220 tensors).  Not accumulating, 32 slots of 4-byte elements are level, 1.002 (0.96, 1.05; 69 tensors).
+// 220 tensors).  Not accumulating, 32 slots of 4-byte elements are level, 1.002 (0.96, 1.05; 69 tensors),
+// 24 and 32 of 8-byte elements gain, 1.035 (0.98, 1.26) and 1.015 (0.97, 1.20; 18 tensors each), although they take up to 512 registers.
 constexpr bool tile_form_with_tables(int elem, int nreg, int threads, bool use_lds, bool align, bool acc, bool loads_first, bool big) {
     return use_lds && threads == 256 && !align && !loads_first && !big && nreg >= 3 && !(acc && elem == 4 && nreg == 32);
 }
