@@ -209,8 +209,11 @@ constexpr bool tile_form_with_tables(int elem, int nreg, int threads, bool use_l
 // 24 slots of 8 bytes lose by the turns themselves, in place / changing places 0.990 over 36 tensors of 125 to 410 us (0.95,
 // 1.11), 0.988 over 22 accumulating ones (0.94, 1.03); the other counts gain or are level (24 slots of 4 bytes 1.001 over 72, 32 slots
 // 1.015 over 66, the rest 1.013 over 218).
+// Kernels for small tensors of up to 16 slots (lean): those make at most 11 rounds (711 seeded tensors up to 40 MB), and with the code for
+// turns 226 of 5 to 25 us take 1.010 times as long: 6 to 16 slots without tables 1.007 (0.99, 1.02), with tables 1.012 (0.99, 1.04);
+// 57 x 83 x 42 x 11 of 4-byte elements, index order 1 0 3 2: 8.07 / 7.91 us.
 constexpr bool tile_form_with_turns(int elem, int nreg, bool use_lds, bool align, bool vec2, bool lean) {
-    return use_lds && !align && !(elem == 8 && ((nreg == 16 && !vec2 && !lean) || nreg == 24));
+    return use_lds && !align && !(lean && nreg <= 16) && !(elem == 8 && ((nreg == 16 && !vec2 && !lean) || nreg == 24));
 }
 
 // Forms of which there is a kernel without that code besides, for launches in which no places change.  Such kernels take

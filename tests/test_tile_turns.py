@@ -40,14 +40,15 @@ def test_every_tile_once_under_counters_in_step_with_the_grid(dims, perm, m, til
 @pytest.mark.parametrize("slots", [1, 2, 3, 4, 6, 24])
 def test_launches_that_keep_places_run_without_the_code_for_turns(slots, elem):
     """Up to four slots, below twelve rounds.  Not row copies, which never had that code; 24 slots of 8 bytes keep
-    their places at any number of rounds."""
+    their places at any number of rounds, and so do small tensors of 6 to 16 slots, which run without masks."""
     def info(tiles, kind=B.KERNEL_TILED, **kw):
         plan = B.tperm_plan_create_ex((16, 16 * slots * tiles), (1, 0), elem, kernel_class=kind, m=1, tile_in=16, k=1, tile_out=16 * slots,
-                                      **{**dict(align_out=1, vec2=1), **kw})
+                                      **{**dict(align_out=1, vec2=1, loads_first=1), **kw})
         assert plan.describe().nreg == slots
         i = B.tperm_plan_launch_info(plan, workgroups=256)
         return i.turns, i.steady
     assert info(11 * 256) == (0, int(slots <= 4))
-    assert info(11 * 256 + 1) == ((0, 0) if slots == 24 and elem == 8 else (88, 0))
+    assert info(11 * 256 + 1) == ((0, 0) if slots == 6 or (slots, elem) == (24, 8) else (88, 0))
+    assert info(40 * 256) == ((0, 0) if (slots, elem) == (24, 8) else (88, 0))      # 6 slots: above 40 MB, with masks
     row = B.tperm_plan_create((512 * 16, 3, 100), (0, 2, 1), elem)
     assert row.describe().kernel_class == B.KERNEL_ROWCOPY and B.tperm_plan_launch_info(row, workgroups=256).steady == 0
