@@ -616,7 +616,8 @@ static uint32_t set_lds_strides(TileDesc* d, const int* dim_of_in, const int* di
 // (0.98, 1.17).  The others 0.996 (0.97, 1.02): there the workgroups drift apart anyway, and neighbours share fewer lines.
 // Row copies gain and lose 2 %; line-aligned windows have no registers for it (13953 x 13953 of 4-byte elements +1 %),
 // nor has one form of sixteen slots, and 24 slots of 8 bytes lose (tile_form_with_turns).
-// Below twelve rounds it gains and loses alike (67 MB of 4-byte elements in 8 and 10.7 rounds: 0.94 to 1.07).
+// Below twelve rounds it gains and loses alike (67 MB of 4-byte elements in 8 and 10.7 rounds: 0.94 to 1.07).  On tensors of 25 to 250 MB alone
+// it is nearly so from twelve to twenty, 1.002 (0.93, 1.09; 114 tensors), and gains from 21 on, 1.010 (0.98, 1.14; 116).
 constexpr uint32_t kTurnRounds = 12;
 void set_turns(const Plan& plan, uint32_t grid, bool accumulate, TileDesc* d) {
     d->turns = 0u;
